@@ -14,6 +14,7 @@
 // that the fragment reads are free of bank conflicts.  For small M (decode) the K range is split
 // across workgroups; the fp32 partials are summed by the kernel that consumes the projection, or
 // by a reduce kernel that applies the epilogue.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -38,7 +39,9 @@ struct GemmParams {
   int M, N_store, epilogue, out_f32, res_f32;
   int k_tiles_total, k_tiles_per_split, splits;
   int tiles_m, tiles_n;
-  int sb_m, sb_n, n_sb_n, n_sb;  // super-blocks of sb_m x sb_n tiles (at most one XCD's worth, 32)
+  // order of the tiles, see gemm_tile_of_block: bands of band_h + 1 (the first n_tall) or band_h rows of tiles; an
+  // XCD takes `chunks` runs of `chunk` tiles, and an eighth of the `rest` tiles behind them
+  int band_h, n_tall, chunk, chunks, rest;
 };
 
 // silu(z) = z / (1 + e^-z), with the hardware reciprocal (1 ulp) in place of an IEEE division: the
@@ -122,13 +125,14 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmParams& p, f32x4 (&acc
 template <int AT, int WT>
 __device__ __forceinline__ void gemm_epilogue16_residual(const GemmParams& p, f32x4 (&acc)[WT][AT], int row0,
                                                          int col0, int l16, int kq) {
-  constexpr int AB = AT >= 4 ? 4 : AT;  // row blocks per batch
+  constexpr int AB = AT > 4 ? (AT + 1) / 2 : AT;  // row blocks per batch
   const int n_last = p.N_store - 4;
 #pragma unroll
   for (int a0 = 0; a0 < AT; a0 += AB) {
     f32x4 r[AB][WT];
 #pragma unroll
     for (int ab = 0; ab < AB; ++ab) {
+      if (a0 + ab >= AT) break;
       const int m = min(row0 + (a0 + ab) * 16 + l16, p.M - 1);
 #pragma unroll
       for (int wt = 0; wt < WT; ++wt) {
@@ -143,6 +147,7 @@ __device__ __forceinline__ void gemm_epilogue16_residual(const GemmParams& p, f3
     }
 #pragma unroll
     for (int ab = 0; ab < AB; ++ab) {
+      if (a0 + ab >= AT) break;
       const int m = row0 + (a0 + ab) * 16 + l16;
 #pragma unroll
       for (int wt = 0; wt < WT; ++wt) {
@@ -163,22 +168,44 @@ __device__ __forceinline__ void gemm_epilogue16_residual(const GemmParams& p, f3
   }
 }
 
-// Workgroup -> (tile_m, tile_n, split).  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2, so the workgroups an XCD runs at once are given one compact sb_m x sb_n block
-// of tiles: they then share sb_m activation panels and sb_n weight panels in that L2.  Super-blocks
-// are numbered split-major, so with split-K an XCD also keeps to one K range.
+// Workgroup -> (tile_m, tile_n, split).  The tiles are put in one order - by split, by band of up to four rows of
+// tiles, and inside a band column by column - so that any run of consecutive tiles is a compact block: the
+// workgroups that make it share a band's activation panels and as few weight panels as there can be.
+// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: an XCD takes runs of as many
+// tiles as it has slots, the eight XCDs' runs side by side, and what is left is divided evenly.  Every
+// workgroup but the last few of the grid has a tile.  (An earlier numbering gave an XCD rectangles of tiles whose
+// corners could lie outside the matrix: the workgroups that found nothing to do sat at regular ids, and
+// as the dispatcher hands out ids to the four shader engines of an XCD in turn, two of them got all the
+// work: with three or six rows of tiles a launch took twice its time, 121 us against 61 at M = 384 on 10240 x 8192.)
 __device__ __forceinline__ bool gemm_tile_of_block(const GemmParams& p, int& tile_m, int& tile_n, int& split) {
   const int xcd = blockIdx.x & 7;
-  const int local = blockIdx.x >> 3;
-  const int sb_size = p.sb_m * p.sb_n;
-  const int sb_global = (local / sb_size) * 8 + xcd;
-  if (sb_global >= p.n_sb * p.splits) return false;
-  split = sb_global / p.n_sb;
-  const int sb = sb_global % p.n_sb;
-  const int within = local % sb_size;
-  tile_m = (sb / p.n_sb_n) * p.sb_m + within % p.sb_m;
-  tile_n = (sb % p.n_sb_n) * p.sb_n + within / p.sb_m;
-  return tile_m < p.tiles_m && tile_n < p.tiles_n;
+  int local = blockIdx.x >> 3;
+  int t;
+  if (local < p.chunks * p.chunk) {
+    t = (local / p.chunk * 8 + xcd) * p.chunk + local % p.chunk;
+  } else {
+    local -= p.chunks * p.chunk;
+    const int q = p.rest >> 3, r = p.rest & 7;
+    if (local >= q + (xcd < r ? 1 : 0)) return false;
+    t = p.chunks * p.chunk * 8 + xcd * q + min(xcd, r) + local;
+  }
+  split = t / (p.tiles_m * p.tiles_n);
+  t -= split * (p.tiles_m * p.tiles_n);
+  const int tall = (p.band_h + 1) * p.tiles_n, low = p.band_h * p.tiles_n;  // tiles per band
+  int h = p.band_h + 1;
+  tile_m = 0;
+  if (t < p.n_tall * tall) {
+    tile_m = t / tall * h;
+    t %= tall;
+  } else {
+    t -= p.n_tall * tall;
+    h = p.band_h;
+    tile_m = p.n_tall * (p.band_h + 1) + t / low * h;
+    t %= low;
+  }
+  tile_n = t / h;
+  tile_m += t % h;
+  return true;
 }
 
 // The same pipeline on v_mfma_f32_16x16x32_bf16: a stage of 32 k is exactly one MFMA k-step, a wave
@@ -197,10 +224,12 @@ __device__ __forceinline__ bool gemm_tile_of_block(const GemmParams& p, int& til
 // shapes; the one exception that pays is two tile rows on a wide projection without split-K (gate/up at
 // M = 512: the two readers of a weight tile are neighbours in one super-block and run at the same time,
 // so the second read still finds the line): -1.8 %.
-template <int BM, int NS, int TM, int TN, int BN = 256, bool WNT = false>
-__global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_mi16_kernel(const GemmParams p) {
-  constexpr int BK = 32;
-  constexpr int WAVES_N = BN / 32 / TN, WAVES = (BM / (TM * 32)) * WAVES_N;
+//
+// A workgroup of four waves (2 x 2) makes a tile of BM = 32 AT rows x BN = 32 WT weight rows; a wave, AT x WT
+// accumulators.
+template <int AT, int WT, int NS, bool WNT>
+__global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
+  constexpr int BM = AT * 32, BN = WT * 32, BK = 32;
   constexpr int CPR = BK / 8;         // 16-byte chunks per row
   // Rows that share one swizzle value.  A fragment read of this kernel is 16 rows x 4 chunks (lane =
   // chunk * 16 + row); measured with SQ_LDS_BANK_CONFLICT on that pattern: the chunk position must
@@ -208,21 +237,22 @@ __global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_m
   // right for the 32 rows x 2 chunks of the 32x32 kernels - costs 8 cycles per read here.
   constexpr int RW = 2;
   constexpr int RPI = 64 / CPR;       // rows per DMA instruction
-  constexpr int IPA = (BM / RPI) / WAVES, IPW = (BN / RPI) / WAVES;
-  static_assert(IPA >= 1 && (BM / RPI) % WAVES == 0 && (BN / RPI) % WAVES == 0, "row blocks divide among waves");
-  constexpr int STAGE = (BM + BN) * BK;
-  constexpr int AT = TM * 2, WT = TN * 2;  // 16-row tiles per wave
+  // DMA instructions per wave and stage.  Where the 2 AT row blocks of the activations do not divide by four, the
+  // last waves request rows of the tile a second time, into ring rows that nothing reads (BMR > BM).
+  constexpr int IPA = (BM / RPI + 3) / 4, IPW = BN / RPI / 4;
+  constexpr int BMR = IPA * 4 * RPI;
+  constexpr int STAGE = (BMR + BN) * BK;
   static_assert(WT % 4 == 0, "gate/up pairing");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  bf16* smem = reinterpret_cast<bf16*>(smem_raw);  // [NS][BM + BN][BK]
+  bf16* smem = reinterpret_cast<bf16*>(smem_raw);  // [NS][BMR + BN][BK]
 
   int tile_m, tile_n, split;
   if (!gemm_tile_of_block(p, tile_m, tile_n, split)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave / WAVES_N) * (TM * 32);
-  const int wn0 = (wave % WAVES_N) * (TN * 32);
+  const int wm0 = (wave >> 1) * (AT * 16);
+  const int wn0 = (wave & 1) * (WT * 16);
   const int l16 = lane & 15;
   const int kq = lane >> 4;
   const int m0 = tile_m * BM;
@@ -249,8 +279,7 @@ __global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_m
     const int c_sw = (lane % CPR) ^ ((row / RW) % CPR);
     // rows past M are computed but never stored; they re-read the tile's valid rows in turn (all of
     // them reading the last valid row makes one hot line for every workgroup of the launch)
-    int m = row;
-    if (m0 + m > p.M - 1) m = row % (p.M - m0);
+    const int m = row % min(BM, p.M - m0);
     a_goff[j] = 2u * (unsigned)(operand_row_offset(p.a_lay, m) + c_sw * 8) + (unsigned)(kImmBias - j * 1024);
   }
   // weight rows need no clamp; the swizzle term (row / RW) % CPR does not depend on the row block j
@@ -291,7 +320,7 @@ __global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_m
   auto dma_one = [&](int j) {
     const unsigned ring = ring_base + req_slot * (STAGE * 2);
     if (j == 0) dma_aim(ring + (wave * IPA * RPI * BK) * 2);
-    if (j == IPA) dma_aim(ring + (BM * BK + wave * IPW * RPI * BK) * 2);
+    if (j == IPA) dma_aim(ring + (BMR * BK + wave * IPW * RPI * BK) * 2);
     switch (j < IPA ? j : j - IPA) {
       case 0: if (j < IPA) TDP_DMA16(a_goff[0], a_req, 0); else TDP_DMA16W(w_goff[0], w_req, 0); break;
       case 1: if (j < IPA) TDP_DMA16(a_goff[1 % IPA], a_req, 1024); else TDP_DMA16W(w_goff[1 % IPW], w_req, 1024); break;
@@ -326,11 +355,10 @@ __global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_m
   // the swizzle term is the lane's alone: one base per operand, the rest are immediate offsets.
   static_assert(16 % (RW * CPR) == 0, "swizzle repeats every 16 rows");
   const int swz = (kq ^ ((l16 / RW) % CPR)) << 3;
-  const int w_off = (BM + wn0 + l16) * BK + swz;
+  const int w_off = (BMR + wn0 + l16) * BK + swz;
   const int a_off = (wm0 + l16) * BK + swz;
   bf16x8 wf[2][WT], af[2][AT];
   constexpr int PENDING = (NS - 2) * N_DMA;
-  static_assert(N_DMA <= WT && AT <= WT && AT >= 4, "one weight tile, one DMA and at most one activation tile per MFMA group");
   int rd_slot = 0;  // ring slot of the stage whose fragments are read next
   int w_next = w_off, a_next = a_off;  // this lane's fragments in that slot (element offsets into smem)
   auto read_frags = [&](int set) {
@@ -343,60 +371,65 @@ __global__ __launch_bounds__((BM / (TM * 32)) * (BN / 32 / TN) * 64) void gemm_m
   // One stage: its fragments are in register set `set`; the next stage was requested NS-2
   // barriers ago.  The MFMAs are inline assembly so that every accumulator stays in place in its
   // AGPRs (left to itself the register allocator shuttles the 64 accumulator tuples through
-  // VGPRs); issue order is therefore explicit: eight groups of MFMAs (one weight tile each), with
-  // the fragment reads and the DMA of the stages ahead slotted in behind single MFMAs and pinned
-  // by scheduling barriers.
+  // VGPRs); issue order is therefore explicit: everything that is not an MFMA - the WT + AT fragment reads
+  // and the N_DMA requests of the stages ahead, then the stage's bookkeeping - goes behind single MFMAs, a
+  // few instructions at a time, so that it issues while the matrix pipe is busy instead of in a gap of
+  // the MFMA stream, and is pinned there by scheduling barriers.
+  constexpr int N_MFMA = AT * WT;
+  constexpr bool GROUPED = AT >= 4 && AT <= WT && N_DMA <= WT;  // a weight read, an activation read, a request per MFMA group
+  constexpr int N_OPS = WT + AT + N_DMA;
   auto stage = [&](int set) {
     // vmcnt: this wave's loads of the next stage have landed; lgkmcnt: its reads of this stage are
     // complete, so after the barrier this stage's buffer may be refilled and the next one read
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PENDING) : "memory");
 #pragma unroll
-    for (int g = 0; g < WT; ++g) {
+    for (int i = 0; i < N_MFMA; ++i) {
+      const int wt = i / AT, at = i % AT;
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[wt][at]) : "v"(wf[set][wt]), "v"(af[set][at]));
+      if constexpr (GROUPED) {
+        if (at < 3) __builtin_amdgcn_sched_barrier(0);
+        if (at == 0) wf[set ^ 1][wt] = ld_bf16x8(smem + w_next + wt * 16 * BK);
+        if (at == 1 && wt < AT) af[set ^ 1][wt] = ld_bf16x8(smem + a_next + wt * 16 * BK);
+        if (at == 2 && wt < N_DMA) dma_one(wt);
+        if (at < 3) __builtin_amdgcn_sched_barrier(0);
+      } else {
+        // operations first .. last - 1 of the list (weight reads, activation reads, requests) are this MFMA's
+        const int first = (i * N_OPS + N_MFMA - 2) / (N_MFMA - 1), last = ((i + 1) * N_OPS + N_MFMA - 2) / (N_MFMA - 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int at = 0; at < AT; ++at) {
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[g][at]) : "v"(wf[set][g]), "v"(af[set][at]));
-        // everything that is not an MFMA goes behind single MFMAs, a few instructions at a time, so
-        // that it issues while the matrix pipe is busy instead of in a gap of the MFMA stream
-        if (at == 0) {
-          __builtin_amdgcn_sched_barrier(0);
-          wf[set ^ 1][g] = ld_bf16x8(smem + w_next + g * 16 * BK);
-          __builtin_amdgcn_sched_barrier(0);
-        } else if (at == 1 && g < AT) {
-          __builtin_amdgcn_sched_barrier(0);
-          af[set ^ 1][g] = ld_bf16x8(smem + a_next + g * 16 * BK);
-          __builtin_amdgcn_sched_barrier(0);
-        } else if (at == 2 && g < N_DMA) {
-          __builtin_amdgcn_sched_barrier(0);
-          dma_one(g);
-          __builtin_amdgcn_sched_barrier(0);
+        for (int op = first; op < last && op < N_OPS; ++op) {
+          if (op < WT) wf[set ^ 1][op] = ld_bf16x8(smem + w_next + op * 16 * BK);
+          else if (op < WT + AT) af[set ^ 1][op - WT] = ld_bf16x8(smem + a_next + (op - WT) * 16 * BK);
+          else dma_one(op - WT - AT);
         }
-        // the stage's bookkeeping, behind MFMAs of the last group that carry nothing else: the
-        // request side moves on one stage, and so do the fragment offsets.  (The empty statements
-        // make the new values exist here rather than wherever their next use is.)
-        if (g == WT - 1 && at == 3) {
-          __builtin_amdgcn_sched_barrier(0);
-          ++req_t;
-          if (req_t < n_stages) {
-            a_req += a_step;
-            w_req += w_step;
-          }
-          asm volatile("" : "+s"(a_req), "+s"(w_req), "+s"(req_t));
-          __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // the bookkeeping, behind MFMAs of the last group that carry nothing else: the request side moves on one
+      // stage, and so do the fragment offsets.  (The empty statements make the new values exist here
+      // rather than wherever their next use is.)
+      if (i == (GROUPED ? (WT - 1) * AT + 3 : N_MFMA - 1)) {
+        __builtin_amdgcn_sched_barrier(0);
+        ++req_t;
+        if (req_t < n_stages) {
+          a_req += a_step;
+          w_req += w_step;
         }
-        if (g == WT - 1 && at == (AT > 4 ? 4 : 3)) {
-          __builtin_amdgcn_sched_barrier(0);
-          req_slot = req_slot + 1 == NS ? 0 : req_slot + 1;
-          rd_slot = rd_slot + 1 == NS ? 0 : rd_slot + 1;
-          asm volatile("" : "+s"(req_slot), "+s"(rd_slot));
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (g == WT - 1 && at == (AT > 5 ? 5 : 3)) {
-          __builtin_amdgcn_sched_barrier(0);
-          w_next = rd_slot * STAGE + w_off;
-          a_next = rd_slot * STAGE + a_off;
-          asm volatile("" : "+v"(w_next), "+v"(a_next));
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        asm volatile("" : "+s"(a_req), "+s"(w_req), "+s"(req_t));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (i == (GROUPED ? (WT - 1) * AT + (AT > 4 ? 4 : 3) : N_MFMA - 1)) {
+        __builtin_amdgcn_sched_barrier(0);
+        req_slot = req_slot + 1 == NS ? 0 : req_slot + 1;
+        rd_slot = rd_slot + 1 == NS ? 0 : rd_slot + 1;
+        asm volatile("" : "+s"(req_slot), "+s"(rd_slot));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (i == (GROUPED ? (WT - 1) * AT + (AT > 5 ? 5 : AT > 4 ? 4 : 3) : N_MFMA - 1)) {
+        __builtin_amdgcn_sched_barrier(0);
+        w_next = rd_slot * STAGE + w_off;
+        a_next = rd_slot * STAGE + a_off;
+        asm volatile("" : "+v"(w_next), "+v"(a_next));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -451,16 +484,37 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmParams p, in
   }
 }
 
+// Kernel variants; 1 .. kGemmTileMax can be selected by callers (GemmArgs::force_tile), the planner chooses among
+// all.  A tile has as many rows as the batch needs, in steps of 32: rows past M cost as much as real ones
+// (matrix pipe, LDS reads, power), and with tiles of 128 and 256 rows alone a batch of 307 paid for 512 (gate/up 57344 x
+// 8192: 366 us, with 2 x 160 rows 278; M = 384: 371 -> 308; M = 200: 202 -> 180).  128 weight rows per
+// tile instead of 256 where the weights are what counts (M up to 128: twice the workgroups, half the split-K
+// factor, no partials at all on many gate/up shapes; M = 48, 4096 x 4096: 22 -> 16 us, 22016 x 4096: 45 -> 39) and
+// between 160 and 256 rows on narrow projections.  The ring takes what LDS there is; two or three workgroups
+// per CU where a tile is small enough (their fill and epilogue then overlap the neighbour's stages).
 struct TileInfo {
-  int bm, bn, lds_bytes, wg_per_cu;
+  int at, wt, ns, wg_per_cu;
+  const void* kernel[2];  // ordinary / non-temporal weight requests
+  int bm() const { return at * 32; }
+  int bn() const { return wt * 32; }
+  int ring_rows() const { return (at * 2 + 3) / 4 * 64 + bn(); }  // rows of a ring stage (see IPA)
+  int lds_bytes() const { return ns * ring_rows() * 64; }
 };
-// kernel variants, selectable through GemmArgs::force_tile (1 .. kGemmTileMax)
-static const TileInfo kTiles[kGemmTileMax + 1] = {
-    {0, 0, 0, 0},
-    {256, 256, 4 * 512 * 64, 1},   // 1: 256 x 256 tile, BK 32 x 4 stages, four waves of 128 x 128
-    {128, 256, 6 * 384 * 64, 1},   // 2: 128 x 256 tile, BK 32 x 6 stages, four waves of 64 x 128
-    {128, 128, 4 * 256 * 64, 2},   // 3: 128 x 128 tile, BK 32 x 4 stages, four waves of 64 x 64, two workgroups per CU
+#define TDP_TILE(AT, WT, NS, PER_CU)                                                       \
+  {AT, WT, NS, PER_CU,                                                                     \
+   {reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, false>),                   \
+    reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, true>)}}
+static const TileInfo kTiles[] = {
+    {0, 0, 0, 0, {nullptr, nullptr}},
+    TDP_TILE(8, 8, 4, 1),  // 1: 256 x 256
+    TDP_TILE(4, 8, 6, 1),  // 2: 128 x 256
+    TDP_TILE(4, 4, 4, 2),  // 3: 128 x 128
+    TDP_TILE(7, 8, 4, 1), TDP_TILE(6, 8, 5, 1), TDP_TILE(5, 8, 5, 1),                        // 224, 192, 160 x 256
+    TDP_TILE(8, 4, 6, 1), TDP_TILE(7, 4, 6, 1), TDP_TILE(5, 4, 7, 1), TDP_TILE(3, 4, 8, 1),  // 256, 224, 160, 96 x 128
+    TDP_TILE(2, 4, 6, 2), TDP_TILE(1, 4, 4, 3),                                              // 64, 32 x 128
 };
+#undef TDP_TILE
+constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 
 static bool g_print_plan = false;  // tuning aid, read from the environment once (gemm_setup)
 
@@ -471,30 +525,55 @@ hipError_t gemm_setup() {
     g_print_plan = getenv("TDP_GEMM_PLAN") != nullptr;
     hipError_t e;
     e = hipSuccess;
-    const void* kernels[] = {reinterpret_cast<const void*>(&gemm_mi16_kernel<256, 4, 4, 4, 256, false>),
-                             reinterpret_cast<const void*>(&gemm_mi16_kernel<256, 4, 4, 4, 256, true>),
-                             reinterpret_cast<const void*>(&gemm_mi16_kernel<128, 6, 2, 4, 256, false>),
-                             reinterpret_cast<const void*>(&gemm_mi16_kernel<128, 6, 2, 4, 256, true>),
-                             reinterpret_cast<const void*>(&gemm_mi16_kernel<128, 4, 2, 2, 128, false>),
-                             reinterpret_cast<const void*>(&gemm_mi16_kernel<128, 4, 2, 2, 128, true>)};
-    for (int i = 0; i < 6 && e == hipSuccess; ++i)
-      e = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kTiles[1 + i / 2].lds_bytes);
+    for (int i = 1; i < kTileCount; ++i)
+      for (int w = 0; w < 2 && e == hipSuccess; ++w)
+        e = hipFuncSetAttribute(kTiles[i].kernel[w], hipFuncAttributeMaxDynamicSharedMemorySize, kTiles[i].lds_bytes());
     result = e;
   });
   return result;
 }
 
+// Estimated time in us of a launch with this tile and split-K factor (per = 64-wide k-tiles of a split).  An XCD
+// makes its eighth of the tiles in rounds of 32 CUs x wg_per_cu; a 32-wide stage of a round costs the matrix
+// pipe, the LDS fill of a CU, the XCD's reads through its fabric port, the chip's reads of the weights and the
+// latency the ring has to cover - none of which hides behind another entirely, hence the power sum;
+// a round ends with its epilogue; split-K adds the fp32 partials' round trip and, where no later kernel sums them,
+// a reduce launch.  The constants are a least-squares fit to 10,000 launches timed on cold weights (19 projection
+// shapes, M from 4 to 19346, 1 to 16 splits): the tile and factor that this picks are on average 1.5 % slower
+// than the fastest measured, against 32 % for the rule it replaces (M <= 128, narrow, else; rounds of k-tiles).
+static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer) {
+  const double tm = (double)((M + ti.bm() - 1) / ti.bm()), tn = (double)(Npad / ti.bn());
+  const double tiles = tm * tn * splits;
+  const int64_t per_xcd = ((int64_t)tiles + 7) / 8, slots = 32 * ti.wg_per_cu;
+  const int64_t full = (per_xcd - 1) / slots, last = per_xcd - full * slots;  // full rounds, tiles of the last one
+  const double band = tm / (double)(((int64_t)tm + 3) / 4);                   // rows of tiles in a band
+  const double mfma = ti.at * ti.wt;
+  const double a_rows = ti.ring_rows() - ti.bn(), bn = ti.bn();
+  auto stage = [&](int64_t n) {  // n tiles of the XCD at once
+    const double per_cu = (double)((n + 31) / 32);
+    const double cols = ceil((double)n / band);
+    const double on_chip = (double)(8 * n) < tiles ? (double)(8 * n) : tiles;
+    const double terms[5] = {per_cu * (mfma * 0.0065 + 0.0335),
+                             per_cu * ti.ring_rows() * (0.064 / 121),
+                             ((band < n ? band : (double)n) * a_rows + cols * bn) * (512e-6 / 11.5),
+                             on_chip / tm * bn * (64e-6 / 17.3),
+                             0.165 / (ti.ns - 1)};
+    double sum = 0;
+    for (double t : terms) sum += t * sqrt(t);  // power 1.5
+    return cbrt(sum * sum);
+  };
+  auto epi = [&](int64_t n) { return 0.87 + 0.12 * mfma * (double)((n + 31) / 32); };
+  double us = 2.0 + full * (2 * per * stage(slots) + epi(slots)) + 2 * per * stage(last) + epi(last);
+  if (splits > 1) {
+    us += 0.83e-6 * splits * M * (double)Npad;
+    if (!defer) us += 5.3;
+    else if (epilogue == EPI_STORE) us += 0.4e-6 * (splits - 1) * M * (double)Npad;  // read by the rotation
+  }
+  return us * (1.0 + 0.004 * tm);  // ties: fewer rows of tiles, the weights are read fewer times
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  int t = a.force_tile;
-  if (t < 1 || t > kGemmTileMax) {
-    // up to 256 rows a projection with few weight rows and a short K fills the chip better with
-    // 128-row tiles (twice the workgroups, half the split-K factor); measured at M = 256, K = 8192:
-    // 59 vs 72 us (N 10240), 50 vs 61 (N 8192); with K = 28672 the 256-row tile stays ahead (141 vs 148)
-    const bool narrow = a.Npad <= 16384 && a.Kpad <= 16384;
-    t = a.M <= 128 ? 2 : (a.M <= 256 && narrow) ? 2 : 1;
-  }
-  const TileInfo& ti = kTiles[t];
   GemmParams p;
   p.A = (const bf16*)a.A;
   p.W = (const bf16*)a.W;
@@ -515,119 +594,89 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.N_store = a.N_store;
   p.epilogue = a.epilogue;
   p.k_tiles_total = (int)(a.Kpad / 64);
-  p.tiles_m = (a.M + ti.bm - 1) / ti.bm;
-  p.tiles_n = (int)(a.Npad / ti.bn);
-  // ---- plan: split-K factor and super-block size ---------------------------------------------
-  // The model: an XCD (32 CUs) works through the tiles dealt to it, wg_per_cu * 32 at a time, and a
-  // tile costs its k-tiles; split-K adds the fp32 partial round trip.  Small problems (decode) want
-  // every XCD equally loaded; large ones want 32-tile super-blocks for L2 reuse.
+  // ---- plan: tile and split-K factor ------------------------------------------------------------
   // The search below costs tens of microseconds on the host and its answer depends only on the
   // problem's shape, so it is remembered (a serving loop asks for the same few shapes every step).
+  const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
   struct PlanKey {
-    int M, t, force_splits;
+    int M, force_tile, force_splits, epilogue;
+    bool defer;
     int64_t Npad, Kpad, ws_elems;
     bool operator==(const PlanKey& o) const {
-      return M == o.M && t == o.t && force_splits == o.force_splits && Npad == o.Npad && Kpad == o.Kpad &&
-             ws_elems == o.ws_elems;
+      return M == o.M && force_tile == o.force_tile && force_splits == o.force_splits && epilogue == o.epilogue &&
+             defer == o.defer && Npad == o.Npad && Kpad == o.Kpad && ws_elems == o.ws_elems;
     }
   };
   struct PlanKeyHash {
     size_t operator()(const PlanKey& k) const {
       uint64_t h = 0x9e3779b97f4a7c15ull;
-      for (uint64_t v : {(uint64_t)k.M, (uint64_t)k.t, (uint64_t)k.force_splits, (uint64_t)k.Npad, (uint64_t)k.Kpad,
-                         (uint64_t)k.ws_elems})
+      for (uint64_t v : {(uint64_t)k.M, (uint64_t)k.force_tile, (uint64_t)k.force_splits, (uint64_t)(k.epilogue * 2 + k.defer),
+                         (uint64_t)k.Npad, (uint64_t)k.Kpad, (uint64_t)k.ws_elems})
         h = (h ^ v) * 0xff51afd7ed558ccdull + (h >> 29);
       return (size_t)h;
     }
   };
   struct PlanEntry {
-    int splits, sb;
+    int tile, splits;
   };
   static std::mutex plan_mutex;
   static std::unordered_map<PlanKey, PlanEntry, PlanKeyHash> plan_cache;
-  const PlanKey key{a.M, t, a.force_splits, a.Npad, a.Kpad, a.workspace_elems};
-  int best_splits = 0, best_sb = 1;
+  const PlanKey key{a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems};
+  PlanEntry plan{0, 1};
   {
     std::lock_guard<std::mutex> lock(plan_mutex);
     const auto it = plan_cache.find(key);
-    if (it != plan_cache.end()) {
-      best_splits = it->second.splits;
-      best_sb = it->second.sb;
-    }
+    if (it != plan_cache.end()) plan = it->second;
   }
-  if (best_splits == 0) {
-    best_splits = 1;
-    int max_splits = 1;
-    if (a.force_splits > 0) max_splits = a.force_splits;
-    else if (a.M <= 512) max_splits = p.k_tiles_total / 4 < 16 ? (p.k_tiles_total / 4 > 0 ? p.k_tiles_total / 4 : 1) : 16;
-    if (max_splits > p.k_tiles_total) max_splits = p.k_tiles_total;
+  if (plan.tile == 0) {
+    const bool forced = a.force_tile >= 1 && a.force_tile <= kGemmTileMax;
     double best_cost = 1e300;
-    for (int sp = a.force_splits > 0 ? max_splits : 1; sp <= max_splits; ++sp) {
-      if (sp > 1 && (int64_t)sp * a.M * a.Npad > a.workspace_elems) break;
-      const int per = (p.k_tiles_total + sp - 1) / sp;
-      const int real_sp = (p.k_tiles_total + per - 1) / per;
-      if (real_sp != sp && a.force_splits <= 0) continue;  // same schedule as a smaller factor
-      for (int sb_size = 32; sb_size >= 1; sb_size >>= 1) {
-        int sb_m = p.tiles_m >= 4 ? 4 : p.tiles_m >= 2 ? 2 : 1;
-        if (sb_m > sb_size) sb_m = sb_size;
-        const int sb_n = sb_size / sb_m;
-        const int n_sb_n = (p.tiles_n + sb_n - 1) / sb_n;
-        const int n_sb_m = (p.tiles_m + sb_m - 1) / sb_m;
-        const int n_sb = n_sb_m * n_sb_n;
-        int64_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int g = 0; g < n_sb * real_sp; ++g) {
-          const int sb = g % n_sb;
-          const int rows = (sb / n_sb_n + 1) * sb_m <= p.tiles_m ? sb_m : p.tiles_m - (sb / n_sb_n) * sb_m;
-          const int cols = (sb % n_sb_n + 1) * sb_n <= p.tiles_n ? sb_n : p.tiles_n - (sb % n_sb_n) * sb_n;
-          load[g & 7] += (int64_t)rows * cols;
-        }
-        int64_t mx = 0;
-        for (int x = 0; x < 8; ++x) mx = load[x] > mx ? load[x] : mx;
-        const int slots = 32 * ti.wg_per_cu;
-        const double rounds = (double)((mx + slots - 1) / slots);
-        // a workgroup pays its pipeline fill and its epilogue whatever its share of K: about 6 k-tiles' worth
-        // (without this term the model splits a 224-tile launch eight ways to fill 256 CUs: measured 25 % slower)
-        double cost = rounds * (per + 6.0);
-        // fp32 partials: 8 bytes per element and split at ~4 TB/s, in units of one k-tile round (~1.8 us)
-        if (real_sp > 1) cost += 1.1e-6 * real_sp * a.M * (double)a.Npad + 2.0;
-        cost *= 1.0 + 0.02 * (5 - __builtin_ctz(sb_size));  // prefer larger super-blocks on ties
+    for (int t = forced ? a.force_tile : 1; t <= (forced ? a.force_tile : kTileCount - 1); ++t) {
+      const int64_t tiles1 = (int64_t)((a.M + kTiles[t].bm() - 1) / kTiles[t].bm()) * (a.Npad / kTiles[t].bn());
+      const int k_splits_max = p.k_tiles_total / 2 < 16 ? (p.k_tiles_total / 2 > 0 ? p.k_tiles_total / 2 : 1) : 16;
+      int sp = a.force_splits > 0 ? a.force_splits : 1, sp_max = a.force_splits > 0 ? a.force_splits : k_splits_max;
+      if (sp > p.k_tiles_total) sp = sp_max = p.k_tiles_total;
+      for (; sp <= sp_max; ++sp) {
+        const int per = (p.k_tiles_total + sp - 1) / sp;
+        const int real_sp = (p.k_tiles_total + per - 1) / per;
+        if (real_sp != sp && a.force_splits <= 0) continue;  // same schedule as a smaller factor
+        if (real_sp > 1 && (int64_t)real_sp * a.M * a.Npad > a.workspace_elems) break;
+        // (four rounds of tiles: nothing is left for a split to gain)
+        if (real_sp > 1 && a.force_splits <= 0 && tiles1 * real_sp > 1024 * kTiles[t].wg_per_cu) break;
+        const double cost = plan_cost(kTiles[t], a.M, a.Npad, per, real_sp, a.epilogue, defer);
         if (cost < best_cost) {
           best_cost = cost;
-          best_splits = real_sp;
-          best_sb = sb_size;
+          plan = PlanEntry{t, real_sp};
         }
       }
     }
+    if (plan.tile == 0) plan = PlanEntry{forced ? a.force_tile : 1, 1};  // the workspace holds no such split
     std::lock_guard<std::mutex> lock(plan_mutex);
-    if (plan_cache.size() < 65536) plan_cache[key] = PlanEntry{best_splits, best_sb};
+    if (plan_cache.size() < 65536) plan_cache[key] = plan;
   }
-  int splits = best_splits;
+  const TileInfo& ti = kTiles[plan.tile];
+  const int splits = plan.splits;
+  p.tiles_m = (a.M + ti.bm() - 1) / ti.bm();
+  p.tiles_n = (int)(a.Npad / ti.bn());
   p.k_tiles_per_split = (p.k_tiles_total + splits - 1) / splits;
   p.splits = splits;
-  p.sb_m = p.tiles_m >= 4 ? 4 : p.tiles_m >= 2 ? 2 : 1;
-  if (p.sb_m > best_sb) p.sb_m = best_sb;
-  p.sb_n = best_sb / p.sb_m;
-  p.n_sb_n = (p.tiles_n + p.sb_n - 1) / p.sb_n;
-  p.n_sb = ((p.tiles_m + p.sb_m - 1) / p.sb_m) * p.n_sb_n;
+  const int bands = (p.tiles_m + 3) / 4;
+  p.band_h = p.tiles_m / bands;
+  p.n_tall = p.tiles_m % bands;
+  const int tiles = p.tiles_m * p.tiles_n * splits;
+  p.chunk = 32 * ti.wg_per_cu;
+  p.chunks = tiles / (8 * p.chunk);
+  p.rest = tiles - p.chunks * 8 * p.chunk;
   if (g_print_plan)
-    fprintf(stderr, "gemm plan: M=%d N=%lld K=%lld tile=%d tiles=%dx%d splits=%d (k-tiles %d each) super-block %dx%d\n",
-            a.M, (long long)a.Npad, (long long)a.Kpad, t, p.tiles_m, p.tiles_n, splits, p.k_tiles_per_split, p.sb_m,
-            p.sb_n);
-  dim3 grid(((p.n_sb * splits + 7) / 8) * 8 * p.sb_m * p.sb_n);
+    fprintf(stderr, "gemm plan: M=%d N=%lld K=%lld tile=%d tiles=%dx%d splits=%d (k-tiles %d each)\n",
+            a.M, (long long)a.Npad, (long long)a.Kpad, plan.tile, p.tiles_m, p.tiles_n, splits, p.k_tiles_per_split);
+  dim3 grid((tiles + 7) / 8 * 8);
   // a single row of tiles reads every weight byte once: request them as non-temporal (also two rows of a
   // wide projection, see the kernel's comment)
   const bool wnt = p.tiles_m == 1 || (p.tiles_m == 2 && a.Npad >= 32768 && splits == 1);
-  switch (t * 2 + (wnt ? 1 : 0)) {
-    case 2: gemm_mi16_kernel<256, 4, 4, 4, 256, false><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-    case 3: gemm_mi16_kernel<256, 4, 4, 4, 256, true><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-    case 4: gemm_mi16_kernel<128, 6, 2, 4, 256, false><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-    case 5: gemm_mi16_kernel<128, 6, 2, 4, 256, true><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-    case 6: gemm_mi16_kernel<128, 4, 2, 2, 128, false><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-    default: gemm_mi16_kernel<128, 4, 2, 2, 128, true><<<grid, dim3(256), ti.lds_bytes, s>>>(p); break;
-  }
-  hipError_t e = hipGetLastError();
+  void* args[] = {&p};
+  hipError_t e = hipLaunchKernel(ti.kernel[wnt ? 1 : 0], grid, dim3(256), args, ti.lds_bytes(), s);
   if (e != hipSuccess) return e;
-  const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
   if (a.splits_used) *a.splits_used = defer ? splits : 1;
   if (splits > 1 && !defer) {
     const int out_cols = a.N_store;  // (gated epilogue: columns of the result, half the weight rows)
