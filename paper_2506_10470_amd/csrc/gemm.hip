@@ -494,24 +494,28 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmParams p, in
 // per CU where a tile is small enough (their fill and epilogue then overlap the neighbour's stages).
 struct TileInfo {
   int at, wt, ns, wg_per_cu;
+  double stage_us;        // a 32-wide stage of one tile on a CU, the matrix pipe's part (see plan_cost)
   const void* kernel[2];  // ordinary / non-temporal weight requests
   int bm() const { return at * 32; }
   int bn() const { return wt * 32; }
   int ring_rows() const { return (at * 2 + 3) / 4 * 64 + bn(); }  // rows of a ring stage (see IPA)
   int lds_bytes() const { return ns * ring_rows() * 64; }
 };
-#define TDP_TILE(AT, WT, NS, PER_CU)                                                       \
-  {AT, WT, NS, PER_CU,                                                                     \
+#define TDP_TILE(AT, WT, NS, PER_CU, US)                                                   \
+  {AT, WT, NS, PER_CU, US,                                                                 \
    {reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, false>),                   \
     reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, true>)}}
 static const TileInfo kTiles[] = {
-    {0, 0, 0, 0, {nullptr, nullptr}},
-    TDP_TILE(8, 8, 4, 1),  // 1: 256 x 256
-    TDP_TILE(4, 8, 6, 1),  // 2: 128 x 256
-    TDP_TILE(4, 4, 4, 2),  // 3: 128 x 128
-    TDP_TILE(7, 8, 4, 1), TDP_TILE(6, 8, 5, 1), TDP_TILE(5, 8, 5, 1),                        // 224, 192, 160 x 256
-    TDP_TILE(8, 4, 6, 1), TDP_TILE(7, 4, 6, 1), TDP_TILE(5, 4, 7, 1), TDP_TILE(3, 4, 8, 1),  // 256, 224, 160, 96 x 128
-    TDP_TILE(2, 4, 6, 2), TDP_TILE(1, 4, 4, 3),                                              // 64, 32 x 128
+    {0, 0, 0, 0, 0.0, {nullptr, nullptr}},
+    TDP_TILE(8, 8, 4, 1, 0.425),  // 1: 256 x 256
+    TDP_TILE(4, 8, 6, 1, 0.252),  // 2: 128 x 256
+    TDP_TILE(4, 4, 4, 2, 0.129),  // 3: 128 x 128
+    // 224, 192, 160 x 256
+    TDP_TILE(7, 8, 4, 1, 0.346), TDP_TILE(6, 8, 5, 1, 0.337), TDP_TILE(5, 8, 5, 1, 0.266),
+    // 256, 224, 160, 96 x 128
+    TDP_TILE(8, 4, 6, 1, 0.244), TDP_TILE(7, 4, 6, 1, 0.202), TDP_TILE(5, 4, 7, 1, 0.168), TDP_TILE(3, 4, 8, 1, 0.097),
+    // 64, 32 x 128
+    TDP_TILE(2, 4, 6, 2, 0.079), TDP_TILE(1, 4, 4, 3, 0.0415),
 };
 #undef TDP_TILE
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
@@ -539,7 +543,7 @@ hipError_t gemm_setup() {
 // latency the ring has to cover - none of which hides behind another entirely, hence the power sum;
 // a round ends with its epilogue; split-K adds the fp32 partials' round trip and, where no later kernel sums them,
 // a reduce launch.  The constants are a least-squares fit to 10,000 launches timed on cold weights (19 projection
-// shapes, M from 4 to 19346, 1 to 16 splits): the tile and factor that this picks are on average 1.5 % slower
+// shapes, M from 4 to 19346, 1 to 16 splits): the tile and factor that this picks are on average 1.3 % slower
 // than the fastest measured, against 32 % for the rule it replaces (M <= 128, narrow, else; rounds of k-tiles).
 static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer) {
   const double tm = (double)((M + ti.bm() - 1) / ti.bm()), tn = (double)(Npad / ti.bn());
@@ -553,20 +557,20 @@ static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, in
     const double per_cu = (double)((n + 31) / 32);
     const double cols = ceil((double)n / band);
     const double on_chip = (double)(8 * n) < tiles ? (double)(8 * n) : tiles;
-    const double terms[5] = {per_cu * (mfma * 0.0065 + 0.0335),
-                             per_cu * ti.ring_rows() * (0.064 / 121),
-                             ((band < n ? band : (double)n) * a_rows + cols * bn) * (512e-6 / 11.5),
-                             on_chip / tm * bn * (64e-6 / 17.3),
-                             0.165 / (ti.ns - 1)};
+    const double terms[5] = {per_cu * ti.stage_us,
+                             per_cu * ti.ring_rows() * (0.064 / 117.6),
+                             ((band < n ? band : (double)n) * a_rows + cols * bn) * (512e-6 / 11.1),
+                             on_chip / tm * bn * (64e-6 / 18.3),
+                             0.21 / (ti.ns - 1)};
     double sum = 0;
     for (double t : terms) sum += t * sqrt(t);  // power 1.5
     return cbrt(sum * sum);
   };
-  auto epi = [&](int64_t n) { return 0.87 + 0.12 * mfma * (double)((n + 31) / 32); };
-  double us = 2.0 + full * (2 * per * stage(slots) + epi(slots)) + 2 * per * stage(last) + epi(last);
+  auto epi = [&](int64_t n) { return 0.94 + 0.12 * mfma * (double)((n + 31) / 32); };
+  double us = 1.9 + full * (2 * per * stage(slots) + epi(slots)) + 2 * per * stage(last) + epi(last);
   if (splits > 1) {
-    us += 0.83e-6 * splits * M * (double)Npad;
-    if (!defer) us += 5.3;
+    us += 0.81e-6 * splits * M * (double)Npad + 0.15 * splits;
+    if (!defer) us += 5.4;
     else if (epilogue == EPI_STORE) us += 0.4e-6 * (splits - 1) * M * (double)Npad;  // read by the rotation
   }
   return us * (1.0 + 0.004 * tm);  // ties: fewer rows of tiles, the weights are read fewer times

@@ -30,7 +30,7 @@ SHAPES = [
     (225, 8200, 2048),   # 96 x 128, three rows
     (128, 30008, 128),   # 128 x 128, two workgroups per CU
     (129, 8200, 2048),   # 64 x 128
-    (1, 8200, 2048), (31, 516, 1024), (33, 1032, 512),   # 32 x 128
+    (1, 8200, 2048), (31, 520, 1024), (33, 1032, 512),   # 32 x 128
     (1301, 520, 192),    # many short rows of tiles: bands of unequal height
 ]
 
