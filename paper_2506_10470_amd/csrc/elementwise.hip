@@ -353,6 +353,79 @@ __global__ __launch_bounds__(THREADS) void rope_kv_kernel(bf16* __restrict__ qkv
   }
 }
 
+// The page that chunk w of a grid over (sequence, page) pairs stands for: the last sequence s with cu_seqlens[s] / 16 + s
+// <= w and its page w - (cu_seqlens[s] / 16 + s); the numbering leaves every sequence room for all its pages, a chunk past
+// a sequence's last page gives false.  The last sequence ends at total_tokens.
+__device__ __forceinline__ bool locate_page(int w, const int32_t* cu_seqlens, int n_seqs, int total_tokens, int& seq,
+                                            int& p, int& t_first, int& n) {
+  int lo = 0, hi = n_seqs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((cu_seqlens[mid] >> 4) + mid <= w) lo = mid; else hi = mid - 1;
+  }
+  seq = lo;
+  t_first = cu_seqlens[lo];
+  const int end = lo == n_seqs - 1 ? total_tokens : min(cu_seqlens[lo + 1], total_tokens);
+  p = w - ((t_first >> 4) + lo);
+  if (p < 0 || p * 16 >= end - t_first) return false;
+  n = min(16, end - t_first - p * 16);
+  return true;
+}
+
+// A page's 16 tokens x up to 512 channels, turned round in LDS between token rows and the transposed V page.
+constexpr int kPageChannels = 512;
+using PageTile = bf16[16][kPageChannels + 8];  // [token][channel]; rows 4 banks apart
+// piece i (16 bytes of a token row): eight pieces of a row, then the 16 tokens, then the next 64 channels - a wave's
+// instruction covers 8 tokens x 128 bytes
+__device__ __forceinline__ int page_piece_token(int i) { return (i >> 3) & 15; }
+__device__ __forceinline__ int page_piece_channel(int i) { return ((i & 7) + ((i >> 7) << 3)) * 8; }
+
+// tile -> page [channel][16 tokens], tokens < n only; all 256 threads
+template <bool KV8>
+__device__ __forceinline__ void store_v_page(const PageTile& tile, uint8_t* v_page, int channels, int n, float v_scale) {
+  if constexpr (KV8) {
+    for (int c = threadIdx.x; c < channels; c += 256) {
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 16; ++t)
+        if (t < n) w[t >> 2] |= f32_to_e4m3((float)tile[t][c] / v_scale) << (8 * (t & 3));
+      uint8_t* dst = v_page + c * 16;
+      if (n == 16) {
+        *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+          if (t < n) dst[t] = (uint8_t)(w[t >> 2] >> (8 * (t & 3)));
+      }
+    }
+  } else {
+    // two channels and eight tokens per thread: dword reads of the tile
+    for (int i = threadIdx.x; i < channels; i += 256) {
+      const int t0 = (i & 1) * 8, c = i & ~1;
+      if (t0 >= n) continue;
+      bf16x8 a, b;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const bf16x2 ab = *reinterpret_cast<const bf16x2*>(&tile[t0 + t][c]);
+        a[t] = ab[0];
+        b[t] = ab[1];
+      }
+      bf16* dst = reinterpret_cast<bf16*>(v_page) + c * 16 + t0;
+      if (t0 + 8 <= n) {
+        st_bf16x8(dst, a);
+        st_bf16x8(dst + 16, b);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          if (t0 + t < n) {
+            dst[t] = a[t];
+            dst[16 + t] = b[t];
+          }
+      }
+    }
+  }
+}
+
 // Prefill, values rounded to bf16 in the token rows: the values of one page (up to 16 consecutive tokens of one
 // prompt) are appended by one workgroup, so that a channel's row of the transposed V page is written
 // as one piece (token by token every 2-byte store dirtied a 32-byte sector of its own: measured ten
@@ -444,6 +517,111 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
 }
 
 // ------------------------------------------------------------------ KV import / export
+// One workgroup moves 16 tokens x up to 512 channels of K and of V between the packed arrays and one page.  Bound: HBM
+// (every byte read once and written once).  A wave's instruction covers 8 tokens x 128 bytes, i.e. whole
+// lines of the packed side and runs of 512 bytes of the key page; values turn round in LDS, so that the
+// transposed page is read and written 16 bytes (8 tokens of a channel; 8-bit: all 16) at a time.  Element by element,
+// with 2-byte accesses on both sides, 23,000 tokens of 40 x 128 channels took 790 us in and 450 us out (0.96 GB each:
+// 1.2 and 2.1 TB/s); like this 195 and 192 us (4.9 TB/s; a plain copy reaches 4.7).
+template <bool KV8, bool TO_PAGES>
+__global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packed, bf16* __restrict__ v_packed,
+                                                      KvLayout kv, const int32_t* __restrict__ cu_seqlens, int n_seqs,
+                                                      int total_tokens, const int32_t* __restrict__ block_tables,
+                                                      int max_pages_per_seq) {
+  constexpr int CH = kPageChannels, PER = 16 * CH / 8 / 256;  // 16-byte pieces of K (and of V) per thread
+  __shared__ __attribute__((aligned(16))) PageTile tile;
+  int seq, p, t_first, n;
+  if (!locate_page(blockIdx.x, cu_seqlens, n_seqs, total_tokens, seq, p, t_first, n)) return;
+  const int64_t page = block_tables[(int64_t)seq * max_pages_per_seq + p];
+  const int dh = kv.head_dim, dkv = kv.n_kv_heads * dh, dh_shift = dh == 128 ? 7 : 6;
+  const int c0 = blockIdx.y * CH;
+  const int channels = min(CH, dkv - c0);  // a multiple of 64
+  const int64_t at = (int64_t)(t_first + p * 16) * dkv + c0;
+  bf16* kp = k_packed + at;
+  bf16* vp = v_packed + at;
+  uint8_t* v_page = (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32);  // [channel][16 tokens]
+  const int pieces = channels * 2;
+  auto k_at = [&](int tok, int ch) {
+    const int c = c0 + ch;
+    return (uint8_t*)kv.k_pool + k_pool_byte(kv, page, c >> dh_shift, tok, (c & (dh - 1)) * (KV8 ? 1 : 2));
+  };
+  if constexpr (TO_PAGES) {
+    bf16x8 k[PER], v[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
+      if (i < pieces && tok < n) {
+        k[j] = ld_bf16x8(kp + (int64_t)tok * dkv + ch);
+        v[j] = ld_bf16x8(vp + (int64_t)tok * dkv + ch);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
+      if (i < pieces && tok < n) {
+        st_bf16x8(&tile[tok][ch], v[j]);
+        if constexpr (KV8) {
+          uint2 c = make_uint2(0u, 0u);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            c.x |= f32_to_e4m3((float)k[j][e] / kv.k_scale) << (8 * e);
+            c.y |= f32_to_e4m3((float)k[j][4 + e] / kv.k_scale) << (8 * e);
+          }
+          *reinterpret_cast<uint2*>(k_at(tok, ch)) = c;
+        } else {
+          st_bf16x8(reinterpret_cast<bf16*>(k_at(tok, ch)), k[j]);
+        }
+      }
+    }
+    __syncthreads();
+    store_v_page<KV8>(tile, v_page, channels, n, kv.v_scale);
+  } else {
+    bf16x8 k[PER];
+    uint2 k8[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
+      if (i < pieces && tok < n) {
+        if constexpr (KV8) k8[j] = *reinterpret_cast<const uint2*>(k_at(tok, ch));
+        else k[j] = ld_bf16x8(reinterpret_cast<const bf16*>(k_at(tok, ch)));
+      }
+    }
+    if constexpr (KV8) {
+      for (int c = threadIdx.x; c < channels; c += 256) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(v_page + c * 16);
+        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+        for (int t = 0; t < 16; ++t) tile[t][c] = (bf16)(e4m3_to_f32((w[t >> 2] >> (8 * (t & 3))) & 255u) * kv.v_scale);
+      }
+    } else {
+      for (int i = threadIdx.x; i < channels; i += 256) {
+        const int t0 = (i & 1) * 8, c = i & ~1;
+        const bf16* src = reinterpret_cast<const bf16*>(v_page) + c * 16 + t0;
+        const bf16x8 a = ld_bf16x8(src), b = ld_bf16x8(src + 16);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) *reinterpret_cast<bf16x2*>(&tile[t0 + t][c]) = bf16x2{a[t], b[t]};
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
+      if (i < pieces && tok < n) {
+        if constexpr (KV8) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            k[j][e] = (bf16)(e4m3_to_f32((k8[j].x >> (8 * e)) & 255u) * kv.k_scale);
+            k[j][4 + e] = (bf16)(e4m3_to_f32((k8[j].y >> (8 * e)) & 255u) * kv.k_scale);
+          }
+        }
+        st_bf16x8(kp + (int64_t)tok * dkv + ch, k[j]);
+        st_bf16x8(vp + (int64_t)tok * dkv + ch, ld_bf16x8(&tile[tok][ch]));
+      }
+    }
+  }
+}
+
+// The same element by element, for packed arrays that are not 16-byte aligned.
 __global__ __launch_bounds__(256) void kv_copy_kernel(int to_pages, bf16* __restrict__ k_packed,
                                                       bf16* __restrict__ v_packed, KvLayout kv,
                                                       const int32_t* __restrict__ cu_seqlens, int n_seqs,
@@ -516,6 +694,19 @@ hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const Kv
                           const int32_t* cu_seqlens, int n_seqs, int total_tokens,
                           const int32_t* block_tables, int max_pages_per_seq, hipStream_t s) {
   if (total_tokens <= 0) return hipSuccess;
+  if ((((uintptr_t)k_packed | (uintptr_t)v_packed) & 15) == 0) {
+    const dim3 grid((total_tokens >> 4) + n_seqs + 1, (kv.n_kv_heads * kv.head_dim + kPageChannels - 1) / kPageChannels);
+#define TDP_MOVE(KV8, TO)                                                                                        \
+  kv_move_kernel<KV8, TO><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
+                                               block_tables, max_pages_per_seq)
+    if (kv.fp8) {
+      if (to_pages) TDP_MOVE(true, true); else TDP_MOVE(true, false);
+    } else {
+      if (to_pages) TDP_MOVE(false, true); else TDP_MOVE(false, false);
+    }
+#undef TDP_MOVE
+    return hipGetLastError();
+  }
   kv_copy_kernel<<<total_tokens, 256, 0, s>>>(to_pages, (bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens,
                                               n_seqs, block_tables, max_pages_per_seq);
   return hipGetLastError();
