@@ -881,44 +881,63 @@ hipError_t launch_to_bf16(const void* src, int src_is_f32, int64_t n, void* dst,
   return hipGetLastError();
 }
 
-// out[m] = the lowest index among the largest of logits[m][0 .. n).  One workgroup per row; a
-// thread walks its columns in increasing order, so within a thread "strictly greater" keeps the
-// first maximum, and the cross-thread reduction breaks value ties towards the lower index.
-// NaNs never win a comparison; a row of NaNs gives 0.
-__global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restrict__ logits, int64_t ld, int n,
-                                                          int32_t* __restrict__ out) {
-  __shared__ float s_val[256];
-  __shared__ int s_idx[256];
+// out[m] = the lowest index among the largest of logits[m][0 .. n).  One workgroup of 1024 threads per row.  NaNs
+// never win a comparison; a row of NaNs gives 0.  The rule "greater, or equal at a lower index" does not depend on the
+// order of comparisons, so a thread may have many loads in flight: 16 bytes x 8 per turn, a row of 32000 in one
+// (a row is aligned by its first up to three elements).  Bound: the latency of a row's first bytes for a few rows, reading the
+// logits for many.  With 256 threads that load and compare one element per turn a launch took 42 us for 48
+// rows of 32000 and 46 us for 512; like this 7 and 14.
+__global__ __launch_bounds__(1024) void argmax_rows_kernel(const float* __restrict__ logits, int64_t ld, int n,
+                                                           int32_t* __restrict__ out) {
+  constexpr int UN = 8;
+  __shared__ float s_val[16];
+  __shared__ int s_idx[16];
   const float* row = logits + (int64_t)blockIdx.x * ld;
+  const int tid = threadIdx.x;
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  for (int j = threadIdx.x; j < n; j += 256) {
-    const float v = row[j];
-    if (v > best || (bi == 0x7fffffff && v == best)) {
+  auto take = [&](float v, int i) {
+    if (v > best || (v == best && i < bi)) {
       best = v;
-      bi = j;
+      bi = i;
+    }
+  };
+  const int head = min(n, (int)((16 - ((uintptr_t)row & 15)) & 15) / 4);
+  const int n4 = (n - head) / 4, tail = head + n4 * 4;
+  const f32x4* body = reinterpret_cast<const f32x4*>(row + head);
+  if (tid < head) take(row[tid], tid);
+  if (tid < n - tail) take(row[tail + tid], tail + tid);
+  for (int j0 = 0; j0 < n4; j0 += 1024 * UN) {
+    f32x4 v[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) v[u] = body[min(j0 + u * 1024 + tid, n4 - 1)];  // (past the end: the last piece again)
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int at = head + 4 * min(j0 + u * 1024 + tid, n4 - 1);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) take(v[u][e], at + e);
     }
   }
-  s_val[threadIdx.x] = best;
-  s_idx[threadIdx.x] = bi;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float v = __shfl_xor(best, o, 64);
+    const int i = __shfl_xor(bi, o, 64);
+    take(v, i);
+  }
+  if ((tid & 63) == 0) {
+    s_val[tid >> 6] = best;
+    s_idx[tid >> 6] = bi;
+  }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const float v = s_val[threadIdx.x + off];
-      const int i = s_idx[threadIdx.x + off];
-      if (v > s_val[threadIdx.x] || (v == s_val[threadIdx.x] && i < s_idx[threadIdx.x])) {
-        s_val[threadIdx.x] = v;
-        s_idx[threadIdx.x] = i;
-      }
-    }
-    __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 16; ++w) take(s_val[w], s_idx[w]);
+    out[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = s_idx[0] == 0x7fffffff ? 0 : s_idx[0];
 }
 
 hipError_t launch_argmax_rows(const float* logits, int64_t ld, int M, int n, int32_t* out, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  argmax_rows_kernel<<<M, 256, 0, s>>>(logits, ld, n, out);
+  argmax_rows_kernel<<<M, 1024, 0, s>>>(logits, ld, n, out);
   return hipGetLastError();
 }
 
