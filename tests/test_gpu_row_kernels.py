@@ -26,3 +26,11 @@ def test_argmax_any_alignment(tdp, n):
     ref = v.argmax(axis=1)
     ref[3] = n - 1  # the only number of its row
     assert np.array_equal(out.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("shape,n", [("tiny_gqa", 257), ("tiny_h128", 600)])
+def test_decode_of_more_requests_than_a_plan_has_threads(tdp, shape, n):
+    rng = np.random.default_rng(n)
+    ctx = rng.integers(0, 40, size=n)
+    ctx[::97] = rng.integers(200, 900, size=len(ctx[::97]))   # several spans of the shortest span length
+    run_decode_case(tdp, shape, ctx)
