@@ -231,7 +231,7 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 }
 
 // ------------------------------------------------------------------ RoPE + KV append
-// One workgroup per token.  The projection arrives in fp32 - the GEMM's fp32 output, or its split-K
+// The projection arrives in fp32 - the GEMM's fp32 output, or its split-K
 // partials, summed here in split order (plus the bias) - so the rotation works on unrounded sums and
 // every query and key element is rounded exactly once, after the rotation.  q heads are rotated and
 // written to the bf16 row the attention kernels read; k heads are rotated and written to the token's
@@ -239,8 +239,15 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 // the bf16 row for the page-by-page append that follows.  Rotation pairs channel i with channel
 // i + head_dim/2 and turns the pair by pos * base^(-2i/head_dim); the table holds (cos, sin) of that
 // angle, computed in double precision on the host.
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void rope_kv_kernel(bf16* __restrict__ qkv, int64_t ld, int n_q_heads,
+//
+// A unit is eight rotated pairs or eight values; a token's units are walked by gridDim.y workgroups of 256 threads.
+// Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In prefill one
+// workgroup takes a token (its look-ups are shared); in decode every unit has a thread of its own and asks for the
+// partials of UN splits at once: as one workgroup of 1024 threads per token that fetched a split per turn, a
+// launch of 16 / 48 (7B shape) / 128 (13B shape) / 512 tokens took 9.4 / 11.3 / 17.6 / 20.5 us, now 5.3 / 7.0 / 14 / 20.2
+// (what is left of the last two is the value append: 2-byte stores 32 bytes apart).
+template <int UN>
+__global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, int64_t ld, int n_q_heads,
                                                       KvLayout kv, const float2* __restrict__ table,
                                                       const int32_t* __restrict__ ctx_lens,
                                                       const int32_t* __restrict__ cu_seqlens, int n_seqs,
@@ -255,10 +262,7 @@ __global__ __launch_bounds__(THREADS) void rope_kv_kernel(bf16* __restrict__ qkv
     constexpr int NCOL = sizeof...(col);
     const float* const first[NCOL] = {(proj + (int64_t)t * ld + col)...};
     const int cols[NCOL] = {col...};
-    // one split per turn: fetching several at once costs registers, hence resident waves, and at the
-    // batch sizes where this kernel takes measurable time (hundreds of rows) that loses more than it
-    // gains (measured at batch 512: 23 us per launch against 21)
-    sum_partials8<NCOL, 1>(first, split_stride, splits, f);
+    sum_partials8<NCOL, UN>(first, split_stride, splits, f);
     if (bias) {
 #pragma unroll
       for (int c = 0; c < NCOL; ++c) {
@@ -276,79 +280,83 @@ __global__ __launch_bounds__(THREADS) void rope_kv_kernel(bf16* __restrict__ qkv
   const int slot = pos % kv.page_size;
   bf16* row = qkv + (int64_t)t * ld;
   const float2* cs = table + (int64_t)pos * half;
-  const int per_head = half / 8;  // 16-byte units per half head
-  const int rot_heads = n_q_heads + kv.n_kv_heads;
-  bf16* vpool = (bf16*)kv.v_pool;
-  for (int w = threadIdx.x; w < rot_heads * per_head; w += THREADS) {
-    const int head = w / per_head;
-    const int c0 = (w % per_head) * 8;
-    bf16* hp = row + (int64_t)head * dh;
-    float ab[2][8];
-    proj8(ab, head * dh + c0, head * dh + half + c0);
-    const float(&a)[8] = ab[0];
-    const float(&b)[8] = ab[1];
-    float fra[8], frb[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float2 t2 = cs[c0 + i];
-      fra[i] = a[i] * t2.x - b[i] * t2.y;
-      frb[i] = a[i] * t2.y + b[i] * t2.x;
-    }
-    // byte offsets of this thread's two 8-channel pieces in the K pool (a piece never straddles a 64-byte cut)
-    const int esz = kv.fp8 ? 1 : 2;
-    const int64_t k_lo = head >= n_q_heads ? k_pool_byte(kv, page, head - n_q_heads, slot, c0 * esz) : 0;
-    const int64_t k_hi = head >= n_q_heads ? k_pool_byte(kv, page, head - n_q_heads, slot, (half + c0) * esz) : 0;
-    if (head >= n_q_heads && kv.fp8) {
-      // 8-bit cache: the rotated key goes from fp32 straight to its code (one rounding)
-      uint2 ca = make_uint2(0u, 0u), cb = make_uint2(0u, 0u);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ca.x |= f32_to_e4m3(fra[i] / kv.k_scale) << (8 * i);
-        ca.y |= f32_to_e4m3(fra[4 + i] / kv.k_scale) << (8 * i);
-        cb.x |= f32_to_e4m3(frb[i] / kv.k_scale) << (8 * i);
-        cb.y |= f32_to_e4m3(frb[4 + i] / kv.k_scale) << (8 * i);
-      }
-      *reinterpret_cast<uint2*>((uint8_t*)kv.k_pool + k_lo) = ca;
-      *reinterpret_cast<uint2*>((uint8_t*)kv.k_pool + k_hi) = cb;
-      continue;
-    }
-    bf16x8 ra, rb;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      ra[i] = (bf16)fra[i];
-      rb[i] = (bf16)frb[i];
-    }
-    if (head < n_q_heads) {
-      st_bf16x8(hp + c0, ra);
-      st_bf16x8(hp + half + c0, rb);
-    } else {
-      st_bf16x8(reinterpret_cast<bf16*>((uint8_t*)kv.k_pool + k_lo), ra);
-      st_bf16x8(reinterpret_cast<bf16*>((uint8_t*)kv.k_pool + k_hi), rb);
-    }
-  }
+  const int head_shift = dh == 128 ? 3 : 2;  // units of eight pairs per head
+  const int rot_units = (n_q_heads + kv.n_kv_heads) << head_shift;
+  const int units = rot_units + kv.n_kv_heads * dh / 8;
   const int v_col = (n_q_heads + kv.n_kv_heads) * dh;
-  for (int w8 = threadIdx.x; w8 < kv.n_kv_heads * dh / 8; w8 += THREADS) {
-    float fv[1][8];
-    proj8(fv, v_col + w8 * 8);
-    const float(&f)[8] = fv[0];
-    if (v_to_row) {  // prefill: the values are appended page by page (v_append_pages_kernel)
-      bf16x8 o;
+  bf16* vpool = (bf16*)kv.v_pool;
+  for (int w = blockIdx.y * 256 + threadIdx.x; w < units; w += gridDim.y * 256) {
+    if (w < rot_units) {
+      const int head = w >> head_shift;
+      const int c0 = (w & ((1 << head_shift) - 1)) * 8;
+      bf16* hp = row + (int64_t)head * dh;
+      float ab[2][8];
+      proj8(ab, head * dh + c0, head * dh + half + c0);
+      const float(&a)[8] = ab[0];
+      const float(&b)[8] = ab[1];
+      float fra[8], frb[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = (bf16)f[i];
-      st_bf16x8(row + v_col + w8 * 8, o);
-      continue;
-    }
+      for (int i = 0; i < 8; i += 2) {
+        const f32x4 t2 = *reinterpret_cast<const f32x4*>(cs + c0 + i);  // (cos, sin) of two angles
+        fra[i] = a[i] * t2[0] - b[i] * t2[1];
+        frb[i] = a[i] * t2[1] + b[i] * t2[0];
+        fra[i + 1] = a[i + 1] * t2[2] - b[i + 1] * t2[3];
+        frb[i + 1] = a[i + 1] * t2[3] + b[i + 1] * t2[2];
+      }
+      // byte offsets of this thread's two 8-channel pieces in the K pool (a piece never straddles a 64-byte cut)
+      const int esz = kv.fp8 ? 1 : 2;
+      const int64_t k_lo = head >= n_q_heads ? k_pool_byte(kv, page, head - n_q_heads, slot, c0 * esz) : 0;
+      const int64_t k_hi = head >= n_q_heads ? k_pool_byte(kv, page, head - n_q_heads, slot, (half + c0) * esz) : 0;
+      if (head >= n_q_heads && kv.fp8) {
+        // 8-bit cache: the rotated key goes from fp32 straight to its code (one rounding)
+        uint2 ca = make_uint2(0u, 0u), cb = make_uint2(0u, 0u);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int w = w8 * 8 + i;
-      const int kvh = w / dh, c = w % dh;
-      const int64_t vi = (((int64_t)page * kv.n_kv_heads + kvh) * dh + c) * kv.page_size + slot;
-      // the value is a bf16 quantity in both forms of the cache (the 8-bit code is taken from it)
-      const bf16 vb = (bf16)f[i];
-      if (kv.fp8)
-        ((uint8_t*)kv.v_pool)[vi] = (uint8_t)f32_to_e4m3((float)vb / kv.v_scale);
-      else
-        vpool[vi] = vb;
+        for (int i = 0; i < 4; ++i) {
+          ca.x |= f32_to_e4m3(fra[i] / kv.k_scale) << (8 * i);
+          ca.y |= f32_to_e4m3(fra[4 + i] / kv.k_scale) << (8 * i);
+          cb.x |= f32_to_e4m3(frb[i] / kv.k_scale) << (8 * i);
+          cb.y |= f32_to_e4m3(frb[4 + i] / kv.k_scale) << (8 * i);
+        }
+        *reinterpret_cast<uint2*>((uint8_t*)kv.k_pool + k_lo) = ca;
+        *reinterpret_cast<uint2*>((uint8_t*)kv.k_pool + k_hi) = cb;
+        continue;
+      }
+      bf16x8 ra, rb;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        ra[i] = (bf16)fra[i];
+        rb[i] = (bf16)frb[i];
+      }
+      if (head < n_q_heads) {
+        st_bf16x8(hp + c0, ra);
+        st_bf16x8(hp + half + c0, rb);
+      } else {
+        st_bf16x8(reinterpret_cast<bf16*>((uint8_t*)kv.k_pool + k_lo), ra);
+        st_bf16x8(reinterpret_cast<bf16*>((uint8_t*)kv.k_pool + k_hi), rb);
+      }
+    } else {
+      const int c = (w - rot_units) * 8;  // value channel, counted through the heads
+      float fv[1][8];
+      proj8(fv, v_col + c);
+      const float(&f)[8] = fv[0];
+      if (v_to_row) {  // prefill: the values are appended page by page (v_append_pages_kernel)
+        bf16x8 o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = (bf16)f[i];
+        st_bf16x8(row + v_col + c, o);
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        // pools are [page][kv head][channel][16 slots]
+        const int64_t vi = ((int64_t)page * kv.n_kv_heads * dh + c + i) * kv.page_size + slot;
+        // the value is a bf16 quantity in both forms of the cache (the 8-bit code is taken from it)
+        const bf16 vb = (bf16)f[i];
+        if (kv.fp8)
+          ((uint8_t*)kv.v_pool)[vi] = (uint8_t)f32_to_e4m3((float)vb / kv.v_scale);
+        else
+          vpool[vi] = vb;
+      }
     }
   }
 }
@@ -462,16 +470,15 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
   if (n_tokens <= 0) return hipSuccess;
   // prefill: the values go page by page; decode (one token per request) has nothing to gather
   const int paged_v = ctx_lens == nullptr;
-  // with split-K partials to sum, 1024 threads per row keep all of a thread's loads in flight at once
-  if (splits > 1)
-    rope_kv_kernel<1024><<<n_tokens, 1024, 0, s>>>((bf16*)qkv, ld, n_q_heads, kv, rope_table, ctx_lens, cu_seqlens,
-                                                  n_seqs, block_tables, max_pages_per_seq, proj, splits, n_tokens,
-                                                  bias, paged_v);
-  else
-    rope_kv_kernel<256><<<n_tokens, 256, 0, s>>>((bf16*)qkv, ld, n_q_heads, kv, rope_table, ctx_lens, cu_seqlens,
-                                                 n_seqs, block_tables, max_pages_per_seq, proj, 1, n_tokens, bias,
-                                                 paged_v);
   const int dh = kv.head_dim;
+  const int units = (n_q_heads + kv.n_kv_heads) * (dh / 16) + kv.n_kv_heads * dh / 8;
+  const dim3 grid(n_tokens, splits > 1 || !paged_v ? (units + 255) / 256 : 1);
+  if (splits > 1)
+    rope_kv_kernel<2><<<grid, 256, 0, s>>>((bf16*)qkv, ld, n_q_heads, kv, rope_table, ctx_lens, cu_seqlens, n_seqs,
+                                           block_tables, max_pages_per_seq, proj, splits, n_tokens, bias, paged_v);
+  else
+    rope_kv_kernel<1><<<grid, 256, 0, s>>>((bf16*)qkv, ld, n_q_heads, kv, rope_table, ctx_lens, cu_seqlens, n_seqs,
+                                           block_tables, max_pages_per_seq, proj, 1, n_tokens, bias, paged_v);
   if (paged_v) {
     const dim3 vgrid((n_tokens >> 4) + n_seqs + 1, (kv.n_kv_heads * dh + kPageChannels - 1) / kPageChannels);
     const int v_col = (n_q_heads + kv.n_kv_heads) * dh;
