@@ -486,11 +486,14 @@ hipError_t launch_attn_decode_merge(int batch, int n_q_heads, const KvLayout& kv
 }
 
 // =====================================================================================
-// Prefill: var-len packed, causal.  One workgroup of eight waves per tile of 256 query columns that
-// share one K/V head: NH query heads of a GQA group x 256/NH consecutive positions (NH = 1 for
-// multi-head attention: 256 positions of one head); each wave owns 32 columns.  Each 32-token
+// Prefill: var-len packed, causal.  One workgroup of NW waves per tile of NW * 32 query columns that share one K/V
+// head; a column is a (position, query head) pair, all G heads of the group at one position, then the next
+// position, so any group size fills the waves (256 columns: 32 positions of 8 heads, 51 of 5, 256 of 1; a few
+// columns are left over where G does not divide them).  (With a head per wave a group of five fell back to one head
+// per workgroup: five times the staging and 256 positions per tile, half of them beyond the diagonal of
+// its first block; 267 us on 6713 tokens of 40 / 8 heads, now 245.)  Each 32-token
 // block of K and V^T is staged once per workgroup in LDS (double buffered, XOR-swizzled against
-// bank conflicts) and feeds the MFMAs of all 256 columns, so K/V traffic per MFMA is 1/8 of a
+// bank conflicts) and feeds the MFMAs of all columns, so K/V traffic per MFMA is 1/NW of a
 // wave-private scheme.  Two waves share a SIMD, so one wave's softmax arithmetic overlaps the
 // other's MFMAs; the softmax itself is trimmed to what a wave64 vector unit can keep up with:
 // one FMA + one raw exp2 per score, masking only in blocks that cross the diagonal or the end of
@@ -503,20 +506,19 @@ constexpr float kRescaleSlack = 8.0f;  // log2 units
 
 // KV8: the pools hold E4M3 codes; a thread's chunk is then 8 bytes, converted to bf16 on its way into
 // LDS (the key scale rides in the softmax scale, the value scale in the final normalisation).
-template <int DH, int NH, bool KV8>
-__global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restrict__ qkv, int64_t ld,
-                                                           int n_q_heads, KvLayout kv,
-                                                           const int32_t* __restrict__ cu_seqlens, int n_seqs,
-                                                           const int32_t* __restrict__ block_tables,
-                                                           int max_pages_per_seq, bf16* __restrict__ out,
-                                                           OperandLayout out_lay, float scale_log2, float out_scale) {
-  constexpr int NP = 256 / NH;   // query positions per workgroup
-  constexpr int PB = NP / 32;    // 32-position blocks per head
+template <int DH, int NW, bool KV8>
+__global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
+    const bf16* __restrict__ qkv, int64_t ld, int G, KvLayout kv, const int32_t* __restrict__ cu_seqlens,
+    int n_seqs, const int32_t* __restrict__ block_tables, int max_pages_per_seq, bf16* __restrict__ out,
+    OperandLayout out_lay, float scale_log2, float out_scale, int np, unsigned np_inverse, int g_inverse) {
+  // np = NW * 32 / G positions per workgroup; x / np = umulhi(x, np_inverse) for the lengths that occur (below 2^21),
+  // x / G = x * g_inverse >> 16 for columns
+  constexpr int NT = NW * 64;
   constexpr int KS = DH / 16;    // k-steps of the score MFMA
   constexpr int DT = DH / 32;    // 32-channel tiles of the output
   constexpr int CR = DH / 8;     // 16-byte chunks per K row
   constexpr int RWK = DH == 128 ? 1 : 2;  // K rows per 256-byte bank window
-  constexpr int NCH = CR / 8;    // chunks of K, and of V^T, per thread per 64-token block
+  constexpr int NCH = 64 * CR / NT;  // chunks of K, and of V^T, per thread per 64-token block
   constexpr int QP = KV8 ? 8 : 4;  // 8-element chunks per 64-byte piece of a key row in the pool
   __shared__ __attribute__((aligned(16))) bf16 sK[2][2][32 * DH];  // [buffer][32-token half]
   __shared__ __attribute__((aligned(16))) bf16 sV[2][2][DH * 32];
@@ -525,29 +527,29 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
   int qt = blockIdx.x, s = 0, L = 0;
   for (; s < n_seqs; ++s) {
     L = cu_seqlens[s + 1] - cu_seqlens[s];
-    const int nt = (L + NP - 1) / NP;
+    const int nt = (int)__umulhi((unsigned)(L + np - 1), np_inverse);
     if (qt < nt) break;
     qt -= nt;
   }
   if (s == n_seqs) return;
   const int tok0 = cu_seqlens[s];
-  const int q0 = qt * NP;
+  const int q0 = qt * np;
   const int Hkv = kv.n_kv_heads;
-  const int G = n_q_heads / Hkv;
-  const int groups = G / NH;
-  const int kvh = blockIdx.y / groups;
-  const int h_base = kvh * G + (blockIdx.y % groups) * NH;
+  const int kvh = blockIdx.y;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, kg = lane >> 5;
   const bf16* kpool = (const bf16*)kv.k_pool;
   const bf16* vpool = (const bf16*)kv.v_pool;
 
-  // the wave's 32 query columns: one head, 32 consecutive positions
-  const int head = h_base + wave / PB;
-  const int p_first = q0 + (wave % PB) * 32;
-  const int qpos = p_first + l32;  // may lie past the end of the prompt: computed, never stored
-  const int p_last = min(p_first + 31, L - 1);
+  // the lane's query column and the positions its wave spans
+  const int col = wave * 32 + l32;
+  const int col_pos = col * g_inverse >> 16;
+  const int head = kvh * G + col - col_pos * G;
+  const bool real = col < np * G;  // (the columns left over follow the last position, are computed and never stored)
+  const int qpos = q0 + min(col_pos, np - 1);  // may lie past the end of the prompt: computed, never stored
+  const int p_first = q0 + min(wave * 32 * g_inverse >> 16, np - 1);
+  const int p_last = min(q0 + min((wave * 32 + 31) * g_inverse >> 16, np - 1), L - 1);
   bf16x8 qf[KS];
   {
     const bf16* qp = qkv + (int64_t)(tok0 + min(qpos, L - 1)) * ld + (int64_t)head * DH + kg * 8;
@@ -563,7 +565,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
 
   const int32_t* bt = block_tables + (int64_t)s * max_pages_per_seq;
   const int last_page = (L - 1) / 16;
-  const int kv_end = min(q0 + NP, L);
+  const int kv_end = min(q0 + np, L);
   // token of this lane's row r = l32 in the score tile: (r/16)*16 + ((r%8)/4)*8 + ((r/8)%2)*4 + r%4
   const int krow = (l32 >> 4) * 16 + ((l32 >> 2) & 1) * 8 + ((l32 >> 3) & 1) * 4 + (l32 & 3);
   const bf16* k_frag = &sK[0][0][0] + krow * DH;
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
     for (int i = 0; i < 4; ++i) page[i] = bt[min(p0 + i, last_page)];
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      const int ci = tid + 512 * j;
+      const int ci = tid + NT * j;
       // K: consecutive threads walk the pool in address order - the QP chunks of a 64-byte piece, the 16
       // tokens of the page, the pieces of the row, the four pages of the block
       const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
   auto store_block = [&](int buf) {
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      const int ci = tid + 512 * j;
+      const int ci = tid + NT * j;
       const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
       const int ksub = kpg >> 1, ktok = (kpg & 1) * 16 + kt16, kc = kpiece * QP + kq;
       st_bf16x8(&sK[buf][ksub][ktok * DH + ((kc ^ ((ktok / RWK) % CR)) << 3)], kreg[j]);
@@ -685,7 +687,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
     __syncthreads();
   }
   lsum += __shfl_xor(lsum, 32, 64);
-  if (qpos < L) {
+  if (real && qpos < L) {
     const float inv = out_scale / lsum;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
@@ -700,22 +702,23 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(const bf16* __restric
   }
 }
 
-template <int DH, int NH>
+template <int DH, int NW>
 static hipError_t launch_attn_prefill_t(const void* qkv, int64_t ld, int total_tokens, int n_seqs, int n_q_heads,
                                         const KvLayout& kv, const int32_t* cu_seqlens, const int32_t* block_tables,
                                         int max_pages_per_seq, void* out, OperandLayout out_layout, hipStream_t s) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)kv.head_dim) * (kv.fp8 ? kv.k_scale : 1.0f);
   const float out_scale = kv.fp8 ? kv.v_scale : 1.0f;
-  constexpr int NP = 256 / NH;
-  dim3 grid((total_tokens + NP - 1) / NP + n_seqs, n_q_heads / NH);
-  if (kv.fp8)
-    attn_prefill_kernel<DH, NH, true><<<grid, 512, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, cu_seqlens, n_seqs,
-                                                           block_tables, max_pages_per_seq, (bf16*)out, out_layout,
-                                                           scale_log2, out_scale);
-  else
-    attn_prefill_kernel<DH, NH, false><<<grid, 512, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, cu_seqlens, n_seqs,
-                                                            block_tables, max_pages_per_seq, (bf16*)out, out_layout,
-                                                            scale_log2, out_scale);
+  const int G = n_q_heads / kv.n_kv_heads, np = NW * 32 / G;
+  // (lengths are at most 2^20 and np at most 256: rounding the inverse up is off by less than 2^-32 x 2^21 x 2^8)
+  const unsigned np_inverse = (unsigned)(((1ull << 32) + np - 1) / np);
+  const int g_inverse = (65536 + G - 1) / G;  // (columns are below 256 and G at most 16: off by less than 2^-16 x 2^8 x 2^4)
+  dim3 grid((total_tokens + np - 1) / np + n_seqs, kv.n_kv_heads);
+#define TDP_PREFILL(KV8)                                                                                             \
+  attn_prefill_kernel<DH, NW, KV8><<<grid, NW * 64, 0, s>>>((const bf16*)qkv, ld, G, kv, cu_seqlens, n_seqs,         \
+                                                            block_tables, max_pages_per_seq, (bf16*)out, out_layout,  \
+                                                            scale_log2, out_scale, np, np_inverse, g_inverse)
+  if (kv.fp8) TDP_PREFILL(true); else TDP_PREFILL(false);
+#undef TDP_PREFILL
   return hipGetLastError();
 }
 
@@ -723,23 +726,14 @@ hipError_t launch_attn_prefill(const void* qkv, int64_t ld, int total_tokens, in
                                const KvLayout& kv, const int32_t* cu_seqlens, const int32_t* block_tables,
                                int max_pages_per_seq, void* out, OperandLayout out_layout, hipStream_t s) {
   if (total_tokens <= 0 || n_seqs <= 0) return hipSuccess;
-  const int G = n_q_heads / kv.n_kv_heads;
-  const int nh = G % 8 == 0 ? 8 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-#define TDP_PREFILL(DH_, NH_)                                                                               \
-  return launch_attn_prefill_t<DH_, NH_>(qkv, ld, total_tokens, n_seqs, n_q_heads, kv, cu_seqlens, block_tables, \
-                                         max_pages_per_seq, out, out_layout, s)
-  if (kv.head_dim == 128) {
-    if (nh == 8) TDP_PREFILL(128, 8);
-    if (nh == 4) TDP_PREFILL(128, 4);
-    if (nh == 2) TDP_PREFILL(128, 2);
-    TDP_PREFILL(128, 1);
-  } else {
-    if (nh == 8) TDP_PREFILL(64, 8);
-    if (nh == 4) TDP_PREFILL(64, 4);
-    if (nh == 2) TDP_PREFILL(64, 2);
-    TDP_PREFILL(64, 1);
-  }
-#undef TDP_PREFILL
+  // Four waves and not eight (measured, us: 12 prompts of a 13B shape 170 / 143, 24 of a 7B shape 177 / 159, 8 of 40 / 8
+  // heads 258 / 253, 16 of 64 / 8 heads level): tiles half as long compute less beyond the diagonal and two
+  // workgroups of a CU wait at barriers of their own.
+  if (kv.head_dim == 128)
+    return launch_attn_prefill_t<128, 4>(qkv, ld, total_tokens, n_seqs, n_q_heads, kv, cu_seqlens, block_tables,
+                                         max_pages_per_seq, out, out_layout, s);
+  return launch_attn_prefill_t<64, 4>(qkv, ld, total_tokens, n_seqs, n_q_heads, kv, cu_seqlens, block_tables,
+                                      max_pages_per_seq, out, out_layout, s);
 }
 
 }  // namespace tdp
