@@ -490,8 +490,8 @@ hipError_t launch_attn_decode_merge(int batch, int n_q_heads, const KvLayout& kv
 // head; a column is a (position, query head) pair, all G heads of the group at one position, then the next
 // position, so any group size fills the waves (256 columns: 32 positions of 8 heads, 51 of 5, 256 of 1; a few
 // columns are left over where G does not divide them).  (With a head per wave a group of five fell back to one head
-// per workgroup: five times the staging and 256 positions per tile, half of them beyond the diagonal of
-// its first block; 267 us on 6713 tokens of 40 / 8 heads, now 245.)  Each 32-token
+// per workgroup: five times the staging and 256 positions per tile; 267 us on 6713 tokens of 40 / 8 heads, 245 with pairs
+// and 207 with the order of the tiles below.)  Each 32-token
 // block of K and V^T is staged once per workgroup in LDS (double buffered, XOR-swizzled against
 // bank conflicts) and feeds the MFMAs of all columns, so K/V traffic per MFMA is 1/NW of a
 // wave-private scheme.  Two waves share a SIMD, so one wave's softmax arithmetic overlaps the
@@ -523,8 +523,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
   __shared__ __attribute__((aligned(16))) bf16 sK[2][2][32 * DH];  // [buffer][32-token half]
   __shared__ __attribute__((aligned(16))) bf16 sV[2][2][DH * 32];
 
-  // locate the sequence that owns query tile blockIdx.x
-  int qt = blockIdx.x, s = 0, L = 0;
+  // locate the sequence that owns the query tile
+  const int Hkv = kv.n_kv_heads;
+  // K/V heads are numbered fastest: workgroups go round-robin to the 8 XCDs, so with a multiple of eight heads every tile
+  // of a head reads K/V through the same L2.  The last tiles come first: within a prompt they are the longest.
+  const int tile = blockIdx.x / Hkv, kvh = blockIdx.x - tile * Hkv;
+  int qt = (int)gridDim.x / Hkv - 1 - tile, s = 0, L = 0;
   for (; s < n_seqs; ++s) {
     L = cu_seqlens[s + 1] - cu_seqlens[s];
     const int nt = (int)__umulhi((unsigned)(L + np - 1), np_inverse);
@@ -534,8 +538,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
   if (s == n_seqs) return;
   const int tok0 = cu_seqlens[s];
   const int q0 = qt * np;
-  const int Hkv = kv.n_kv_heads;
-  const int kvh = blockIdx.y;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, kg = lane >> 5;
@@ -712,7 +714,7 @@ static hipError_t launch_attn_prefill_t(const void* qkv, int64_t ld, int total_t
   // (lengths are at most 2^20 and np at most 256: rounding the inverse up is off by less than 2^-32 x 2^21 x 2^8)
   const unsigned np_inverse = (unsigned)(((1ull << 32) + np - 1) / np);
   const int g_inverse = (65536 + G - 1) / G;  // (columns are below 256 and G at most 16: off by less than 2^-16 x 2^8 x 2^4)
-  dim3 grid((total_tokens + np - 1) / np + n_seqs, kv.n_kv_heads);
+  const unsigned grid = (unsigned)((total_tokens + np - 1) / np + n_seqs) * kv.n_kv_heads;
 #define TDP_PREFILL(KV8)                                                                                             \
   attn_prefill_kernel<DH, NW, KV8><<<grid, NW * 64, 0, s>>>((const bf16*)qkv, ld, G, kv, cu_seqlens, n_seqs,         \
                                                             block_tables, max_pages_per_seq, (bf16*)out, out_layout,  \
