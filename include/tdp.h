@@ -295,9 +295,9 @@ TDP_API int tdp_probe_mfma_bf16(int32_t iters, int32_t launches, int32_t random_
  * Timing hooks: when enabled, prefill/decode record HIP events around each kernel class on the
  * call's stream; tdp_stage_timing_read synchronises and returns the summed milliseconds of the
  * most recent call per class (order: rmsnorm, gemm_qkv, rope_kv, attention, gemm_o, gemm_gate_up,
- * gemm_down, attention_merge) into ms[8].  "attention" is the attention kernel alone (prefill or
- * decode), "attention_merge" the kernel that combines the partial results of decode requests longer
- * than one span (0 in prefill, and when no request of the batch can be that long).
+ * gemm_down, attention_merge) into ms[8].  "attention" is the attention kernel (prefill or
+ * decode).  The partial results of decode requests longer than one span are combined inside it, so
+ * "attention_merge", the class of the separate kernel that used to do that, reads 0.
  */
 TDP_API int tdp_stage_timing_enable(tdp_stage* st, int32_t on);
 TDP_API int tdp_stage_timing_read(tdp_stage* st, float* ms /* host [8] */);

@@ -16,14 +16,23 @@
 
 namespace tdp {
 
+// Floats past the caches of an XCD, for workgroups of other XCDs in the same launch.
+__device__ __forceinline__ void store_agent(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_agent2(const float* p) {  // (8-byte aligned)
+  return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT));
+}
+
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for -inf: exp2 gives exactly 0, no inf-inf
 
 // =====================================================================================
 // Decode.  Work item = (request, span of span_len tokens of its context); one workgroup
 // of four waves per (item, kv head).  The four waves split the span's 32-token blocks evenly and
 // merge their partial softmax states through LDS; a request whose context fits one span is
-// finished there (no partials in HBM), longer ones leave one partial per span for the merge
-// kernel.  The item list is compact (built once per decode step by attn_plan_kernel), so the grid
+// finished there (no partials in HBM), longer ones leave one partial per span, which the workgroup
+// that finishes last combines.  The item list is compact (built once per decode step by attn_plan_kernel), so the grid
 // holds no workgroup that finds nothing to do except at its very end.
 // Keys and values are requested as non-temporal: a launch reads each of them exactly once, and as
 // ordinary loads they evict everything else from L2 on their way through (measured: 5.9 TB/s against
@@ -134,7 +143,8 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
                                                           const int4* __restrict__ items,
                                                           const int32_t* __restrict__ item_pages,
                                                           float* __restrict__ part_o, float* __restrict__ part_ml,
-                                                          int max_spans, int span_len, bf16* __restrict__ out,
+                                                          unsigned* __restrict__ spans_done, int max_spans,
+                                                          int span_len, bf16* __restrict__ out,
                                                           OperandLayout out_lay, float scale_log2, float out_scale) {
   constexpr int KS = DH / 32;          // k-steps of the score MFMA
   constexpr int DT = DH / 16;          // 16-channel tiles of the output
@@ -389,36 +399,70 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
       out[operand_offset(out_lay, b, h * DH + c)] = (bf16)(num / den * out_scale);
     } else {
       const int64_t slot = ((int64_t)b * n_q_heads + h) * max_spans + span;
-      part_o[slot * DH + c] = num;
+      store_agent(part_o + slot * DH + c, num);
       if (c == 0) {
-        part_ml[slot * 2 + 0] = mt;
-        part_ml[slot * 2 + 1] = den;
+        store_agent(part_ml + slot * 2 + 0, mt);
+        store_agent(part_ml + slot * 2 + 1, den);
       }
     }
   }
-}
-
-// Requests longer than one span: out = sum_s o_s 2^(m_s - m) / sum_s l_s 2^(m_s - m).
-template <int DH>
-__global__ __launch_bounds__(DH) void attn_decode_merge_kernel(const float* __restrict__ part_o,
-                                                               const float* __restrict__ part_ml,
-                                                               const int32_t* __restrict__ ctx_lens,
-                                                               int n_q_heads, int max_spans, int span_len,
-                                                               bf16* __restrict__ out, OperandLayout out_lay,
-                                                               float out_scale) {
-  const int h = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
-  const int n_spans = min((ctx_lens[b] + span_len) / span_len, max_spans);
-  if (n_spans <= 1) return;  // finished by the attention kernel itself
-  const int64_t base = ((int64_t)b * n_q_heads + h) * max_spans;
-  float m = kNegBig;
-  for (int k = 0; k < n_spans; ++k) m = fmaxf(m, part_ml[(base + k) * 2]);
-  float num = 0.f, den = 0.f;
-  for (int k = 0; k < n_spans; ++k) {
-    const float w = exp2f(part_ml[(base + k) * 2] - m);
-    den += w * part_ml[(base + k) * 2 + 1];
-    num += w * part_o[(base + k) * DH + c];
+  if (n_spans == 1) return;
+  // ---- a request of several spans: whoever finishes last combines them, in the order of the spans whoever that is,
+  //   out = sum_k o_k 2^(m_k - m) / sum_k l_k 2^(m_k - m).
+  // The spans of a request are made on different XCDs, whose L2s do not see each other: partials are stored
+  // and read at agent scope (past the L2), each wave waits until its stores have arrived, and only then is the span
+  // counted.  The last one puts the counter back to zero for the next launch.  (A second kernel did this: a launch of 4.5 to
+  // 5 us in every layer for small batches, 10 us for 512 requests, nearly all of its workgroups with nothing to do.)
+  __shared__ int s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned* done = spans_done + (int64_t)b * Hkv + kvh;
+    const unsigned before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = before + 1 == (unsigned)n_spans;
+    if (s_last) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  out[operand_offset(out_lay, b, h * DH + c)] = (bf16)(num / den * out_scale);
+  __syncthreads();
+  if (!s_last) return;
+  // four channels of one query head per thread; eight spans are asked for at once, so up to eight cost one round trip
+  constexpr int UN = 8;
+  for (int e = threadIdx.x; e < G * (DH / 4); e += 256) {
+    const int q = e / (DH / 4), c = e % (DH / 4) * 4, h = kvh * G + q;
+    const int64_t base = ((int64_t)b * n_q_heads + h) * max_spans;
+    float2 ml[UN], oa[UN], ob[UN];
+    auto fetch = [&](int k0) {
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int64_t slot = base + min(k0 + u, n_spans - 1);
+        ml[u] = load_agent2(part_ml + slot * 2);
+        oa[u] = load_agent2(part_o + slot * DH + c);
+        ob[u] = load_agent2(part_o + slot * DH + c + 2);
+      }
+    };
+    fetch(0);
+    float mt = kNegBig;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) mt = fmaxf(mt, ml[u].x);  // (past the end: the last span again)
+    for (int k = UN; k < n_spans; ++k) mt = fmaxf(mt, load_agent2(part_ml + (base + k) * 2).x);
+    float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+    for (int k0 = 0; k0 < n_spans; k0 += UN) {
+      if (k0 > 0) fetch(k0);
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        if (k0 + u >= n_spans) break;
+        const float w = exp2f(ml[u].x - mt);
+        den += w * ml[u].y;
+        num[0] += w * oa[u].x;
+        num[1] += w * oa[u].y;
+        num[2] += w * ob[u].x;
+        num[3] += w * ob[u].y;
+      }
+    }
+    bf16x4 o4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o4[i] = (bf16)(num[i] / den * out_scale);
+    *reinterpret_cast<bf16x4*>(out + operand_offset(out_lay, b, h * DH + c)) = o4;
+  }
 }
 
 // Span length.  A workgroup's fixed costs (start-up, the merge of its four waves, its partial
@@ -448,7 +492,8 @@ hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables
 
 hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_heads, const KvLayout& kv,
                               const int4* items, const int32_t* item_pages, float* part_o, float* part_ml,
-                              int max_spans, int span_len, void* out, OperandLayout out_layout, hipStream_t s) {
+                              unsigned* spans_done, int max_spans, int span_len, void* out, OperandLayout out_layout,
+                              hipStream_t s) {
   if (batch <= 0) return hipSuccess;
   // 8-bit pools hold value / scale: the key scale joins the softmax scale, the value scale the final division
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)kv.head_dim) * (kv.fp8 ? kv.k_scale : 1.0f);
@@ -457,31 +502,14 @@ hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_he
   const unsigned grid = (unsigned)max_items * kv.n_kv_heads;
 #define TDP_DECODE(DH, KV8)                                                                                        \
   attn_decode_kernel<DH, KV8><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, items, item_pages, part_o, \
-                                                   part_ml, max_spans, span_len, (bf16*)out, out_layout,          \
-                                                   scale_log2, out_scale)
+                                                   part_ml, spans_done, max_spans, span_len, (bf16*)out,          \
+                                                   out_layout, scale_log2, out_scale)
   if (kv.head_dim == 128) {
     if (kv.fp8) TDP_DECODE(128, true); else TDP_DECODE(128, false);
   } else {
     if (kv.fp8) TDP_DECODE(64, true); else TDP_DECODE(64, false);
   }
 #undef TDP_DECODE
-  return hipGetLastError();
-}
-
-hipError_t launch_attn_decode_merge(int batch, int n_q_heads, const KvLayout& kv, const int32_t* ctx_lens,
-                                    const float* part_o, const float* part_ml, int max_spans, int span_len, void* out,
-                                    OperandLayout out_layout, hipStream_t s) {
-  if (batch <= 0) return hipSuccess;
-  // with one span per request at most, every request was finished by the attention kernel itself
-  if (attn_decode_items(batch, max_spans, span_len) / batch <= 1) return hipSuccess;
-  const float out_scale = kv.fp8 ? kv.v_scale : 1.0f;
-  dim3 mgrid(n_q_heads, batch);
-  if (kv.head_dim == 128)
-    attn_decode_merge_kernel<128><<<mgrid, 128, 0, s>>>(part_o, part_ml, ctx_lens, n_q_heads, max_spans, span_len,
-                                                        (bf16*)out, out_layout, out_scale);
-  else
-    attn_decode_merge_kernel<64><<<mgrid, 64, 0, s>>>(part_o, part_ml, ctx_lens, n_q_heads, max_spans, span_len,
-                                                      (bf16*)out, out_layout, out_scale);
   return hipGetLastError();
 }
 

@@ -32,7 +32,7 @@ int fail_hip(hipError_t e, const char* what) {
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
-enum TimeClass { T_NORM = 0, T_QKV, T_ROPE, T_ATTN, T_O, T_GU, T_DOWN, T_MERGE, T_COUNT };
+enum TimeClass { T_NORM = 0, T_QKV, T_ROPE, T_ATTN, T_O, T_GU, T_DOWN, T_MERGE, T_COUNT };  // T_MERGE: no kernel of its own any more, reads 0
 
 }  // namespace
 
@@ -60,6 +60,7 @@ struct tdp_stage {
     float *h = nullptr, *xa = nullptr, *xb = nullptr;  // residual stream, fp32 between layers
     float* ws = nullptr;
     float *part_o = nullptr, *part_ml = nullptr;
+    unsigned* spans_done = nullptr;  // finished spans of every (request, K/V head): zero between launches
     int4* attn_items = nullptr;     // decode work list, rebuilt every step
     int32_t* attn_n_items = nullptr;
     int32_t* attn_item_pages = nullptr;  // physical pages of every item's span
@@ -228,15 +229,11 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
       Timer t(st, s, timed, T_ATTN);
       if (ctx_lens)
         HIP_TRY(launch_attn_decode(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, sc.attn_items, sc.attn_item_pages,
-                                   sc.part_o, sc.part_ml, st->max_chunks, span_len, sc.attn, layout_paired(st->dq), s));
+                                   sc.part_o, sc.part_ml, sc.spans_done, st->max_chunks, span_len, sc.attn,
+                                   layout_paired(st->dq), s));
       else
         HIP_TRY(launch_attn_prefill(sc.qkv, st->Nqkv_pad, M, n_seqs, c.n_q_heads, kv, cu_seqlens, block_tables,
                                     c.max_pages_per_seq, sc.attn, layout_paired(st->dq), s));
-    }
-    if (ctx_lens) {  // a4, second kernel: requests longer than one span are combined from their partials
-      Timer t(st, s, timed, T_MERGE);
-      HIP_TRY(launch_attn_decode_merge(M, c.n_q_heads, kv, ctx_lens, sc.part_o, sc.part_ml, st->max_chunks, span_len,
-                                       sc.attn, layout_paired(st->dq), s));
     }
     {  // a5: output projection + residual -> h (fp32)
       Timer t(st, s, timed, T_O);
@@ -352,6 +349,7 @@ int tdp_stage_create(const tdp_stage_config* cfg, tdp_stage** out) {
     }
     A(&sc.part_o, mb * c.n_q_heads * st->max_chunks * dh, false);
     A(&sc.part_ml, mb * c.n_q_heads * st->max_chunks * 2, false);
+    A(&sc.spans_done, mb * c.n_kv_heads, true);
     A(&sc.attn_items, mb * st->max_chunks, false);
     // spans longer than the minimum round the span count up: up to (1024 / 256 - 1) extra minimum spans' worth
     A(&sc.attn_item_pages, mb * (st->max_chunks + kDecodeSpanMax / kDecodeSpanMin) * (kDecodeSpanMin / 16), false);
@@ -394,7 +392,7 @@ void tdp_stage_destroy(tdp_stage* st) {
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (tdp_stage::Scratch& sc : st->sc) {
-    void* sp[] = {sc.y, sc.qkv, sc.qkv32, sc.attn, sc.h, sc.u, sc.xa, sc.xb, sc.ws, sc.part_o, sc.part_ml, sc.attn_items,
+    void* sp[] = {sc.y, sc.qkv, sc.qkv32, sc.attn, sc.h, sc.u, sc.xa, sc.xb, sc.ws, sc.part_o, sc.part_ml, sc.spans_done, sc.attn_items,
                   sc.attn_n_items, sc.attn_item_pages};
     for (void* p : sp)
       if (p) (void)hipFree(p);
