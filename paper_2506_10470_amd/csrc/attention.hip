@@ -141,7 +141,8 @@ template <int DH, bool KV8>
 __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restrict__ qkv, int64_t ld,
                                                           int n_q_heads, KvLayout kv,
                                                           const int4* __restrict__ items,
-                                                          const int32_t* __restrict__ item_pages,
+                                                          const int32_t* __restrict__ item_pages, int item_pitch,
+                                                          const int32_t* __restrict__ ctx_lens,
                                                           float* __restrict__ part_o, float* __restrict__ part_ml,
                                                           unsigned* __restrict__ spans_done, int max_spans,
                                                           int span_len, bf16* __restrict__ out,
@@ -161,11 +162,14 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   int my_pages[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    my_pages[j] = item_pages[(int64_t)item * pages_per_span + min(lane + 64 * j, pages_per_span - 1)];
-  const int4 it = items[item];
+    my_pages[j] = item_pages[(int64_t)item * item_pitch + min(lane + 64 * j, item_pitch - 1)];
+  // without a work list (see attn_decode_planned) item b is the whole context of request b and its pages are the block table's
+  // row, whose entries behind the request's last page are not page ids and are not used
+  const int4 it = items ? items[item] : make_int4(item, 0, ctx_lens[item] + 1, 0);
   if (it.x < 0) return;
   const int b = it.x, span = it.y;
   const int n_total = it.z;  // ctx + 1: the new token's K/V were appended before this kernel
+  const int last_entry = items ? pages_per_span - 1 : (n_total - 1) >> 4;
   const int s_begin = span * span_len;
   const int s_end = min(s_begin + span_len, n_total);
   const int G = n_q_heads / Hkv;
@@ -227,7 +231,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
       const int pi = (tb >> 4) - page_base;
       int64_t page[BT / 16];
 #pragma unroll
-      for (int j = 0; j < BT / 16; ++j) page[j] = page_of(min(pi + j, pages_per_span - 1));
+      for (int j = 0; j < BT / 16; ++j) page[j] = page_of(min(pi + j, last_entry));
       if constexpr (KV8) {
         // score tile t, row r16 -> token (r16/4)*16 + t*4 + r16%4: page r16/4 of the block, slot t*4 + r16%4
         const int64_t kpage = (r16 >> 2) == 0 ? page[0] : (r16 >> 2) == 1 ? page[1] : (r16 >> 2) == 2 ? page[2] : page[3];
@@ -254,7 +258,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
       const int pi = (tb >> 4) - page_base;
       int64_t page[BT / 16];  // the look-up index must be wave-uniform: all pages first, then the lane's pick
 #pragma unroll
-      for (int j = 0; j < BT / 16; ++j) page[j] = page_of(min(pi + j, pages_per_span - 1));
+      for (int j = 0; j < BT / 16; ++j) page[j] = page_of(min(pi + j, last_entry));
       if constexpr (KV8) {
         // channel r16 of tile d, the 16 tokens of page kg of the block
         const int64_t vpage = kg == 0 ? page[0] : kg == 1 ? page[1] : kg == 2 ? page[2] : page[3];
@@ -480,6 +484,14 @@ int attn_decode_items(int batch, int max_spans, int span_len) {
   return batch * ((max_spans * kDecodeSpanMin + span_len - 1) / span_len);
 }
 
+// Whether a decode step makes a work list.  Without one a workgroup's look-ups are the request's length and its table row.
+// The list is what orders work (longest first) and cuts it into spans: with at most one span per request and no more
+// workgroups than run at once (three per CU) it does neither, and its launch was 4 of 67 us of a two-layer step of
+// the toy shape with four requests.
+bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len) {
+  return attn_decode_items(batch, max_spans, span_len) > batch || batch * n_kv_heads > 3 * 256;
+}
+
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
                             int max_spans, int span_len, int4* items, int32_t* n_items, int32_t* item_pages,
                             hipStream_t s) {
@@ -491,9 +503,9 @@ hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables
 }
 
 hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_heads, const KvLayout& kv,
-                              const int4* items, const int32_t* item_pages, float* part_o, float* part_ml,
-                              unsigned* spans_done, int max_spans, int span_len, void* out, OperandLayout out_layout,
-                              hipStream_t s) {
+                              const int4* items, const int32_t* item_pages, int item_pitch, const int32_t* ctx_lens,
+                              float* part_o, float* part_ml, unsigned* spans_done, int max_spans, int span_len,
+                              void* out, OperandLayout out_layout, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
   // 8-bit pools hold value / scale: the key scale joins the softmax scale, the value scale the final division
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)kv.head_dim) * (kv.fp8 ? kv.k_scale : 1.0f);
@@ -501,8 +513,9 @@ hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_he
   const int max_items = attn_decode_items(batch, max_spans, span_len);
   const unsigned grid = (unsigned)max_items * kv.n_kv_heads;
 #define TDP_DECODE(DH, KV8)                                                                                        \
-  attn_decode_kernel<DH, KV8><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, items, item_pages, part_o, \
-                                                   part_ml, spans_done, max_spans, span_len, (bf16*)out,          \
+  attn_decode_kernel<DH, KV8><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, items, item_pages,         \
+                                                   item_pitch, ctx_lens, part_o, part_ml, spans_done, max_spans, \
+                                                   span_len, (bf16*)out,                                         \
                                                    out_layout, scale_log2, out_scale)
   if (kv.head_dim == 128) {
     if (kv.fp8) TDP_DECODE(128, true); else TDP_DECODE(128, false);

@@ -176,7 +176,8 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
   const void* x = hidden_in;
   int x_f32 = 0;
   const int span_len = st->decode_span > 0 ? st->decode_span : attn_decode_span(M, c.n_kv_heads);
-  if (ctx_lens)
+  const bool planned = ctx_lens && attn_decode_planned(M, c.n_kv_heads, st->max_chunks, span_len);
+  if (planned)
     HIP_TRY(launch_attn_plan(ctx_lens, block_tables, c.max_pages_per_seq, M, st->max_chunks, span_len, sc.attn_items,
                              sc.attn_n_items, sc.attn_item_pages, s));
   const int l_begin = st->layer_count > 0 ? st->layer_first : 0;
@@ -228,7 +229,9 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
     {  // a4: attention
       Timer t(st, s, timed, T_ATTN);
       if (ctx_lens)
-        HIP_TRY(launch_attn_decode(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, sc.attn_items, sc.attn_item_pages,
+        HIP_TRY(launch_attn_decode(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, planned ? sc.attn_items : nullptr,
+                                   planned ? sc.attn_item_pages : block_tables,
+                                   planned ? span_len / 16 : c.max_pages_per_seq, ctx_lens,
                                    sc.part_o, sc.part_ml, sc.spans_done, st->max_chunks, span_len, sc.attn,
                                    layout_paired(st->dq), s));
       else
