@@ -41,7 +41,8 @@ struct GemmParams {
   int tiles_m, tiles_n;
   // order of the tiles, see gemm_tile_of_block: bands of band_h + 1 (the first n_tall) or band_h rows of tiles; an
   // XCD takes `chunks` runs of `chunk` tiles, and an eighth of the `rest` tiles behind them
-  int band_h, n_tall, chunk, chunks, rest;
+  int band_h, n_tall, chunk_shift, chunks, rest;
+  unsigned per_split_inv, tall_inv, low_inv, h_tall_inv, h_low_inv;  // see divide
 };
 
 // silu(z) = z / (1 + e^-z), with the hardware reciprocal (1 ulp) in place of an IEEE division: the
@@ -177,34 +178,41 @@ __device__ __forceinline__ void gemm_epilogue16_residual(const GemmParams& p, f3
 // corners could lie outside the matrix: the workgroups that found nothing to do sat at regular ids, and
 // as the dispatcher hands out ids to the four shader engines of an XCD in turn, two of them got all the
 // work: with three or six rows of tiles a launch took twice its time, 121 us against 61 at M = 384 on 10240 x 8192.)
+// (The look-up stands in front of a workgroup's first request, so its divisions are by multiplication: x / d =
+// umulhi(x, ceil(2^32 / d)) while x * d < 2^32, 0 standing for d = 1 and for divisors where that does not hold.)
+__device__ __forceinline__ int divide(int x, int d, unsigned inv) {
+  return inv ? (int)__umulhi((unsigned)x, inv) : d == 1 ? x : x / d;
+}
 __device__ __forceinline__ bool gemm_tile_of_block(const GemmParams& p, int& tile_m, int& tile_n, int& split) {
   const int xcd = blockIdx.x & 7;
   int local = blockIdx.x >> 3;
   int t;
-  if (local < p.chunks * p.chunk) {
-    t = (local / p.chunk * 8 + xcd) * p.chunk + local % p.chunk;
+  const int whole = p.chunks << p.chunk_shift;  // tiles of this XCD that come in whole runs
+  if (local < whole) {
+    const int run = local >> p.chunk_shift;
+    t = ((run * 8 + xcd) << p.chunk_shift) + (local - (run << p.chunk_shift));
   } else {
-    local -= p.chunks * p.chunk;
+    local -= whole;
     const int q = p.rest >> 3, r = p.rest & 7;
     if (local >= q + (xcd < r ? 1 : 0)) return false;
-    t = p.chunks * p.chunk * 8 + xcd * q + min(xcd, r) + local;
+    t = whole * 8 + xcd * q + min(xcd, r) + local;
   }
-  split = t / (p.tiles_m * p.tiles_n);
-  t -= split * (p.tiles_m * p.tiles_n);
+  const int per_split = p.tiles_m * p.tiles_n;
+  split = divide(t, per_split, p.per_split_inv);
+  t -= split * per_split;
   const int tall = (p.band_h + 1) * p.tiles_n, low = p.band_h * p.tiles_n;  // tiles per band
-  int h = p.band_h + 1;
-  tile_m = 0;
   if (t < p.n_tall * tall) {
-    tile_m = t / tall * h;
-    t %= tall;
+    const int band = divide(t, tall, p.tall_inv);
+    t -= band * tall;
+    tile_n = divide(t, p.band_h + 1, p.h_tall_inv);
+    tile_m = band * (p.band_h + 1) + t - tile_n * (p.band_h + 1);
   } else {
     t -= p.n_tall * tall;
-    h = p.band_h;
-    tile_m = p.n_tall * (p.band_h + 1) + t / low * h;
-    t %= low;
+    const int band = divide(t, low, p.low_inv);
+    t -= band * low;
+    tile_n = divide(t, p.band_h, p.h_low_inv);
+    tile_m = p.n_tall * (p.band_h + 1) + band * p.band_h + t - tile_n * p.band_h;
   }
-  tile_n = t / h;
-  tile_m += t % h;
   return true;
 }
 
@@ -272,6 +280,7 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
   // taken out of the per-lane offsets again.  The per-lane offset is zero-extended by the hardware
   // and must not go negative: a constant bias keeps it positive and is subtracted from the bases.
   constexpr int kImmBias = 3 * 1024;
+  const int valid = min(BM, p.M - m0), spread = (1 << (31 - __builtin_clz(valid))) - 1;
   unsigned a_goff[IPA];  // bytes
 #pragma unroll
   for (int j = 0; j < IPA; ++j) {
@@ -279,7 +288,7 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
     const int c_sw = (lane % CPR) ^ ((row / RW) % CPR);
     // rows past M are computed but never stored; they re-read the tile's valid rows in turn (all of
     // them reading the last valid row makes one hot line for every workgroup of the launch)
-    const int m = row % min(BM, p.M - m0);
+    const int m = row < valid ? row : row & spread;
     a_goff[j] = 2u * (unsigned)(operand_row_offset(p.a_lay, m) + c_sw * 8) + (unsigned)(kImmBias - j * 1024);
   }
   // weight rows need no clamp; the swizzle term (row / RW) % CPR does not depend on the row block j
@@ -668,9 +677,15 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.band_h = p.tiles_m / bands;
   p.n_tall = p.tiles_m % bands;
   const int tiles = p.tiles_m * p.tiles_n * splits;
-  p.chunk = 32 * ti.wg_per_cu;
-  p.chunks = tiles / (8 * p.chunk);
-  p.rest = tiles - p.chunks * 8 * p.chunk;
+  p.chunk_shift = 5 + (ti.wg_per_cu > 2 ? 2 : ti.wg_per_cu - 1);  // (an XCD's slots, or the next power of two)
+  p.chunks = tiles >> (3 + p.chunk_shift);
+  p.rest = tiles - (p.chunks << (3 + p.chunk_shift));
+  auto inverse = [&](int64_t d) { return d > 1 && d * tiles < (1ll << 32) ? (unsigned)(((1ll << 32) + d - 1) / d) : 0u; };
+  p.per_split_inv = inverse((int64_t)p.tiles_m * p.tiles_n);
+  p.tall_inv = inverse((int64_t)(p.band_h + 1) * p.tiles_n);
+  p.low_inv = inverse((int64_t)p.band_h * p.tiles_n);
+  p.h_tall_inv = inverse(p.band_h + 1);
+  p.h_low_inv = inverse(p.band_h);
   if (g_print_plan)
     fprintf(stderr, "gemm plan: M=%d N=%lld K=%lld tile=%d tiles=%dx%d splits=%d (k-tiles %d each)\n",
             a.M, (long long)a.Npad, (long long)a.Kpad, plan.tile, p.tiles_m, p.tiles_n, splits, p.k_tiles_per_split);
