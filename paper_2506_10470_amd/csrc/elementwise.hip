@@ -36,40 +36,38 @@ __device__ __forceinline__ void load8(const void* row, int c, float (&f)[8]) {
 }
 
 template <bool F32_IN>
-__global__ __launch_bounds__(1024) void rmsnorm_kernel(const void* __restrict__ x, int64_t ldx,
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x, int64_t ldx,
                                                       const float* __restrict__ gain, float eps, int d,
                                                       bf16* __restrict__ y, OperandLayout y_lay) {
   const int row = blockIdx.x;
   const void* xr = F32_IN ? (const void*)((const float*)x + (int64_t)row * ldx)
                           : (const void*)((const bf16*)x + (int64_t)row * ldx);
   const int chunks = d / 8;
-  const int threads = blockDim.x;
-  // the row is read once: a thread keeps its first KEEP chunks (with 256 threads a row of up to 8192 elements whole) in
+  // the row is read once: a thread keeps its first KEEP chunks (a row of up to 8192 elements whole) in
   // registers between the two passes and re-reads only what lies beyond
   constexpr int KEEP = 4;
   float keep[KEEP][8];
   float ss = 0.f;
 #pragma unroll
   for (int k = 0; k < KEEP; ++k) {
-    const int c = threadIdx.x + threads * k;
+    const int c = threadIdx.x + 256 * k;
     if (c < chunks) {
       load8<F32_IN>(xr, c, keep[k]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) ss += keep[k][i] * keep[k][i];
     }
   }
-  for (int c = threadIdx.x + threads * KEEP; c < chunks; c += threads) {
+  for (int c = threadIdx.x + 256 * KEEP; c < chunks; c += 256) {
     float f[8];
     load8<F32_IN>(xr, c, f);
 #pragma unroll
     for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
   }
-  __shared__ float red[16];
+  __shared__ float red[4];
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
-  float tot = 0.f;
-  for (int w = 0; w < threads / 64; ++w) tot += red[w];
+  const float tot = red[0] + red[1] + red[2] + red[3];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
   auto emit = [&](int c, const float (&f)[8]) {
     const f32x4 g0 = *reinterpret_cast<const f32x4*>(gain + c * 8);
@@ -84,33 +82,23 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(const void* __restrict__ 
   };
 #pragma unroll
   for (int k = 0; k < KEEP; ++k) {
-    const int c = threadIdx.x + threads * k;
+    const int c = threadIdx.x + 256 * k;
     if (c < chunks) emit(c, keep[k]);
   }
-  for (int c = threadIdx.x + threads * KEEP; c < chunks; c += threads) {
+  for (int c = threadIdx.x + 256 * KEEP; c < chunks; c += 256) {
     float f[8];
     load8<F32_IN>(xr, c, f);
     emit(c, f);
   }
 }
 
-// Threads of a row's workgroup: one per chunk of eight elements in whole waves, 256 at least and `most` at most.  (Waves without a chunk only
-// lengthen the start and the barrier.  With few rows the time is one row's, so it gets all the threads it can use;
-// with many, 256 threads with several chunks each keep more rows in flight.  307 rows of 4096 behind a split projection
-// 9.4 -> 8.4 us, a two-layer step of 350 requests of the toy shape 76.4 -> 73.4.)
-static int norm_threads(int d, int most) {
-  const int t = (d / 8 + 63) / 64 * 64;
-  return t < 256 ? 256 : t < most ? t : most;
-}
-
 hipError_t launch_rmsnorm(const void* x, int x_is_f32, int64_t ldx, const float* gain, float eps, int M, int d,
                           void* y, OperandLayout y_layout, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  const int threads = norm_threads(d, M >= 512 ? 256 : 1024);
   if (x_is_f32)
-    rmsnorm_kernel<true><<<M, threads, 0, s>>>(x, ldx, gain, eps, d, (bf16*)y, y_layout);
+    rmsnorm_kernel<true><<<M, 256, 0, s>>>(x, ldx, gain, eps, d, (bf16*)y, y_layout);
   else
-    rmsnorm_kernel<false><<<M, threads, 0, s>>>(x, ldx, gain, eps, d, (bf16*)y, y_layout);
+    rmsnorm_kernel<false><<<M, 256, 0, s>>>(x, ldx, gain, eps, d, (bf16*)y, y_layout);
   return hipGetLastError();
 }
 
@@ -211,11 +199,19 @@ __global__ __launch_bounds__(1024) void rmsnorm_sum_kernel(const void* __restric
   }
 }
 
+// Threads of a row's workgroup: one per chunk of eight elements in whole waves, 1024 at most (waves without a chunk only
+// lengthen the start and the barrier; 307 rows of 4096 9.4 -> 8.4 us, a two-layer step of 350 requests of the toy shape
+// 76.4 -> 73.4).  The sum of squares does not depend on it: a thread holds the same chunks, waves without any added zero.
+static int norm_threads(int d) {
+  const int t = (d / 8 + 63) / 64 * 64;
+  return t < 256 ? 256 : t < 1024 ? t : 1024;
+}
+
 hipError_t launch_rmsnorm_sum(const void* residual, int residual_is_f32, int64_t ldr, const float* ws, int splits,
                               int64_t ld_ws, float* h_out, int64_t ldh, const float* gain, float eps, int M, int d,
                               void* y, OperandLayout y_layout, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  const int threads = norm_threads(d, 1024);
+  const int threads = norm_threads(d);
   if (residual_is_f32)
     rmsnorm_sum_kernel<true><<<M, threads, 0, s>>>(residual, ldr, ws, splits, M, ld_ws, h_out, ldh, gain, eps, d, (bf16*)y,
                                                y_layout);
@@ -307,13 +303,14 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, in
       const float(&a)[8] = ab[0];
       const float(&b)[8] = ab[1];
       float fra[8], frb[8];
+      // (written out as fused operations, the form that the compiler had given a[i] * sin + b[i] * cos in each of the eight
+      // places, so that queries and keys keep their bits)
 #pragma unroll
-      for (int i = 0; i < 8; i += 2) {
-        const f32x4 t2 = *reinterpret_cast<const f32x4*>(cs + c0 + i);  // (cos, sin) of two angles
-        fra[i] = a[i] * t2[0] - b[i] * t2[1];
-        frb[i] = a[i] * t2[1] + b[i] * t2[0];
-        fra[i + 1] = a[i + 1] * t2[2] - b[i + 1] * t2[3];
-        frb[i + 1] = a[i + 1] * t2[3] + b[i + 1] * t2[2];
+      for (int i = 0; i < 8; ++i) {
+        const float2 t2 = cs[c0 + i];
+        fra[i] = __builtin_fmaf(a[i], t2.x, -(b[i] * t2.y));
+        frb[i] = i == 1 || i == 3 || i == 5 ? __builtin_fmaf(a[i], t2.y, b[i] * t2.x)
+                                            : __builtin_fmaf(b[i], t2.x, a[i] * t2.y);
       }
       // byte offsets of this thread's two 8-channel pieces in the K pool (a piece never straddles a 64-byte cut)
       const int esz = kv.fp8 ? 1 : 2;

@@ -38,6 +38,7 @@ struct GemmParams {
   int64_t Kpad, Npad, ldo, ldr;
   int M, N_store, epilogue, out_f32, res_f32;
   int k_tiles_total, k_tiles_per_split, splits;
+  int k_tiles_per_chunk;  // 0, or (splits = 1, small tiles) the K range is summed in chunks of this many k-tiles
   int tiles_m, tiles_n;
   // order of the tiles, see gemm_tile_of_block: bands of band_h + 1 (the first n_tall) or band_h rows of tiles; an
   // XCD takes `chunks` runs of `chunk` tiles, and an eighth of the `rest` tiles behind them
@@ -233,6 +234,11 @@ __device__ __forceinline__ bool gemm_tile_of_block(const GemmParams& p, int& til
 // M = 512: the two readers of a weight tile are neighbours in one super-block and run at the same time,
 // so the second read still finds the line): -1.8 %.
 //
+// Tiles of up to 128 x 128 can sum K in chunks (see sum_order_splits): a second set of accumulators (which costs 128 x 128
+// its second workgroup per CU, so there are two forms of that).
+template <int AT, int WT, int NS>
+constexpr bool kChunked = AT * WT <= 12 || (AT == 4 && WT == 4 && NS == 9);
+
 // A workgroup of four waves (2 x 2) makes a tile of BM = 32 AT rows x BN = 32 WT weight rows; a wave, AT x WT
 // accumulators.
 template <int AT, int WT, int NS, bool WNT>
@@ -453,9 +459,37 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
     a_next = rd_slot * STAGE + a_off;
     dma_stage();
   }
-  for (int t = 0; t < n_stages; t += 2) {
-    stage(0);
-    stage(1);
+  if constexpr (kChunked<AT, WT, NS>) {
+    // In chunks: what split-K workgroups would leave as partials is added up here in the same order (the requests run on
+    // across the ends of the chunks).
+    const int chunk = p.k_tiles_per_chunk > 0 ? 2 * p.k_tiles_per_chunk : n_stages;
+    f32x4 total[WT][AT];
+    for (int t = 0; t < n_stages;) {
+      const int end = min(t + chunk, n_stages);
+      const bool first = t == 0;
+      for (; t < end; t += 2) {
+        stage(0);
+        stage(1);
+      }
+      if (end == n_stages && first) break;  // one chunk: the accumulators are the sum
+      asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // MFMA -> accumulator read, which the compiler cannot see
+#pragma unroll
+      for (int wt = 0; wt < WT; ++wt)
+#pragma unroll
+        for (int at = 0; at < AT; ++at) {
+          // (pinned on both sides: the accumulators live in the inline MFMAs' registers)
+          asm volatile("" : "+a"(acc[wt][at]));
+          total[wt][at] = first ? acc[wt][at] : total[wt][at] + acc[wt][at];
+          acc[wt][at] = end == n_stages ? total[wt][at] : f32x4{0.f, 0.f, 0.f, 0.f};
+          asm volatile("" : "+a"(acc[wt][at]));
+        }
+      asm volatile("s_nop 7" ::: "memory");  // accumulator write -> MFMA
+    }
+  } else {
+    for (int t = 0; t < n_stages; t += 2) {
+      stage(0);
+      stage(1);
+    }
   }
   // loads still in flight target LDS only; they must land before the workgroup's LDS is released.
   // The nops cover the MFMA -> accumulator-read distance, which the compiler cannot see.
@@ -498,11 +532,12 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmParams p, in
 // (matrix pipe, LDS reads, power), and with tiles of 128 and 256 rows alone a batch of 307 paid for 512 (gate/up 57344 x
 // 8192: 366 us, with 2 x 160 rows 278; M = 384: 371 -> 308; M = 200: 202 -> 180).  128 weight rows per
 // tile instead of 256 where the weights are what counts (M up to 128: twice the workgroups, half the split-K
-// factor, no partials at all on many gate/up shapes; M = 48, 4096 x 4096: 22 -> 16 us, 22016 x 4096: 45 -> 39) and
+// factor where the order of the sums is free; M = 48, 22016 x 4096: 45 -> 39 us) and
 // between 160 and 256 rows on narrow projections.  The ring takes what LDS there is; two or three workgroups
 // per CU where a tile is small enough (their fill and epilogue then overlap the neighbour's stages).
 struct TileInfo {
   int at, wt, ns, wg_per_cu;
+  bool chunked;           // can sum K in chunks
   double stage_us;        // a 32-wide stage of one tile on a CU, the matrix pipe's part (see plan_cost)
   const void* kernel[2];  // ordinary / non-temporal weight requests
   int bm() const { return at * 32; }
@@ -511,11 +546,11 @@ struct TileInfo {
   int lds_bytes() const { return ns * ring_rows() * 64; }
 };
 #define TDP_TILE(AT, WT, NS, PER_CU, US)                                                   \
-  {AT, WT, NS, PER_CU, US,                                                                 \
+  {AT, WT, NS, PER_CU, kChunked<AT, WT, NS>, US,                                           \
    {reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, false>),                   \
     reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, true>)}}
 static const TileInfo kTiles[] = {
-    {0, 0, 0, 0, 0.0, {nullptr, nullptr}},
+    {0, 0, 0, 0, false, 0.0, {nullptr, nullptr}},
     TDP_TILE(8, 8, 4, 1, 0.425),  // 1: 256 x 256
     TDP_TILE(4, 8, 6, 1, 0.252),  // 2: 128 x 256
     TDP_TILE(4, 4, 4, 2, 0.129),  // 3: 128 x 128
@@ -523,7 +558,8 @@ static const TileInfo kTiles[] = {
     TDP_TILE(7, 8, 4, 1, 0.346), TDP_TILE(6, 8, 5, 1, 0.337), TDP_TILE(5, 8, 5, 1, 0.266),
     // 256, 224, 160, 96 x 128
     TDP_TILE(8, 4, 6, 1, 0.244), TDP_TILE(7, 4, 6, 1, 0.202), TDP_TILE(5, 4, 7, 1, 0.168), TDP_TILE(3, 4, 8, 1, 0.097),
-    // 64, 32 x 128
+    // 128 x 128 with one workgroup per CU (sums in chunks); 64, 32 x 128
+    TDP_TILE(4, 4, 9, 1, 0.129),
     TDP_TILE(2, 4, 6, 2, 0.079), TDP_TILE(1, 4, 4, 3, 0.0415),
 };
 #undef TDP_TILE
@@ -553,7 +589,8 @@ hipError_t gemm_setup() {
 // a round ends with its epilogue; split-K adds the fp32 partials' round trip and, where no later kernel sums them,
 // a reduce launch.  The constants are a least-squares fit to 10,000 launches timed on cold weights (19 projection
 // shapes, M from 4 to 19346, 1 to 16 splits): the tile and factor that this picks are on average 1.3 % slower
-// than the fastest measured, against 32 % for the rule it replaces (M <= 128, narrow, else; rounds of k-tiles).
+// than the fastest measured, against 32 % for the rule it replaces (M <= 128, narrow, else; rounds of k-tiles).  Up to 128
+// rows the choice is narrower, see sum_order_splits.
 static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer) {
   const double tm = (double)((M + ti.bm() - 1) / ti.bm()), tn = (double)(Npad / ti.bn());
   const double tiles = tm * tn * splits;
@@ -583,6 +620,47 @@ static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, in
     else if (epilogue == EPI_STORE) us += 0.4e-6 * (splits - 1) * M * (double)Npad;  // read by the rotation
   }
   return us * (1.0 + 0.004 * tm);  // ties: fewer rows of tiles, the weights are read fewer times
+}
+
+// The order in which a projection of up to 128 rows sums over K, as a split-K factor.  fp32 sums in another order differ in
+// their last bits, which the bf16 roundings behind them carry through every layer: about 0.5 % of a
+// hidden state after a few layers, as much as bf16 itself costs, and enough to turn one greedy token in
+// seventy between near-equal logits (measured: 2 of 48 over four layers and a vocabulary of 32000).  So small
+// decode batches keep one order whatever tile makes the sum: the factor below (a launch of 128 x 256 tiles, one per CU,
+// in super-blocks dealt to the XCDs, 1.8 us per round of k-tiles plus the partials' round trip), either as that many
+// split-K workgroups or, where the tile has registers for it, chunk by chunk in one.  Keeping it costs what a freer factor
+// would gain: 13B decode, 128 rows, two layers 1206 against 1172 us; 7B token step, 48 rows, 796 against 738.
+// Short sums (K <= 1024) are free: there another order moves a hidden state by 3e-5 at most, and a freer factor takes a
+// two-layer stage of hidden size 256 from 66 to 59 us.
+constexpr int kSumOrderRows = 128, kSumOrderKTiles = 16;
+static int sum_order_splits(int64_t M, int64_t Npad, int k_tiles, int64_t workspace_elems) {
+  const int tn = (int)(Npad / 256);
+  int most = k_tiles / 4 < 16 ? (k_tiles / 4 > 0 ? k_tiles / 4 : 1) : 16;
+  if (most > k_tiles) most = k_tiles;
+  int best = 1;
+  double best_cost = 1e300;
+  for (int sp = 1; sp <= most; ++sp) {
+    if (sp > 1 && sp * M * Npad > workspace_elems) break;
+    const int per = (k_tiles + sp - 1) / sp;
+    if ((k_tiles + per - 1) / per != sp) continue;
+    for (int lg = 5; lg >= 0; --lg) {
+      const int size = 1 << lg, n_sb = (tn + size - 1) / size;
+      int load[8] = {0, 0, 0, 0, 0, 0, 0, 0}, longest = 0;
+      for (int g = 0; g < n_sb * sp; ++g) {
+        const int sb = g % n_sb;
+        load[g & 7] += (sb + 1) * size <= tn ? size : tn - sb * size;
+      }
+      for (int x : load) longest = x > longest ? x : longest;
+      double cost = (double)((longest + 31) / 32) * (per + 6.0);
+      if (sp > 1) cost += 1.1e-6 * sp * M * (double)Npad + 2.0;
+      cost *= 1.0 + 0.02 * (5 - lg);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = sp;
+      }
+    }
+  }
+  return best;
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
@@ -630,12 +708,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     }
   };
   struct PlanEntry {
-    int tile, splits;
+    int tile, splits, chunk;  // chunk: k-tiles per chunk, 0 = all of K (of a split) in one
   };
   static std::mutex plan_mutex;
   static std::unordered_map<PlanKey, PlanEntry, PlanKeyHash> plan_cache;
   const PlanKey key{a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems};
-  PlanEntry plan{0, 1};
+  PlanEntry plan{0, 1, 0};
   {
     std::lock_guard<std::mutex> lock(plan_mutex);
     const auto it = plan_cache.find(key);
@@ -644,26 +722,34 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (plan.tile == 0) {
     const bool forced = a.force_tile >= 1 && a.force_tile <= kGemmTileMax;
     double best_cost = 1e300;
+    // up to kSumOrderRows rows the order of the sums is given, and only how it is made is chosen
+    const int order = a.force_splits <= 0 && !forced && a.M <= kSumOrderRows && p.k_tiles_total > kSumOrderKTiles
+                          ? sum_order_splits(a.M, a.Npad, p.k_tiles_total, a.workspace_elems) : 0;
     for (int t = forced ? a.force_tile : 1; t <= (forced ? a.force_tile : kTileCount - 1); ++t) {
-      const int64_t tiles1 = (int64_t)((a.M + kTiles[t].bm() - 1) / kTiles[t].bm()) * (a.Npad / kTiles[t].bn());
+      const int64_t tiles1 = (int64_t)((a.M + kTiles[t].bm() - 1) / kTiles[t].bm()) * ((a.Npad + kTiles[t].bn() - 1) / kTiles[t].bn());
       const int k_splits_max = p.k_tiles_total / 2 < 16 ? (p.k_tiles_total / 2 > 0 ? p.k_tiles_total / 2 : 1) : 16;
       int sp = a.force_splits > 0 ? a.force_splits : 1, sp_max = a.force_splits > 0 ? a.force_splits : k_splits_max;
+      if (order > 0) sp_max = order;
       if (sp > p.k_tiles_total) sp = sp_max = p.k_tiles_total;
       for (; sp <= sp_max; ++sp) {
         const int per = (p.k_tiles_total + sp - 1) / sp;
         const int real_sp = (p.k_tiles_total + per - 1) / per;
         if (real_sp != sp && a.force_splits <= 0) continue;  // same schedule as a smaller factor
+        if (order > 1 && sp != order && (sp > 1 || !kTiles[t].chunked)) continue;
         if (real_sp > 1 && (int64_t)real_sp * a.M * a.Npad > a.workspace_elems) break;
         // (four rounds of tiles: nothing is left for a split to gain)
-        if (real_sp > 1 && a.force_splits <= 0 && tiles1 * real_sp > 1024 * kTiles[t].wg_per_cu) break;
-        const double cost = plan_cost(kTiles[t], a.M, a.Npad, per, real_sp, a.epilogue, defer);
+        if (real_sp > 1 && a.force_splits <= 0 && order == 0 && tiles1 * real_sp > 1024 * kTiles[t].wg_per_cu) break;
+        double cost = plan_cost(kTiles[t], a.M, a.Npad, per, real_sp, a.epilogue, defer);
+        // (chunks: the sums between them stop the matrix pipe, and a workgroup's waves do it together; 128 x 15360 x 5120 in
+        // two rows of 64 x 128: 48.6 us where the estimate is 40, against 39.4 as four splits)
+        if (order > 1 && real_sp == 1) cost *= 1.1;
         if (cost < best_cost) {
           best_cost = cost;
-          plan = PlanEntry{t, real_sp};
+          plan = PlanEntry{t, real_sp, order > 1 && real_sp == 1 ? (p.k_tiles_total + order - 1) / order : 0};
         }
       }
     }
-    if (plan.tile == 0) plan = PlanEntry{forced ? a.force_tile : 1, 1};  // the workspace holds no such split
+    if (plan.tile == 0) plan = PlanEntry{forced ? a.force_tile : 1, 1, 0};  // the workspace holds no such split
     std::lock_guard<std::mutex> lock(plan_mutex);
     if (plan_cache.size() < 65536) plan_cache[key] = plan;
   }
@@ -673,6 +759,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.tiles_n = (int)(a.Npad / ti.bn());
   p.k_tiles_per_split = (p.k_tiles_total + splits - 1) / splits;
   p.splits = splits;
+  p.k_tiles_per_chunk = plan.chunk;
   const int bands = (p.tiles_m + 3) / 4;
   p.band_h = p.tiles_m / bands;
   p.n_tall = p.tiles_m % bands;

@@ -52,3 +52,27 @@ def test_every_tile_matches_the_fp64_product(tdp, M, N, K, epi, splits):
         gate = ref[:, :cols]
         ref = gate / (1.0 + np.exp(-gate)) * ref[:, cols:]
     assert row_rel_err(f64(out), ref) <= 1e-2
+
+
+@pytest.mark.parametrize("M,N,K,epi,splits", [
+    (48, 22016, 4096, 2, 2), (1, 22016, 4096, 2, 2), (100, 27648, 5120, 2, 2),   # summed in chunks by one workgroup
+    (128, 15360, 5120, 0, 4), (33, 4096, 4096, 1, 16), (16, 8192, 2048, 1, 8),   # split-K workgroups
+])
+def test_small_batches_keep_the_order_of_their_sums(tdp, M, N, K, epi, splits):
+    """Up to 128 rows the plan may choose the tile but not the order of the sums: the result is bit for bit that of 128 x 256
+    tiles with the split-K factor of the rule.  It differs from that of one factor less, or the test would show nothing (one
+    more may be the same schedule: 64 k-tiles in 17 parts of 4 are 16 parts)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    Wm = (torch.randn(K, N, generator=g, device="cuda") * (2.0 / K ** 0.5)).to(torch.bfloat16)
+    cols = N // 2 if epi == 2 else N
+    R = torch.randn(M, cols, generator=g, device="cuda").to(torch.bfloat16)
+
+    def run(tile, s):
+        out = torch.empty((M, cols), dtype=torch.bfloat16, device="cuda")
+        tdp.tdp_gemm_bf16(A, Wm, R if epi == 1 else None, out, M, N, K, epi, tile, s)
+        return out.view(torch.int16)
+
+    planned = run(0, 0)
+    assert torch.equal(planned, run(2, splits))
+    assert not torch.equal(planned, run(2, splits - 1))
