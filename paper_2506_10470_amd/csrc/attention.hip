@@ -529,9 +529,9 @@ hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_he
 // =====================================================================================
 // Prefill: var-len packed, causal.  One workgroup of NW waves per tile of NW * 32 query columns that share one K/V
 // head; a column is a (position, query head) pair, all G heads of the group at one position, then the next
-// position, so any group size fills the waves (256 columns: 32 positions of 8 heads, 51 of 5, 256 of 1; a few
+// position, so any group size fills the waves (128 columns: 16 positions of 8 heads, 25 of 5, 128 of 1; a few
 // columns are left over where G does not divide them).  (With a head per wave a group of five fell back to one head
-// per workgroup: five times the staging and 256 positions per tile; 267 us on 6713 tokens of 40 / 8 heads, 245 with pairs
+// per workgroup: five times the staging and a tile of one head; 267 us on 6713 tokens of 40 / 8 heads, 245 with pairs
 // and 207 with the order of the tiles below.)  Each 32-token
 // block of K and V^T is staged once per workgroup in LDS (double buffered, XOR-swizzled against
 // bank conflicts) and feeds the MFMAs of all columns, so K/V traffic per MFMA is 1/NW of a
