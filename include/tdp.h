@@ -22,8 +22,10 @@
  *    engine's business (Sec. 3.2.1).  The stage only writes the slot the tables name.
  *    Contents of device-side tables are trusted by the prefill / decode / import / export calls:
  *    a page id outside [0, num_pages) or a position beyond 16 * max_pages_per_seq is undefined
- *    behaviour there.  tdp_stage_check_decode / tdp_stage_check_prefill validate them first for a
- *    caller that wants that (they cost a synchronisation, so they are not part of the hot calls).
+ *    behaviour there (a decode step takes the nearest position of the row instead: that request's
+ *    result means nothing, the others' and those of later calls are not touched).
+ *    tdp_stage_check_decode / tdp_stage_check_prefill validate them first for a caller that wants
+ *    that (they cost a synchronisation, so they are not part of the hot calls).
  */
 #ifndef TDP_H_
 #define TDP_H_

@@ -52,6 +52,9 @@ constexpr float kNegBig = -1.0e30f;  // finite stand-in for -inf: exp2 gives exa
 // scans the counts a wave per class, then each of its four waves writes the items and pages of one request: one launch
 // instead of one workgroup that scanned 256 counts in turn and a second launch that copied the pages of its list
 // (16 / 200 / 512 requests: 9.6 / 11.2 / 11.9 us together, now 5.6 / 6.9 / 7.6).
+// A length that its block-table row cannot hold is brought into the row's range (decode_position, also in the rotation), so
+// that the list never outgrows its buffer and the grid: every span counted here is made, and spans_done ends at zero,
+// whatever ctx_lens holds.
 __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restrict__ ctx_lens, int batch, int span_len,
                                                         const int32_t* __restrict__ block_tables,
                                                         int max_pages_per_seq, int4* __restrict__ items, int max_items,
@@ -71,7 +74,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
 #pragma unroll
   for (int c = 0; c < NB; ++c) part[c][tid] = 0;
   for (int b = tid * per; b < min((tid + 1) * per, batch); ++b) {
-    const int n_total = ctx_lens[b] + 1;
+    const int n_total = decode_position(ctx_lens[b], max_pages_per_seq) + 1;
     const int n = (n_total + span_len - 1) / span_len;
     part[0][tid] += n - 1;
     part[last_class(n_total, n)][tid] += 1;
@@ -103,14 +106,14 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
   const int b = blockIdx.x * 4 + wave;  // this wave's request
   if (b >= batch) return;
   const int own = b / per;              // the thread that counted it
-  const int n_total = ctx_lens[b] + 1;
+  const int n_total = decode_position(ctx_lens[b], max_pages_per_seq) + 1;
   const int n = (n_total + span_len - 1) / span_len;
   const int cl = last_class(n_total, n);
   int full_at = part[0][own], last_at = part[cl][own];
 #pragma unroll
   for (int c = 1; c < NB; ++c) last_at += c == cl ? class_base[c] : 0;
   for (int b2 = own * per; b2 < b; ++b2) {  // requests of the same thread in front of this one
-    const int t2 = ctx_lens[b2] + 1, n2 = (t2 + span_len - 1) / span_len;
+    const int t2 = decode_position(ctx_lens[b2], max_pages_per_seq) + 1, n2 = (t2 + span_len - 1) / span_len;
     full_at += n2 - 1;
     last_at += last_class(t2, n2) == cl ? 1 : 0;
   }
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
     my_pages[j] = item_pages[(int64_t)item * item_pitch + min(lane + 64 * j, item_pitch - 1)];
   // without a work list (see attn_decode_planned) item b is the whole context of request b and its pages are the block table's
   // row, whose entries behind the request's last page are not page ids and are not used
-  const int4 it = items ? items[item] : make_int4(item, 0, ctx_lens[item] + 1, 0);
+  const int4 it = items ? items[item] : make_int4(item, 0, decode_position(ctx_lens[item], item_pitch) + 1, 0);
   if (it.x < 0) return;
   const int b = it.x, span = it.y;
   const int n_total = it.z;  // ctx + 1: the new token's K/V were appended before this kernel

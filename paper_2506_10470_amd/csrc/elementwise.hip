@@ -223,10 +223,10 @@ hipError_t launch_rmsnorm_sum(const void* residual, int residual_is_f32, int64_t
 
 // ------------------------------------------------------------------ token -> (sequence, position)
 __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, const int32_t* cu_seqlens,
-                                             int n_seqs, int& seq, int& pos) {
+                                             int n_seqs, int max_pages_per_seq, int& seq, int& pos) {
   if (ctx_lens) {  // decode: one token per request
     seq = t;
-    pos = ctx_lens[t];
+    pos = decode_position(ctx_lens[t], max_pages_per_seq);
   } else {         // prefill: largest s with cu_seqlens[s] <= t
     int lo = 0, hi = n_seqs - 1;
     while (lo < hi) {
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, in
     }
   };
   int seq, pos;
-  locate_token(t, ctx_lens, cu_seqlens, n_seqs, seq, pos);
+  locate_token(t, ctx_lens, cu_seqlens, n_seqs, max_pages_per_seq, seq, pos);
   const int dh = kv.head_dim, half = dh >> 1;
   const int page = block_tables[(int64_t)seq * max_pages_per_seq + pos / kv.page_size];
   const int slot = pos % kv.page_size;
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(int to_pages, bf16* __rest
                                                       int max_pages_per_seq) {
   const int t = blockIdx.x;
   int seq, pos;
-  locate_token(t, nullptr, cu_seqlens, n_seqs, seq, pos);
+  locate_token(t, nullptr, cu_seqlens, n_seqs, max_pages_per_seq, seq, pos);
   const int dh = kv.head_dim;
   const int page = block_tables[(int64_t)seq * max_pages_per_seq + pos / kv.page_size];
   const int slot = pos % kv.page_size;

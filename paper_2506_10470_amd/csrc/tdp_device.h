@@ -46,6 +46,13 @@ __device__ __forceinline__ bf16x8 zero_bf16x8() {
   return z;
 }
 
+// The position that a decode step gives a request's new token: ctx, brought into what a block-table row holds.  Every kernel of
+// the step takes it from here, so a length outside that range (an error of the caller) costs that request its result
+// and nothing else: no look-up past the row or the rotation table, no span more than the buffers and the grid are made for.
+__device__ __forceinline__ int decode_position(int ctx, int max_pages_per_seq) {
+  return min(max(ctx, 0), max_pages_per_seq * 16 - 1);
+}
+
 // Offset of element (r, k) in an operand laid out as
 // (r >> shift)*group + (k>>5)*kb + (r & (2^shift - 1))*par + (k&31).
 template <typename L>

@@ -1,0 +1,60 @@
+"""A decode step whose ctx_lens do not fit their block-table rows.  The kernels bring such a length into the row's range, so every
+access stays inside the tables, the work list and the grid, and the counters of finished spans end where they began:
+what the step leaves behind is one overwritten slot of the request's own pages, and later steps are not affected."""
+import numpy as np
+import pytest
+import torch
+
+from harness import workload as W
+from harness.runner import Stage, i32
+
+pytestmark = pytest.mark.gpu
+
+WIDTH, SPAN = 40, 256           # 640 tokens per row: three spans at most
+
+
+@pytest.mark.parametrize("shape", ["tiny_gqa", "tiny_h128"])
+@pytest.mark.parametrize("span", [SPAN, 1024])  # with a work list, and (one span per request) without one
+def test_lengths_outside_a_row_leave_later_steps_alone(shape, span):
+    from paper_2506_10470_amd import tdp
+    sh = W.SHAPES[shape].with_layers(2)
+    good = np.array([0, 300, 639, 17, 511])
+    bad = np.array([2 ** 31 - 1, 640, 100000, -5, -2 ** 31])
+    B = len(good)
+    tables = np.random.default_rng(3).permutation(B * WIDTH).reshape(B, WIDTH)
+    x = W.hidden_states(sh, B, 1, device="cuda")
+    full = i32(np.arange(B + 1) * WIDTH * 16)
+    total = B * WIDTH * 16
+
+    def fill(st):
+        for l in range(sh.n_layers):
+            k, v = (W.kv_packed(sh, l, w, total, 7, device="cuda") for w in "kv")
+            tdp.tdp_stage_kv_import(st.h, l, k, v, full, i32(tables), B, total)
+
+    def step(st, ctx):
+        out = torch.full_like(x, float("nan"))
+        tdp.tdp_stage_decode(st.h, x, i32(ctx.astype(np.int64).astype(np.int32)), i32(tables), B, out)
+        torch.cuda.synchronize()
+        return out.view(torch.int16)
+
+    with Stage(tdp, sh, B * WIDTH, B, 0, 0, WIDTH) as st:
+        tdp.tdp_stage_set_decode_span(st.h, span)
+        fill(st)
+        expected = step(st, good)
+    with Stage(tdp, sh, B * WIDTH, B, 0, 0, WIDTH) as st:
+        tdp.tdp_stage_set_decode_span(st.h, span)
+        fill(st)
+        before = [tuple(t.clone() for t in st.pools(l)) for l in range(sh.n_layers)]
+        step(st, bad)
+        for l in range(sh.n_layers):
+            k, v = st.pools(l)
+            changed_k = (k.view(torch.int16) != before[l][0].view(torch.int16)).any(dim=3).any(dim=1)  # [page][slot]
+            changed_v = (v.view(torch.int16) != before[l][1].view(torch.int16)).any(dim=2).any(dim=1)
+            allowed = torch.zeros_like(changed_k)
+            for b in range(B):
+                pos = min(max(int(bad[b]), 0), WIDTH * 16 - 1)
+                allowed[tables[b, pos // 16], pos % 16] = True
+            assert not (changed_k & ~allowed).any() and not (changed_v & ~allowed).any()
+        fill(st)
+        for _ in range(2):
+            assert torch.equal(step(st, good), expected)
