@@ -245,6 +245,17 @@ TDP_API int tdp_gemm_bf16(const void* A, const void* W, const void* residual, vo
                   int32_t K, int32_t epilogue, int32_t tile, int32_t splits, void* stream);
 
 /*
+ * Diagnostic, on the host alone: how the library makes a projection of this shape (epilogues as in
+ * tdp_gemm_bf16).  deferred = 1: as a stage makes its QKV (epilogue 0), O and down (1) projections,
+ * the fp32 partials of a split summed by the kernel behind it.  workspace_elems: floats that the partials
+ * may take (tdp_gemm_bf16: 16 * M * N with N rounded up to 256, or to 2 * 128 columns of F).  plan (host int32 [5]):
+ * tile number, output rows and weight rows of a tile, split-K factor, and the k of one chunk where a
+ * workgroup sums its K range in chunks (0: in one go).
+ */
+TDP_API int tdp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t deferred, int64_t workspace_elems,
+                          int32_t* plan);
+
+/*
  * tdp_gemm_bf16 (epilogues 0 and 1) for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): same kernels, same results, but
  * the repacked weights and the split-K partials live in a device array that is part of the library

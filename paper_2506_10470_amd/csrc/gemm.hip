@@ -564,6 +564,9 @@ static const TileInfo kTiles[] = {
 };
 #undef TDP_TILE
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
+// The 128 x 128 tile that has room for chunked sums is used for those only: otherwise two workgroups per CU (tile 3) are 7 to 15 %
+// faster at the same split-K factor (1367 pairs of launches, M from 1 to 16384).
+constexpr int kChunksOnlyTile = 11;
 
 static bool g_print_plan = false;  // tuning aid, read from the environment once (gemm_setup)
 
@@ -591,7 +594,14 @@ hipError_t gemm_setup() {
 // shapes, M from 4 to 19346, 1 to 16 splits): the tile and factor that this picks are on average 1.3 % slower
 // than the fastest measured, against 32 % for the rule it replaces (M <= 128, narrow, else; rounds of k-tiles).  Up to 128
 // rows the choice is narrower, see sum_order_splits.
-static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer) {
+// `rotated`: the QKV projection of a stage where its sums are free.  It stores fp32 whether it is split or not, so each
+// store costs alike (0.6 us per million elements), and each split more costs the rotation 0.5 us and 0.33 per million
+// elements (128 to 512 rows, seven shapes).  Charged for the store of a split alone, like the other projections, 13B at 512 rows took
+// 256 x 128 tiles unsplit where 256 x 256 in two splits are faster (with the rotation 79.2 + 51.2 us against 70.5 + 51.9); Qwen at
+// 512 rows 56.0 + 16.9 against 45.3 + 17.8, 70B at 384 rows 87.1 + 15.8 against 67.5 + 18.4.  Over 264 cases with M from 129 to
+// 16384 the choice was 2.5 % slower than the fastest, now 0.2 %.
+static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer,
+                        bool rotated) {
   const double tm = (double)((M + ti.bm() - 1) / ti.bm()), tn = (double)(Npad / ti.bn());
   const double tiles = tm * tn * splits;
   const int64_t per_xcd = ((int64_t)tiles + 7) / 8, slots = 32 * ti.wg_per_cu;
@@ -614,10 +624,13 @@ static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, in
   };
   auto epi = [&](int64_t n) { return 0.94 + 0.12 * mfma * (double)((n + 31) / 32); };
   double us = 1.9 + full * (2 * per * stage(slots) + epi(slots)) + 2 * per * stage(last) + epi(last);
-  if (splits > 1) {
-    us += 0.81e-6 * splits * M * (double)Npad + 0.15 * splits;
+  const double elems = M * (double)Npad;
+  if (rotated) {
+    us += 0.6e-6 * splits * elems + (splits - 1) * (0.5 + 0.33e-6 * elems);
+  } else if (splits > 1) {
+    us += 0.81e-6 * splits * elems + 0.15 * splits;
     if (!defer) us += 5.4;
-    else if (epilogue == EPI_STORE) us += 0.4e-6 * (splits - 1) * M * (double)Npad;  // read by the rotation
+    else if (epilogue == EPI_STORE) us += 0.4e-6 * (splits - 1) * elems;  // read by the rotation
   }
   return us * (1.0 + 0.004 * tm);  // ties: fewer rows of tiles, the weights are read fewer times
 }
@@ -663,6 +676,75 @@ static int sum_order_splits(int64_t M, int64_t Npad, int k_tiles, int64_t worksp
   return best;
 }
 
+static GemmPlan search_plan(const GemmPlanKey& a) {
+  GemmPlan plan{0, 1, 0};
+  const int k_tiles_total = (int)(a.Kpad / 64);
+  const bool forced = a.force_tile >= 1 && a.force_tile <= kGemmTileMax;
+  double best_cost = 1e300;
+  // up to kSumOrderRows rows the order of the sums is given, and only how it is made is chosen
+  const int order = a.force_splits <= 0 && !forced && a.M <= kSumOrderRows && k_tiles_total > kSumOrderKTiles
+                        ? sum_order_splits(a.M, a.Npad, k_tiles_total, a.workspace_elems) : 0;
+  const bool rotated = a.defer && a.epilogue == EPI_STORE && order == 0;
+  for (int t = forced ? a.force_tile : 1; t <= (forced ? a.force_tile : kTileCount - 1); ++t) {
+    const int64_t tiles1 = (int64_t)((a.M + kTiles[t].bm() - 1) / kTiles[t].bm()) * ((a.Npad + kTiles[t].bn() - 1) / kTiles[t].bn());
+    const int k_splits_max = k_tiles_total / 2 < 16 ? (k_tiles_total / 2 > 0 ? k_tiles_total / 2 : 1) : 16;
+    int sp = a.force_splits > 0 ? a.force_splits : 1, sp_max = a.force_splits > 0 ? a.force_splits : k_splits_max;
+    if (order > 0) sp_max = order;
+    if (sp > k_tiles_total) sp = sp_max = k_tiles_total;
+    for (; sp <= sp_max; ++sp) {
+      const int per = (k_tiles_total + sp - 1) / sp;
+      const int real_sp = (k_tiles_total + per - 1) / per;
+      const bool chunks = order > 1 && real_sp == 1;
+      if (real_sp != sp && a.force_splits <= 0) continue;  // same schedule as a smaller factor
+      if (order > 1 && sp != order && (sp > 1 || !kTiles[t].chunked)) continue;
+      if (t == kChunksOnlyTile && !chunks && !forced) continue;
+      if (real_sp > 1 && (int64_t)real_sp * a.M * a.Npad > a.workspace_elems) break;
+      // (four rounds of tiles: nothing is left for a split to gain)
+      if (real_sp > 1 && a.force_splits <= 0 && order == 0 && tiles1 * real_sp > 1024 * kTiles[t].wg_per_cu) break;
+      double cost = plan_cost(kTiles[t], a.M, a.Npad, per, real_sp, a.epilogue, a.defer, rotated);
+      // (chunks: the sums between them stop the matrix pipe, and a workgroup's waves do it together; 128 x 15360 x 5120 in
+      // two rows of 64 x 128: 48.6 us where the estimate is 40, against 39.4 as four splits)
+      if (chunks) cost *= 1.1;
+      if (cost < best_cost) {
+        best_cost = cost;
+        plan = GemmPlan{t, real_sp, chunks ? (k_tiles_total + order - 1) / order : 0};
+      }
+    }
+  }
+  if (plan.tile == 0) plan = GemmPlan{forced ? a.force_tile : 1, 1, 0};  // the workspace holds no such split
+  return plan;
+}
+
+// The search costs tens of microseconds on the host and its answer depends only on the problem's shape, so it
+// is remembered (a serving loop asks for the same few shapes every step).
+GemmPlan gemm_plan(const GemmPlanKey& key) {
+  struct Hash {
+    size_t operator()(const GemmPlanKey& k) const {
+      uint64_t h = 0x9e3779b97f4a7c15ull;
+      for (uint64_t v : {(uint64_t)k.M, (uint64_t)k.force_tile, (uint64_t)k.force_splits, (uint64_t)(k.epilogue * 2 + k.defer),
+                         (uint64_t)k.Npad, (uint64_t)k.Kpad, (uint64_t)k.workspace_elems})
+        h = (h ^ v) * 0xff51afd7ed558ccdull + (h >> 29);
+      return (size_t)h;
+    }
+  };
+  static std::mutex mutex;
+  static std::unordered_map<GemmPlanKey, GemmPlan, Hash> cache;
+  {
+    std::lock_guard<std::mutex> lock(mutex);
+    const auto it = cache.find(key);
+    if (it != cache.end()) return it->second;
+  }
+  const GemmPlan plan = search_plan(key);
+  std::lock_guard<std::mutex> lock(mutex);
+  if (cache.size() < 65536) cache[key] = plan;
+  return plan;
+}
+
+void gemm_tile_size(int tile, int* rows, int* weight_rows) {
+  *rows = kTiles[tile].bm();
+  *weight_rows = kTiles[tile].bn();
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   GemmParams p;
@@ -685,74 +767,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.N_store = a.N_store;
   p.epilogue = a.epilogue;
   p.k_tiles_total = (int)(a.Kpad / 64);
-  // ---- plan: tile and split-K factor ------------------------------------------------------------
-  // The search below costs tens of microseconds on the host and its answer depends only on the
-  // problem's shape, so it is remembered (a serving loop asks for the same few shapes every step).
   const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
-  struct PlanKey {
-    int M, force_tile, force_splits, epilogue;
-    bool defer;
-    int64_t Npad, Kpad, ws_elems;
-    bool operator==(const PlanKey& o) const {
-      return M == o.M && force_tile == o.force_tile && force_splits == o.force_splits && epilogue == o.epilogue &&
-             defer == o.defer && Npad == o.Npad && Kpad == o.Kpad && ws_elems == o.ws_elems;
-    }
-  };
-  struct PlanKeyHash {
-    size_t operator()(const PlanKey& k) const {
-      uint64_t h = 0x9e3779b97f4a7c15ull;
-      for (uint64_t v : {(uint64_t)k.M, (uint64_t)k.force_tile, (uint64_t)k.force_splits, (uint64_t)(k.epilogue * 2 + k.defer),
-                         (uint64_t)k.Npad, (uint64_t)k.Kpad, (uint64_t)k.ws_elems})
-        h = (h ^ v) * 0xff51afd7ed558ccdull + (h >> 29);
-      return (size_t)h;
-    }
-  };
-  struct PlanEntry {
-    int tile, splits, chunk;  // chunk: k-tiles per chunk, 0 = all of K (of a split) in one
-  };
-  static std::mutex plan_mutex;
-  static std::unordered_map<PlanKey, PlanEntry, PlanKeyHash> plan_cache;
-  const PlanKey key{a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems};
-  PlanEntry plan{0, 1, 0};
-  {
-    std::lock_guard<std::mutex> lock(plan_mutex);
-    const auto it = plan_cache.find(key);
-    if (it != plan_cache.end()) plan = it->second;
-  }
-  if (plan.tile == 0) {
-    const bool forced = a.force_tile >= 1 && a.force_tile <= kGemmTileMax;
-    double best_cost = 1e300;
-    // up to kSumOrderRows rows the order of the sums is given, and only how it is made is chosen
-    const int order = a.force_splits <= 0 && !forced && a.M <= kSumOrderRows && p.k_tiles_total > kSumOrderKTiles
-                          ? sum_order_splits(a.M, a.Npad, p.k_tiles_total, a.workspace_elems) : 0;
-    for (int t = forced ? a.force_tile : 1; t <= (forced ? a.force_tile : kTileCount - 1); ++t) {
-      const int64_t tiles1 = (int64_t)((a.M + kTiles[t].bm() - 1) / kTiles[t].bm()) * ((a.Npad + kTiles[t].bn() - 1) / kTiles[t].bn());
-      const int k_splits_max = p.k_tiles_total / 2 < 16 ? (p.k_tiles_total / 2 > 0 ? p.k_tiles_total / 2 : 1) : 16;
-      int sp = a.force_splits > 0 ? a.force_splits : 1, sp_max = a.force_splits > 0 ? a.force_splits : k_splits_max;
-      if (order > 0) sp_max = order;
-      if (sp > p.k_tiles_total) sp = sp_max = p.k_tiles_total;
-      for (; sp <= sp_max; ++sp) {
-        const int per = (p.k_tiles_total + sp - 1) / sp;
-        const int real_sp = (p.k_tiles_total + per - 1) / per;
-        if (real_sp != sp && a.force_splits <= 0) continue;  // same schedule as a smaller factor
-        if (order > 1 && sp != order && (sp > 1 || !kTiles[t].chunked)) continue;
-        if (real_sp > 1 && (int64_t)real_sp * a.M * a.Npad > a.workspace_elems) break;
-        // (four rounds of tiles: nothing is left for a split to gain)
-        if (real_sp > 1 && a.force_splits <= 0 && order == 0 && tiles1 * real_sp > 1024 * kTiles[t].wg_per_cu) break;
-        double cost = plan_cost(kTiles[t], a.M, a.Npad, per, real_sp, a.epilogue, defer);
-        // (chunks: the sums between them stop the matrix pipe, and a workgroup's waves do it together; 128 x 15360 x 5120 in
-        // two rows of 64 x 128: 48.6 us where the estimate is 40, against 39.4 as four splits)
-        if (order > 1 && real_sp == 1) cost *= 1.1;
-        if (cost < best_cost) {
-          best_cost = cost;
-          plan = PlanEntry{t, real_sp, order > 1 && real_sp == 1 ? (p.k_tiles_total + order - 1) / order : 0};
-        }
-      }
-    }
-    if (plan.tile == 0) plan = PlanEntry{forced ? a.force_tile : 1, 1, 0};  // the workspace holds no such split
-    std::lock_guard<std::mutex> lock(plan_mutex);
-    if (plan_cache.size() < 65536) plan_cache[key] = plan;
-  }
+  const GemmPlan plan = gemm_plan({a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems});
   const TileInfo& ti = kTiles[plan.tile];
   const int splits = plan.splits;
   p.tiles_m = (a.M + ti.bm() - 1) / ti.bm();

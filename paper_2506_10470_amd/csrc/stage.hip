@@ -600,6 +600,23 @@ int tdp_stage_check_prefill(tdp_stage* st, const int32_t* cu_seqlens, const int3
   return check_tables(st, 0, cu_seqlens, block_tables, n_seqs, total_tokens, (hipStream_t)stream);
 }
 
+int tdp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t deferred, int64_t workspace_elems,
+                  int32_t* plan) {
+  if (M < 1 || N < 4 || K < 64 || K % 64 || N % 4) return fail(TDP_EINVAL, "bad GEMM shape");
+  if (epilogue < 0 || epilogue > 2) return fail(TDP_EINVAL, "epilogue must be 0, 1 or 2");
+  if (epilogue == 2 && (N % 8 || deferred)) return fail(TDP_EINVAL, "the gated epilogue needs N = 2 F with F a multiple of 4, and sums at once");
+  if (workspace_elems < 0) return fail(TDP_EINVAL, "negative workspace");
+  if (!plan) return fail(TDP_EINVAL, "null pointer");
+  const int64_t Npad = epilogue == 2 ? 2 * round_up(N / 2, 128) : round_up(N, 256);
+  const GemmPlan p = gemm_plan({M, 0, 0, epilogue == 2 ? EPI_SWIGLU : epilogue ? EPI_RESIDUAL : EPI_STORE, deferred != 0, Npad, K,
+                                workspace_elems});
+  plan[0] = p.tile;
+  gemm_tile_size(p.tile, plan + 1, plan + 2);
+  plan[3] = p.splits;
+  plan[4] = p.chunk * 64;
+  return TDP_OK;
+}
+
 int tdp_gemm_bf16(const void* A, const void* W, const void* residual, void* out, int32_t M, int32_t N, int32_t K,
                   int32_t epilogue, int32_t tile, int32_t splits, void* stream) {
   if (M < 0 || N <= 0 || K <= 0) return fail(TDP_EINVAL, "bad GEMM shape");

@@ -67,6 +67,22 @@ struct GemmArgs {
   int* splits_used;       // null = reduce here
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+
+// How a GEMM is made: a pure function of its shape and of what the caller fixes (host only).
+struct GemmPlanKey {
+  int M, force_tile, force_splits, epilogue;
+  bool defer;  // the partials of a split are left to the consumer (GemmArgs::splits_used)
+  int64_t Npad, Kpad, workspace_elems;
+  bool operator==(const GemmPlanKey& o) const {
+    return M == o.M && force_tile == o.force_tile && force_splits == o.force_splits && epilogue == o.epilogue &&
+           defer == o.defer && Npad == o.Npad && Kpad == o.Kpad && workspace_elems == o.workspace_elems;
+  }
+};
+struct GemmPlan {
+  int tile, splits, chunk;  // chunk: k-tiles of 64 per chunk, 0 = all of K (of a split) in one sum
+};
+GemmPlan gemm_plan(const GemmPlanKey& key);
+void gemm_tile_size(int tile, int* rows, int* weight_rows);
 hipError_t gemm_setup();  // one-time function attributes (dynamic LDS size)
 
 // ---- weight repack: dst[row_of(n)][k] = src[k][n] -------------------------------------------

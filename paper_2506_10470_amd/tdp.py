@@ -71,6 +71,7 @@ _SIGS = {
     "tdp_stage_check_prefill": (C.c_int, [_vp, _vp, _vp, _i32, _i32, _vp]),
     "tdp_stage_set_layer_range": (C.c_int, [_vp, _i32, _i32]),
     "tdp_stage_set_decode_span": (C.c_int, [_vp, _i32]),
+    "tdp_gemm_plan": (C.c_int, [_i32, _i32, _i32, _i32, _i32, _i64, C.POINTER(_i32)]),
     "tdp_gemm_bf16": (C.c_int, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "tdp_gemm_bf16_static": (C.c_int, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "tdp_e4m3_from_f32": (C.c_int, [_vp, _vp, _i64, C.c_float, _vp]),
@@ -180,6 +181,16 @@ def tdp_stage_set_layer_range(st, first: int, count: int) -> None:
 
 def tdp_stage_set_decode_span(st, span_tokens: int) -> None:
     _check(lib.tdp_stage_set_decode_span(st, span_tokens))
+
+
+def tdp_gemm_plan(M, N, K, epilogue=0, deferred=False, workspace_elems=None) -> dict:
+    """How a projection is made; the workspace of tdp_gemm_bf16 unless given."""
+    if workspace_elems is None:
+        n_pad = 2 * (-(-(N // 2) // 128) * 128) if epilogue == 2 else -(-N // 256) * 256
+        workspace_elems = 16 * M * n_pad
+    p = (_i32 * 5)()
+    _check(lib.tdp_gemm_plan(M, N, K, epilogue, int(bool(deferred)), workspace_elems, p))
+    return dict(zip(("tile", "rows", "weight_rows", "splits", "chunk_k"), p))
 
 
 def tdp_gemm_bf16(A, W, residual, out, M, N, K, epilogue=0, tile=0, splits=0, stream=None) -> None:
