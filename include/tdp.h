@@ -256,6 +256,17 @@ TDP_API int tdp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int
                           int32_t* plan);
 
 /*
+ * Diagnostic: tdp_gemm_bf16 made in exactly one way, so that every kernel variant can be tested whatever
+ * the plan would take: tile = a tile number of tdp_gemm_plan (from 1), splits = the split-K factor (one
+ * that leaves no split empty), chunk_k = 0 or a multiple of 64: a workgroup sums its K range in chunks of
+ * that many (splits = 1, tiles of at most 96 x 128 and the 128 x 128 one made for it).  TDP_EINVAL if
+ * there is no such form.
+ */
+TDP_API int tdp_gemm_bf16_form(const void* A, const void* W, const void* residual, void* out, int32_t M, int32_t N,
+                               int32_t K, int32_t epilogue, int32_t tile, int32_t splits, int32_t chunk_k,
+                               void* stream);
+
+/*
  * tdp_gemm_bf16 (epilogues 0 and 1) for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): same kernels, same results, but
  * the repacked weights and the split-K partials live in a device array that is part of the library

@@ -740,6 +740,15 @@ GemmPlan gemm_plan(const GemmPlanKey& key) {
   return plan;
 }
 
+bool gemm_form_fits(const GemmPlan& f, int M, int64_t Npad, int64_t Kpad, int64_t workspace_elems) {
+  const int k_tiles = (int)(Kpad / 64);
+  if (f.tile < 1 || f.tile >= kTileCount || f.splits < 1 || f.splits > k_tiles || f.chunk < 0) return false;
+  const int per = (k_tiles + f.splits - 1) / f.splits;
+  if ((k_tiles + per - 1) / per != f.splits) return false;  // the last splits would have nothing to sum
+  if (f.chunk > 0 && (f.splits > 1 || !kTiles[f.tile].chunked)) return false;
+  return f.splits == 1 || f.splits * (int64_t)M * Npad <= workspace_elems;
+}
+
 void gemm_tile_size(int tile, int* rows, int* weight_rows) {
   *rows = kTiles[tile].bm();
   *weight_rows = kTiles[tile].bn();
@@ -768,7 +777,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.epilogue = a.epilogue;
   p.k_tiles_total = (int)(a.Kpad / 64);
   const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
-  const GemmPlan plan = gemm_plan({a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems});
+  const GemmPlan plan = a.form.tile ? a.form : gemm_plan({a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems});
   const TileInfo& ti = kTiles[plan.tile];
   const int splits = plan.splits;
   p.tiles_m = (a.M + ti.bm() - 1) / ti.bm();

@@ -617,24 +617,19 @@ int tdp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t def
   return TDP_OK;
 }
 
-int tdp_gemm_bf16(const void* A, const void* W, const void* residual, void* out, int32_t M, int32_t N, int32_t K,
-                  int32_t epilogue, int32_t tile, int32_t splits, void* stream) {
-  if (M < 0 || N <= 0 || K <= 0) return fail(TDP_EINVAL, "bad GEMM shape");
-  if (K % 64 || N % 4) return fail(TDP_EINVAL, "K must be a multiple of 64 and N of 4");
-  if (epilogue < 0 || epilogue > 2) return fail(TDP_EINVAL, "epilogue must be 0, 1 or 2");
-  if (epilogue == 2 && N % 8) return fail(TDP_EINVAL, "the gated epilogue needs N = 2 F with F a multiple of 4");
-  if (tile < 0 || tile > kGemmTileMax || splits < 0) return fail(TDP_EINVAL, "bad tile / splits");
-  if (M == 0) return TDP_OK;
+// one projection from a row-major weight matrix; form.tile = 0: planned, with tile and splits as far as they are given
+static int gemm_bf16(const char* what, const void* A, const void* W, const void* residual, void* out, int M, int N, int K,
+                     int epilogue, int tile, int splits, GemmPlan form, hipStream_t s) {
   if (!A || !W || !out || (epilogue == 1 && !residual)) return fail(TDP_EINVAL, "null pointer");
-  hipStream_t s = (hipStream_t)stream;
-  HIP_TRY(gemm_setup());
   // gated: the weights are stored as the stage stores gate/up (blocks of 32 gate rows, 32 up rows; F rounded up
   // to 128), the result has F = N / 2 columns
   const int64_t F = N / 2;
   const int64_t Npad = epilogue == 2 ? 2 * round_up(F, 128) : round_up(N, 256);
   uint16_t* wt = nullptr;
   float* ws = nullptr;
-  const int64_t ws_elems = (int64_t)(splits > 0 ? splits : 16) * M * Npad;
+  const int64_t ws_elems = (int64_t)(form.tile ? form.splits : splits > 0 ? splits : 16) * M * Npad;
+  if (form.tile && !gemm_form_fits(form, M, Npad, K, ws_elems)) return fail(TDP_EINVAL, "no such form of this GEMM");
+  HIP_TRY(gemm_setup());
   HIP_TRY(hipMalloc((void**)&wt, (size_t)(Npad * K) * 2));
   hipError_t e = hipMalloc((void**)&ws, (size_t)ws_elems * 4);
   if (e == hipSuccess) e = hipMemsetAsync(wt, 0, (size_t)(Npad * K) * 2, s);
@@ -655,14 +650,36 @@ int tdp_gemm_bf16(const void* A, const void* W, const void* residual, void* out,
     g.N_store = epilogue == 2 ? (int)F : N;
     g.out = out; g.ldo = g.N_store; g.u_layout = layout_row_major(F); g.residual = residual; g.ldr = N;
     g.epilogue = epilogue == 2 ? EPI_SWIGLU : epilogue ? EPI_RESIDUAL : EPI_STORE;
-    g.workspace = ws; g.workspace_elems = ws_elems; g.force_tile = tile; g.force_splits = splits;
+    g.workspace = ws; g.workspace_elems = ws_elems; g.force_tile = tile; g.force_splits = splits; g.form = form;
     e = launch_gemm(g, s);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (wt) (void)hipFree(wt);
   if (ws) (void)hipFree(ws);
-  if (e != hipSuccess) return fail_hip(e, "tdp_gemm_bf16");
+  if (e != hipSuccess) return fail_hip(e, what);
   return TDP_OK;
+}
+
+int tdp_gemm_bf16(const void* A, const void* W, const void* residual, void* out, int32_t M, int32_t N, int32_t K,
+                  int32_t epilogue, int32_t tile, int32_t splits, void* stream) {
+  if (M < 0 || N <= 0 || K <= 0) return fail(TDP_EINVAL, "bad GEMM shape");
+  if (K % 64 || N % 4) return fail(TDP_EINVAL, "K must be a multiple of 64 and N of 4");
+  if (epilogue < 0 || epilogue > 2) return fail(TDP_EINVAL, "epilogue must be 0, 1 or 2");
+  if (epilogue == 2 && N % 8) return fail(TDP_EINVAL, "the gated epilogue needs N = 2 F with F a multiple of 4");
+  if (tile < 0 || tile > kGemmTileMax || splits < 0) return fail(TDP_EINVAL, "bad tile / splits");
+  if (M == 0) return TDP_OK;
+  return gemm_bf16("tdp_gemm_bf16", A, W, residual, out, M, N, K, epilogue, tile, splits, GemmPlan{0, 0, 0}, (hipStream_t)stream);
+}
+
+int tdp_gemm_bf16_form(const void* A, const void* W, const void* residual, void* out, int32_t M, int32_t N, int32_t K,
+                       int32_t epilogue, int32_t tile, int32_t splits, int32_t chunk_k, void* stream) {
+  if (M < 1 || N <= 0 || K <= 0) return fail(TDP_EINVAL, "bad GEMM shape");
+  if (K % 64 || N % 4) return fail(TDP_EINVAL, "K must be a multiple of 64 and N of 4");
+  if (epilogue < 0 || epilogue > 2) return fail(TDP_EINVAL, "epilogue must be 0, 1 or 2");
+  if (epilogue == 2 && N % 8) return fail(TDP_EINVAL, "the gated epilogue needs N = 2 F with F a multiple of 4");
+  if (tile < 1 || splits < 1 || chunk_k < 0 || chunk_k % 64) return fail(TDP_EINVAL, "bad form");
+  return gemm_bf16("tdp_gemm_bf16_form", A, W, residual, out, M, N, K, epilogue, 0, 0, GemmPlan{tile, splits, chunk_k / 64},
+                   (hipStream_t)stream);
 }
 
 int tdp_e4m3_from_f32(const float* src, uint8_t* codes, int64_t n, float scale, void* stream) {

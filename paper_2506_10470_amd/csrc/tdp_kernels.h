@@ -38,7 +38,10 @@ enum Epilogue : int {
                      //                                   in blocks of 32: gate block, up block)
 };
 
-constexpr int kGemmTileMax = 3;  // kernel variants: 1 = 256 x 256 tile, 2 = 128 x 256, 3 = 128 x 128
+constexpr int kGemmTileMax = 3;  // kernel variants that force_tile selects: 1 = 256 x 256 tile, 2 = 128 x 256, 3 = 128 x 128
+struct GemmPlan {
+  int tile, splits, chunk;  // chunk: k-tiles of 64 per chunk, 0 = all of K (of a split) in one sum
+};
 struct GemmArgs {
   const void* A;      // bf16, M rows x Kpad columns in a_layout; rows >= M are never read
   OperandLayout a_layout;
@@ -60,6 +63,7 @@ struct GemmArgs {
   int64_t workspace_elems;
   int force_tile;         // 0 = choose; else 1..kGemmTileMax selects a kernel variant (tests / tuning)
   int force_splits;       // 0 = choose
+  GemmPlan form;          // tile 0 = planned; else made exactly like this (gemm_form_fits)
   // Deferred reduction (plain and residual epilogues only): when the plan splits K, leave the fp32
   // partials in the workspace, ws[(z * M + m) * Npad + n] for split z, apply nothing and launch no
   // reduce kernel; *splits_used (host) receives the number of splits, 1 meaning `out` was written as
@@ -78,10 +82,8 @@ struct GemmPlanKey {
            defer == o.defer && Npad == o.Npad && Kpad == o.Kpad && workspace_elems == o.workspace_elems;
   }
 };
-struct GemmPlan {
-  int tile, splits, chunk;  // chunk: k-tiles of 64 per chunk, 0 = all of K (of a split) in one sum
-};
 GemmPlan gemm_plan(const GemmPlanKey& key);
+bool gemm_form_fits(const GemmPlan& form, int M, int64_t Npad, int64_t Kpad, int64_t workspace_elems);
 void gemm_tile_size(int tile, int* rows, int* weight_rows);
 hipError_t gemm_setup();  // one-time function attributes (dynamic LDS size)
 

@@ -73,6 +73,7 @@ _SIGS = {
     "tdp_stage_set_decode_span": (C.c_int, [_vp, _i32]),
     "tdp_gemm_plan": (C.c_int, [_i32, _i32, _i32, _i32, _i32, _i64, C.POINTER(_i32)]),
     "tdp_gemm_bf16": (C.c_int, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
+    "tdp_gemm_bf16_form": (C.c_int, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "tdp_gemm_bf16_static": (C.c_int, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]),
     "tdp_e4m3_from_f32": (C.c_int, [_vp, _vp, _i64, C.c_float, _vp]),
     "tdp_e4m3_to_f32": (C.c_int, [_vp, _vp, _i64, _vp]),
@@ -196,6 +197,11 @@ def tdp_gemm_plan(M, N, K, epilogue=0, deferred=False, workspace_elems=None) -> 
 def tdp_gemm_bf16(A, W, residual, out, M, N, K, epilogue=0, tile=0, splits=0, stream=None) -> None:
     _check(lib.tdp_gemm_bf16(_ptr(A), _ptr(W), _ptr(residual), _ptr(out), M, N, K, epilogue, tile, splits,
                              _stream(stream)))
+
+
+def tdp_gemm_bf16_form(A, W, residual, out, M, N, K, epilogue, tile, splits=1, chunk_k=0, stream=None) -> None:
+    _check(lib.tdp_gemm_bf16_form(_ptr(A), _ptr(W), _ptr(residual), _ptr(out), M, N, K, epilogue, tile, splits, chunk_k,
+                                  _stream(stream)))
 
 
 def tdp_gemm_bf16_static(A, W, residual, out, M, N, K, epilogue=0, tile=0, splits=0, stream=None) -> None:
