@@ -389,30 +389,37 @@ __device__ __forceinline__ bool locate_page(int w, const int32_t* cu_seqlens, in
   return true;
 }
 
-// A page's 16 tokens x up to 512 channels, turned round in LDS between token rows and the transposed V page.
+// A page's 16 tokens x up to CH channels, turned round in LDS between token rows and the transposed V page.
 constexpr int kPageChannels = 512;
-using PageTile = bf16[16][kPageChannels + 8];  // [token][channel]; rows 4 banks apart
+template <int CH>
+using PageTile = bf16[16][CH + 8];  // [token][channel]; rows 4 banks apart
 // piece i (16 bytes of a token row): eight pieces of a row, then the 16 tokens, then the next 64 channels - a wave's
 // instruction covers 8 tokens x 128 bytes
 __device__ __forceinline__ int page_piece_token(int i) { return (i >> 3) & 15; }
 __device__ __forceinline__ int page_piece_channel(int i) { return ((i & 7) + ((i >> 7) << 3)) * 8; }
 
-// tile -> page [channel][16 tokens], tokens < n only; all 256 threads
-template <bool KV8>
-__device__ __forceinline__ void store_v_page(const PageTile& tile, uint8_t* v_page, int channels, int n, float v_scale) {
+// tile -> page [channel][16 tokens], tokens < n only; all 256 threads (8-bit: with few channels, two threads for each)
+template <bool KV8, int CH>
+__device__ __forceinline__ void store_v_page(const PageTile<CH>& tile, uint8_t* v_page, int channels, int n, float v_scale) {
   if constexpr (KV8) {
-    for (int c = threadIdx.x; c < channels; c += 256) {
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
+    constexpr int PARTS = CH < 256 ? 2 : 1, TOK = 16 / PARTS;
+    for (int i = threadIdx.x; i < channels * PARTS; i += 256) {
+      const int c = i / PARTS, t0 = i % PARTS * TOK;
+      if (t0 >= n) continue;
+      uint32_t w[TOK / 4];
 #pragma unroll
-      for (int t = 0; t < 16; ++t)
-        if (t < n) w[t >> 2] |= f32_to_e4m3((float)tile[t][c] / v_scale) << (8 * (t & 3));
-      uint8_t* dst = v_page + c * 16;
-      if (n == 16) {
-        *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+      for (int q = 0; q < TOK / 4; ++q) w[q] = 0u;
+#pragma unroll
+      for (int t = 0; t < TOK; ++t)
+        if (t0 + t < n) w[t >> 2] |= f32_to_e4m3((float)tile[t0 + t][c] / v_scale) << (8 * (t & 3));
+      uint8_t* dst = v_page + c * 16 + t0;
+      if (t0 + TOK <= n) {
+        if constexpr (TOK == 16) *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+        else *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
       } else {
 #pragma unroll
-        for (int t = 0; t < 16; ++t)
-          if (t < n) dst[t] = (uint8_t)(w[t >> 2] >> (8 * (t & 3)));
+        for (int t = 0; t < TOK; ++t)
+          if (t0 + t < n) dst[t] = (uint8_t)(w[t >> 2] >> (8 * (t & 3)));
       }
     }
   } else {
@@ -456,7 +463,7 @@ __global__ __launch_bounds__(256) void v_append_pages_kernel(const bf16* __restr
                                                              const int32_t* __restrict__ block_tables,
                                                              int max_pages_per_seq) {
   constexpr int CH = kPageChannels, PER = 16 * CH / 8 / 256;
-  __shared__ __attribute__((aligned(16))) PageTile tile;
+  __shared__ __attribute__((aligned(16))) PageTile<CH> tile;
   int seq, p, t_first, n;
   if (!locate_page(blockIdx.x, cu_seqlens, n_seqs, total_tokens, seq, p, t_first, n)) return;
   const int64_t page = block_tables[(int64_t)seq * max_pages_per_seq + p];
@@ -468,7 +475,7 @@ __global__ __launch_bounds__(256) void v_append_pages_kernel(const bf16* __restr
     if (i < channels * 2 && tok < n) st_bf16x8(&tile[tok][ch], ld_bf16x8(src + (int64_t)tok * ld + ch));
   }
   __syncthreads();
-  store_v_page<KV8>(tile, (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32), channels, n, kv.v_scale);
+  store_v_page<KV8, CH>(tile, (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32), channels, n, kv.v_scale);
 }
 
 hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, const KvLayout& kv,
@@ -502,19 +509,19 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
 }
 
 // ------------------------------------------------------------------ KV import / export
-// One workgroup moves 16 tokens x up to 512 channels of K and of V between the packed arrays and one page.  Bound: HBM
+// One workgroup moves 16 tokens x up to CH channels of K and of V between the packed arrays and one page.  Bound: HBM
 // (every byte read once and written once).  A wave's instruction covers 8 tokens x 128 bytes, i.e. whole
 // lines of the packed side and runs of 512 bytes of the key page; values turn round in LDS, so that the
 // transposed page is read and written 16 bytes (8 tokens of a channel; 8-bit: all 16) at a time.  Element by element,
 // with 2-byte accesses on both sides, 23,000 tokens of 40 x 128 channels took 790 us in and 450 us out (0.96 GB each:
 // 1.2 and 2.1 TB/s); like this 195 and 192 us (4.9 TB/s; a plain copy reaches 4.7).
-template <bool KV8, bool TO_PAGES>
+template <bool KV8, bool TO_PAGES, int CH>
 __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packed, bf16* __restrict__ v_packed,
                                                       KvLayout kv, const int32_t* __restrict__ cu_seqlens, int n_seqs,
                                                       int total_tokens, const int32_t* __restrict__ block_tables,
                                                       int max_pages_per_seq) {
-  constexpr int CH = kPageChannels, PER = 16 * CH / 8 / 256;  // 16-byte pieces of K (and of V) per thread
-  __shared__ __attribute__((aligned(16))) PageTile tile;
+  constexpr int PER = 16 * CH / 8 / 256;  // 16-byte pieces of K (and of V) per thread
+  __shared__ __attribute__((aligned(16))) PageTile<CH> tile;
   int seq, p, t_first, n;
   if (!locate_page(blockIdx.x, cu_seqlens, n_seqs, total_tokens, seq, p, t_first, n)) return;
   const int64_t page = block_tables[(int64_t)seq * max_pages_per_seq + p];
@@ -559,7 +566,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       }
     }
     __syncthreads();
-    store_v_page<KV8>(tile, v_page, channels, n, kv.v_scale);
+    store_v_page<KV8, CH>(tile, v_page, channels, n, kv.v_scale);
   } else {
     bf16x8 k[PER];
     uint2 k8[PER];
@@ -572,11 +579,20 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       }
     }
     if constexpr (KV8) {
-      for (int c = threadIdx.x; c < channels; c += 256) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(v_page + c * 16);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+      constexpr int PARTS = CH < 256 ? 2 : 1, TOK = 16 / PARTS;
+      for (int i = threadIdx.x; i < channels * PARTS; i += 256) {
+        const int c = i / PARTS, t0 = i % PARTS * TOK;
+        uint32_t w[TOK / 4];
+        if constexpr (TOK == 16) {
+          const uint4 raw = *reinterpret_cast<const uint4*>(v_page + c * 16);
+          w[0] = raw.x, w[1] = raw.y, w[2] = raw.z, w[3] = raw.w;
+        } else {
+          const uint2 raw = *reinterpret_cast<const uint2*>(v_page + c * 16 + t0);
+          w[0] = raw.x, w[1] = raw.y;
+        }
 #pragma unroll
-        for (int t = 0; t < 16; ++t) tile[t][c] = (bf16)(e4m3_to_f32((w[t >> 2] >> (8 * (t & 3))) & 255u) * kv.v_scale);
+        for (int t = 0; t < TOK; ++t)
+          tile[t0 + t][c] = (bf16)(e4m3_to_f32((w[t >> 2] >> (8 * (t & 3))) & 255u) * kv.v_scale);
       }
     } else {
       for (int i = threadIdx.x; i < channels; i += 256) {
@@ -606,7 +622,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
   }
 }
 
-// The same element by element, for packed arrays that are not 16-byte aligned.
+// The same element by element, for packed arrays that are not 16-byte aligned and for the smallest 8-bit imports.
 __global__ __launch_bounds__(256) void kv_copy_kernel(int to_pages, bf16* __restrict__ k_packed,
                                                       bf16* __restrict__ v_packed, KvLayout kv,
                                                       const int32_t* __restrict__ cu_seqlens, int n_seqs,
@@ -679,17 +695,30 @@ hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const Kv
                           const int32_t* cu_seqlens, int n_seqs, int total_tokens,
                           const int32_t* block_tables, int max_pages_per_seq, hipStream_t s) {
   if (total_tokens <= 0) return hipSuccess;
-  if ((((uintptr_t)k_packed | (uintptr_t)v_packed) & 15) == 0) {
-    const dim3 grid((total_tokens >> 4) + n_seqs + 1, (kv.n_kv_heads * kv.head_dim + kPageChannels - 1) / kPageChannels);
-#define TDP_MOVE(KV8, TO)                                                                                        \
-  kv_move_kernel<KV8, TO><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
-                                               block_tables, max_pages_per_seq)
+  const int dkv = kv.n_kv_heads * kv.head_dim, pages = (total_tokens >> 4) + n_seqs + 1;
+  const bool aligned = (((uintptr_t)k_packed | (uintptr_t)v_packed) & 15) == 0;
+  // 8-bit imports of a few small tokens go element by element: one or two codes per thread instead of 16 in a row (128 channels,
+  // 256 / 2048 tokens 4.3 / 4.4 us against 4.6 / 4.9 page by page; 3072 tokens 5.8 against 5.0)
+  const bool few = kv.fp8 && to_pages && dkv <= 256 && total_tokens <= 2048;
+  if (aligned && !few) {
+    // 128 channels per workgroup as long as the chip could hold the workgroups of 512 channels all at once (eight per CU): the
+    // time is then a thread's own chain, above all the conversions of an 8-bit import, 16 of them and not 64 (1024 channels, 8 bits:
+    // 32 / 1024 tokens 4.5 / 5.9 us against 11.2 / 11.8, 15,138 tokens 29 against 36; bf16 within 0.3 us).  With more
+    // of them throughput counts (8 bits, 4096 channels, 21,768 tokens: 142 us with 512 channels, 153 with 128).
+    const bool narrow = pages * ((dkv + kPageChannels - 1) / kPageChannels) < 2048;
+    const int ch = narrow ? 128 : kPageChannels;
+    const dim3 grid(pages, (dkv + ch - 1) / ch);
+#define TDP_MOVE_(KV8, TO, CH)                                                                                             \
+  kv_move_kernel<KV8, TO, CH><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
+                                                   block_tables, max_pages_per_seq)
+#define TDP_MOVE(KV8, TO) do { if (narrow) TDP_MOVE_(KV8, TO, 128); else TDP_MOVE_(KV8, TO, kPageChannels); } while (0)
     if (kv.fp8) {
       if (to_pages) TDP_MOVE(true, true); else TDP_MOVE(true, false);
     } else {
       if (to_pages) TDP_MOVE(false, true); else TDP_MOVE(false, false);
     }
 #undef TDP_MOVE
+#undef TDP_MOVE_
     return hipGetLastError();
   }
   kv_copy_kernel<<<total_tokens, 256, 0, s>>>(to_pages, (bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens,

@@ -17,15 +17,17 @@ def tdp():
 
 
 LENS = [1, 15, 16, 17, 48, 0, 33, 7]
+MANY = LENS + [4096, 1, 4097, 2900]      # 690 pages: more workgroups of 512 channels than run at once ("wide")
 
 
 @pytest.mark.parametrize("kv_scales", [None, (0.03125, 0.7)])
-@pytest.mark.parametrize("shape", ["tiny_gqa", "tiny", "tiny_g2", "wide"])
-def test_page_moves_equal_the_element_path(tdp, shape, kv_scales):
+@pytest.mark.parametrize("shape,seq_lens", [("tiny_gqa", LENS), ("tiny", LENS), ("tiny_g2", LENS), ("wide", LENS), ("wide", MANY),
+                                            ("tiny_gqa", MANY)])
+def test_page_moves_equal_the_element_path(tdp, shape, seq_lens, kv_scales):
     sh = W.SHAPES["tiny"] if shape == "wide" else W.SHAPES[shape]
     if shape == "wide":   # 1280 channels: three column blocks, the last one half full
         sh = W.StageShape("wide", 1, 256, 10, 10, 128, 64)
-    lens = np.array(LENS, dtype=np.int64)
+    lens = np.array(seq_lens, dtype=np.int64)
     tab, pages = W.block_tables(77, lens)
     cu = np.concatenate([[0], np.cumsum(lens)])
     total, ch = int(cu[-1]), sh.n_kv_heads * sh.head_dim
