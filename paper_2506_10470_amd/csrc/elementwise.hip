@@ -895,17 +895,19 @@ hipError_t launch_to_bf16(const void* src, int src_is_f32, int64_t n, void* dst,
   return hipGetLastError();
 }
 
-// out[m] = the lowest index among the largest of logits[m][0 .. n).  One workgroup of 1024 threads per row.  NaNs
+// out[m] = the lowest index among the largest of logits[m][0 .. n).  One workgroup per row.  NaNs
 // never win a comparison; a row of NaNs gives 0.  The rule "greater, or equal at a lower index" does not depend on the
-// order of comparisons, so a thread may have many loads in flight: 16 bytes x 8 per turn, a row of 32000 in one
-// (a row is aligned by its first up to three elements).  Bound: the latency of a row's first bytes for a few rows, reading the
-// logits for many.  With 256 threads that load and compare one element per turn a launch took 42 us for 48
+// order of comparisons, so a thread may have many loads in flight: up to 8 x 16 bytes per turn, with 1024 threads a row of
+// 32000 in one (a row is aligned by its first up to three elements).  Bound: the latency of a row's first bytes for a few rows,
+// reading the logits for many.  With 256 threads that load and compare one element per turn a launch took 42 us for 48
 // rows of 32000 and 46 us for 512; like this 7 and 14.
-__global__ __launch_bounds__(1024) void argmax_rows_kernel(const float* __restrict__ logits, int64_t ld, int n,
-                                                           int32_t* __restrict__ out) {
-  constexpr int UN = 8;
-  __shared__ float s_val[16];
-  __shared__ int s_idx[16];
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void argmax_rows_kernel(const float* __restrict__ logits, int64_t ld, int n,
+                                                              int32_t* __restrict__ out) {
+  constexpr int UN = 8, WAVES = THREADS / 64;
+  constexpr bool SHORT = THREADS < 1024;
+  __shared__ float s_val[WAVES];
+  __shared__ int s_idx[WAVES];
   const float* row = logits + (int64_t)blockIdx.x * ld;
   const int tid = threadIdx.x;
   float best = -INFINITY;
@@ -921,13 +923,15 @@ __global__ __launch_bounds__(1024) void argmax_rows_kernel(const float* __restri
   const f32x4* body = reinterpret_cast<const f32x4*>(row + head);
   if (tid < head) take(row[tid], tid);
   if (tid < n - tail) take(row[tail + tid], tail + tid);
-  for (int j0 = 0; j0 < n4; j0 += 1024 * UN) {
+  for (int j0 = 0; j0 < n4; j0 += THREADS * UN) {
     f32x4 v[UN];
 #pragma unroll
-    for (int u = 0; u < UN; ++u) v[u] = body[min(j0 + u * 1024 + tid, n4 - 1)];  // (past the end: the last piece again)
+    for (int u = 0; u < UN; ++u)  // (past the end: the last piece again; short rows have fewer than UN pieces per thread)
+      if (!SHORT || j0 + u * THREADS < n4) v[u] = body[min(j0 + u * THREADS + tid, n4 - 1)];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const int at = head + 4 * min(j0 + u * 1024 + tid, n4 - 1);
+      if (SHORT && j0 + u * THREADS >= n4) break;
+      const int at = head + 4 * min(j0 + u * THREADS + tid, n4 - 1);
 #pragma unroll
       for (int e = 0; e < 4; ++e) take(v[u][e], at + e);
     }
@@ -944,14 +948,24 @@ __global__ __launch_bounds__(1024) void argmax_rows_kernel(const float* __restri
   }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 16; ++w) take(s_val[w], s_idx[w]);
+    for (int w = 1; w < WAVES; ++w) take(s_val[w], s_idx[w]);
     out[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
   }
 }
 
 hipError_t launch_argmax_rows(const float* logits, int64_t ld, int M, int n, int32_t* out, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  argmax_rows_kernel<<<M, 1024, 0, s>>>(logits, ld, n, out);
+  // As many threads as the row keeps busy: more of them only lengthen the workgroup's start and its last step, and on short rows
+  // the loads past the end (a row of 1000: 2.7 us with 128 threads, 3.8 with 1024, 5.9 with 1024 that all load eight
+  // pieces; 512 rows 3.2 / 5.5 / 9.0; a row of 4000 3.3 with 256 / 3.8 / 5.9; of 16000 4.8 with 512, 5.0 with 1024).  From
+  // 20000 on all eight pieces are there and are loaded without asking (32000: 5.9 us against 6.5).
+#define TDP_ARGMAX(THREADS) argmax_rows_kernel<THREADS><<<M, THREADS, 0, s>>>(logits, ld, n, out)
+  if (n <= 512) TDP_ARGMAX(64);
+  else if (n <= 2048) TDP_ARGMAX(128);
+  else if (n <= 5000) TDP_ARGMAX(256);
+  else if (n < 20000) TDP_ARGMAX(512);
+  else TDP_ARGMAX(1024);
+#undef TDP_ARGMAX
   return hipGetLastError();
 }
 

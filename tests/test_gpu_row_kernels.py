@@ -9,7 +9,7 @@ from test_gpu_parity import run_decode_case, tdp  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 1023, 4099, 32768, 32771, 70001])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 511, 515, 1023, 2048, 2051, 4099, 5003, 16383, 19999, 20003, 32768, 32771, 70001])
 def test_argmax_any_alignment(tdp, n):
     """Rows ld apart start at every offset inside 16 bytes; few distinct values, so ties are everywhere."""
     M, ld = 9, n + 5 if n % 2 else n + 3
