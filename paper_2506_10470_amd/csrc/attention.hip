@@ -431,32 +431,42 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   }
   __syncthreads();
   if (!s_last) return;
-  // four channels of one query head per thread; eight spans are asked for at once, so up to eight cost one round trip
+  // Four channels of one query head per thread; eight spans are asked for at once, so up to eight cost one round trip.  With more
+  // than two such turns, threads that a small group of heads leaves over share the spans out: `parts` runs of them, each with a
+  // maximum of its own, put together through LDS.  (391 spans, a layer in all: 16 K/V heads of 128 channels with one query head each
+  // 259 us on 32 threads, 201 in eight runs, 240 with the separate kernel; four requests, 8 K/V heads of 64 channels with four
+  // query heads each 324, 266 and 312.)  Up to two turns the order is one run's whatever the heads.
   constexpr int UN = 8;
-  for (int e = threadIdx.x; e < G * (DH / 4); e += 256) {
-    const int q = e / (DH / 4), c = e % (DH / 4) * 4, h = kvh * G + q;
+  const int columns = G * (DH / 4);
+  const int parts = n_spans > 2 * UN && columns <= 128 ? 256 / columns : 1;
+  float* const s_parts = &s_o[0][0][0];  // [part][column][4 sums, denominator, maximum]
+  static_assert(256 * 6 <= 4 * 16 * (DH + 4), "a record per thread");
+  for (int e = threadIdx.x; e < columns * parts; e += 256) {
+    const int part = e / columns, r = e - part * columns;
+    const int q = r / (DH / 4), c = r % (DH / 4) * 4, h = kvh * G + q;
     const int64_t base = ((int64_t)b * n_q_heads + h) * max_spans;
+    const int k_begin = part * n_spans / parts, k_end = (part + 1) * n_spans / parts;
     float2 ml[UN], oa[UN], ob[UN];
     auto fetch = [&](int k0) {
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
-        const int64_t slot = base + min(k0 + u, n_spans - 1);
+        const int64_t slot = base + min(k0 + u, k_end - 1);
         ml[u] = load_agent2(part_ml + slot * 2);
         oa[u] = load_agent2(part_o + slot * DH + c);
         ob[u] = load_agent2(part_o + slot * DH + c + 2);
       }
     };
-    fetch(0);
+    fetch(k_begin);
     float mt = kNegBig;
 #pragma unroll
     for (int u = 0; u < UN; ++u) mt = fmaxf(mt, ml[u].x);  // (past the end: the last span again)
-    for (int k = UN; k < n_spans; ++k) mt = fmaxf(mt, load_agent2(part_ml + (base + k) * 2).x);
+    for (int k = k_begin + UN; k < k_end; ++k) mt = fmaxf(mt, load_agent2(part_ml + (base + k) * 2).x);
     float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
-    for (int k0 = 0; k0 < n_spans; k0 += UN) {
-      if (k0 > 0) fetch(k0);
+    for (int k0 = k_begin; k0 < k_end; k0 += UN) {
+      if (k0 > k_begin) fetch(k0);
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
-        if (k0 + u >= n_spans) break;
+        if (k0 + u >= k_end) break;
         const float w = exp2f(ml[u].x - mt);
         den += w * ml[u].y;
         num[0] += w * oa[u].x;
@@ -464,6 +474,33 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
         num[2] += w * ob[u].x;
         num[3] += w * ob[u].y;
       }
+    }
+    if (parts > 1) {
+      float* rec = s_parts + e * 6;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rec[i] = num[i];
+      rec[4] = den;
+      rec[5] = mt;
+    } else {
+      bf16x4 o4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o4[i] = (bf16)(num[i] / den * out_scale);
+      *reinterpret_cast<bf16x4*>(out + operand_offset(out_lay, b, h * DH + c)) = o4;
+    }
+  }
+  if (parts == 1) return;
+  __syncthreads();
+  if ((int)threadIdx.x < columns) {
+    const int r = threadIdx.x, q = r / (DH / 4), c = r % (DH / 4) * 4, h = kvh * G + q;
+    float mt = kNegBig;
+    for (int part = 0; part < parts; ++part) mt = fmaxf(mt, s_parts[(part * columns + r) * 6 + 5]);
+    float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+    for (int part = 0; part < parts; ++part) {
+      const float* rec = s_parts + (part * columns + r) * 6;
+      const float w = exp2f(rec[5] - mt);
+      den += w * rec[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) num[i] += w * rec[i];
     }
     bf16x4 o4;
 #pragma unroll

@@ -1,12 +1,14 @@
-"""A decode step whose ctx_lens do not fit their block-table rows.  The kernels bring such a length into the row's range, so every
-access stays inside the tables, the work list and the grid, and the counters of finished spans end where they began:
-what the step leaves behind is one overwritten slot of the request's own pages, and later steps are not affected."""
+"""Decode steps at lengths where the sharing-out of a context changes: requests of many spans, and ctx_lens that do not fit their
+block-table rows.  The kernels bring such a length into the row's range, so every access stays inside the tables, the work list
+and the grid, and the counters of finished spans end where they began: what the step leaves behind is one overwritten slot
+of the request's own pages, and later steps are not affected."""
 import numpy as np
 import pytest
 import torch
 
 from harness import workload as W
 from harness.runner import Stage, i32
+from test_gpu_parity import run_decode_case
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +60,12 @@ def test_lengths_outside_a_row_leave_later_steps_alone(shape, span):
         fill(st)
         for _ in range(2):
             assert torch.equal(step(st, good), expected)
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,head_dim", [(2, 2, 64), (2, 2, 128), (6, 2, 128), (10, 2, 64), (16, 2, 128)])
+def test_many_spans_are_combined_by_all_threads(q_heads, kv_heads, head_dim):
+    """More than 16 spans are shared out in runs where a group of heads leaves threads over: 16, 8, 2, 3 and (none left) 1 run,
+    with 16 spans (still one), 17 and 40, and a request of one span beside them."""
+    from paper_2506_10470_amd import tdp
+    sh = W.StageShape("spans", 1, 256, q_heads, kv_heads, head_dim, 128)
+    run_decode_case(tdp, sh, [4095, 4096, 10000, 3], max_pages_per_seq=626, span=256)
