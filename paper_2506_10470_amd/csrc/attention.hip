@@ -39,7 +39,7 @@ constexpr float kNegBig = -1.0e30f;  // finite stand-in for -inf: exp2 gives exa
 // 5.5 at batch 512, 5.7 against 5.2 at batch 256).
 // =====================================================================================
 
-// items[i] = (request, span index, tokens to attend to = ctx + 1, 0) for i < n_items[0], and
+// items[i] = (request, span index, tokens to attend to = ctx + 1, 0) for every span of the batch, and
 // (-1, ...) for the rest of the list up to max_items, so a workgroup learns everything about its
 // work - or that it has none - from one 16-byte record.  item_pages[i][j] = physical page of the j-th
 // 16-token page of item i's span (span_len / 16 entries), entries past the request's last page clamped to
@@ -58,7 +58,6 @@ constexpr float kNegBig = -1.0e30f;  // finite stand-in for -inf: exp2 gives exa
 __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restrict__ ctx_lens, int batch, int span_len,
                                                         const int32_t* __restrict__ block_tables,
                                                         int max_pages_per_seq, int4* __restrict__ items, int max_items,
-                                                        int32_t* __restrict__ n_items,
                                                         int32_t* __restrict__ item_pages) {
   constexpr int NP = 16;      // parts of a span
   constexpr int NB = NP + 1;  // class 0: full spans; 1..NP: last span with > (NP-c)/NP of span_len
@@ -101,7 +100,6 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
     class_base[c] = total;
     total += class_total[c];
   }
-  if (blockIdx.x == 0 && tid == 0) n_items[0] = total;
   for (int i = total + blockIdx.x * 256 + tid; i < max_items; i += gridDim.x * 256) items[i] = make_int4(-1, 0, 0, 0);
   const int b = blockIdx.x * 4 + wave;  // this wave's request
   if (b >= batch) return;
@@ -533,12 +531,11 @@ bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len)
 }
 
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
-                            int max_spans, int span_len, int4* items, int32_t* n_items, int32_t* item_pages,
-                            hipStream_t s) {
+                            int max_spans, int span_len, int4* items, int32_t* item_pages, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
   const int max_items = attn_decode_items(batch, max_spans, span_len);
   attn_plan_kernel<<<(batch + 3) / 4, 256, 0, s>>>(ctx_lens, batch, span_len, block_tables, max_pages_per_seq, items,
-                                                  max_items, n_items, item_pages);
+                                                  max_items, item_pages);
   return hipGetLastError();
 }
 

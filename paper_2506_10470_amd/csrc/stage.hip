@@ -62,7 +62,6 @@ struct tdp_stage {
     float *part_o = nullptr, *part_ml = nullptr;
     unsigned* spans_done = nullptr;  // finished spans of every (request, K/V head): zero between launches
     int4* attn_items = nullptr;     // decode work list, rebuilt every step
-    int32_t* attn_n_items = nullptr;
     int32_t* attn_item_pages = nullptr;  // physical pages of every item's span
   };
   Scratch sc[2];
@@ -179,7 +178,7 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
   const bool planned = ctx_lens && attn_decode_planned(M, c.n_kv_heads, st->max_chunks, span_len);
   if (planned)
     HIP_TRY(launch_attn_plan(ctx_lens, block_tables, c.max_pages_per_seq, M, st->max_chunks, span_len, sc.attn_items,
-                             sc.attn_n_items, sc.attn_item_pages, s));
+                             sc.attn_item_pages, s));
   const int l_begin = st->layer_count > 0 ? st->layer_first : 0;
   const int l_end = st->layer_count > 0 ? st->layer_first + st->layer_count : c.n_layers;
   // A projection whose K range was split leaves fp32 partials in the workspace; the kernel that
@@ -356,7 +355,6 @@ int tdp_stage_create(const tdp_stage_config* cfg, tdp_stage** out) {
     A(&sc.attn_items, mb * st->max_chunks, false);
     // spans longer than the minimum round the span count up: up to (1024 / 256 - 1) extra minimum spans' worth
     A(&sc.attn_item_pages, mb * (st->max_chunks + kDecodeSpanMax / kDecodeSpanMin) * (kDecodeSpanMin / 16), false);
-    A(&sc.attn_n_items, 1, true);
   }
   if (e == hipSuccess && st->n_scratch == 2) {
     e = hipStreamCreateWithFlags(&st->aux_stream, hipStreamNonBlocking);
@@ -395,8 +393,8 @@ void tdp_stage_destroy(tdp_stage* st) {
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (tdp_stage::Scratch& sc : st->sc) {
-    void* sp[] = {sc.y, sc.qkv, sc.qkv32, sc.attn, sc.h, sc.u, sc.xa, sc.xb, sc.ws, sc.part_o, sc.part_ml, sc.spans_done, sc.attn_items,
-                  sc.attn_n_items, sc.attn_item_pages};
+    void* sp[] = {sc.y, sc.qkv, sc.qkv32, sc.attn, sc.h, sc.u, sc.xa, sc.xb, sc.ws, sc.part_o, sc.part_ml,
+                  sc.spans_done, sc.attn_items, sc.attn_item_pages};
     for (void* p : sp)
       if (p) (void)hipFree(p);
   }

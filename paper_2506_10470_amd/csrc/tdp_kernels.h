@@ -163,8 +163,7 @@ int attn_decode_span(int batch, int n_kv_heads);
 // of its span (span_len / 16 entries each)
 int attn_decode_items(int batch, int max_spans, int span_len);
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
-                            int max_spans, int span_len, int4* items, int32_t* n_items, int32_t* item_pages,
-                            hipStream_t s);
+                            int max_spans, int span_len, int4* items, int32_t* item_pages, hipStream_t s);
 // The attention kernel: finishes every request whose context fits one span in one workgroup per K/V head; of a longer one
 // the workgroups leave fp32 partials (part_o, part_ml) and the last of them to finish combines them.  spans_done [batch]
 // [n_kv_heads] counts the finished spans: zero before the first launch, zero again after every launch.
