@@ -807,8 +807,10 @@ hipError_t launch_attn_prefill(const void* qkv, int64_t ld, int total_tokens, in
                                int max_pages_per_seq, void* out, OperandLayout out_layout, hipStream_t s) {
   if (total_tokens <= 0 || n_seqs <= 0) return hipSuccess;
   // Four waves and not eight (measured, us: 12 prompts of a 13B shape 170 / 143, 24 of a 7B shape 177 / 159, 8 of 40 / 8
-  // heads 258 / 253, 16 of 64 / 8 heads level): tiles half as long compute less beyond the diagonal and two
-  // workgroups of a CU wait at barriers of their own.
+  // heads 258 / 253, 16 of 64 / 8 heads level; 64 channels, 32 / 8 heads: one prompt of 4096 156 / 114, of 16384 1603 / 1499, 16 of
+  // 1024 173 / 141, 24 ragged ones 126 / 118; 32 / 32 heads 161 / 113, 1716 / 1491, 175 / 143, 114 / 103): tiles half as long
+  // compute less beyond the diagonal and two workgroups of a CU wait at barriers of their own.  One prompt of 100 tokens
+  // costs 0.5 to 1.5 us more, a thread stages twice the keys (128 channels 11 / 12, 64 channels 9 / 9).
   if (kv.head_dim == 128)
     return launch_attn_prefill_t<128, 4>(qkv, ld, total_tokens, n_seqs, n_q_heads, kv, cu_seqlens, block_tables,
                                          max_pages_per_seq, out, out_layout, s);

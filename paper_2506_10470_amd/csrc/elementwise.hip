@@ -249,11 +249,12 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 // angle, computed in double precision on the host.
 //
 // A unit is eight rotated pairs or eight values; a token's units are walked by gridDim.y workgroups of 256 threads.
-// Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In prefill one
-// workgroup takes a token (its look-ups are shared); in decode every unit has a thread of its own and asks for the
-// partials of UN splits at once: as one workgroup of 1024 threads per token that fetched a split per turn, a
-// launch of 16 / 48 (7B shape) / 128 (13B shape) / 512 tokens took 9.4 / 11.3 / 17.6 / 20.5 us, now 5.3 / 7.0 / 14 / 20.2
-// (what is left of the last two is the value append: 2-byte stores 32 bytes apart).
+// Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In decode, and in prefill
+// where there are partials to sum, every unit has a thread of its own, which asks for the partials of UN splits at
+// once; only a prefill without partials takes one workgroup per token (its look-ups are shared).  As one workgroup of 1024
+// threads per token that fetched a split per turn, a launch of 16 / 48 (7B shape) / 128 (13B shape) / 512 tokens took
+// 9.4 / 11.3 / 17.6 / 20.5 us, now 5.4 / 8.1 / 16 / 21 (what is left of the last two is the value append: 2-byte stores
+// 32 bytes apart).
 template <int UN>
 __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, int64_t ld, int n_q_heads,
                                                       KvLayout kv, const float2* __restrict__ table,
@@ -303,8 +304,9 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, in
       const float(&a)[8] = ab[0];
       const float(&b)[8] = ab[1];
       float fra[8], frb[8];
-      // (written out as fused operations, the form that the compiler had given a[i] * sin + b[i] * cos in each of the eight
-      // places, so that queries and keys keep their bits)
+      // (Which product of the second half is fused has no meaning of its own: written out, it is the choice that the compiler
+      // once made in each of the eight places, and keeps queries and keys to the bit.  Either form rounds the other product
+      // once in fp32, 2^-16 of the bf16 or 8-bit rounding behind it.)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float2 t2 = cs[c0 + i];

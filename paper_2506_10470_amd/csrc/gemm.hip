@@ -231,8 +231,8 @@ __device__ __forceinline__ bool gemm_tile_of_block(const GemmParams& p, int& til
 // on the 70B shapes: +6 to +12 % on the down projection, +2 to +8 % on gate/up, +1 to +4 % on QKV and
 // O.  With more tile rows the weights are shared through L2 and the hint costs 5-10 % on the large
 // shapes; the one exception that pays is two tile rows on a wide projection without split-K (gate/up at
-// M = 512: the two readers of a weight tile are neighbours in one super-block and run at the same time,
-// so the second read still finds the line): -1.8 %.
+// M = 512: the two readers of a weight tile are neighbours in the order of the tiles and run at the same
+// time, so the second read still finds the line): -1.8 %.
 //
 // Tiles of up to 128 x 128 can sum K in chunks (see sum_order_splits): a second set of accumulators (which costs 128 x 128
 // its second workgroup per CU, so there are two forms of that).
@@ -637,12 +637,15 @@ static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, in
 
 // The order in which a projection of up to 128 rows sums over K, as a split-K factor.  fp32 sums in another order differ in
 // their last bits, which the bf16 roundings behind them carry through every layer: about 0.5 % of a
-// hidden state after a few layers, as much as bf16 itself costs, and enough to turn one greedy token in
-// seventy between near-equal logits (measured: 2 of 48 over four layers and a vocabulary of 32000).  So small
-// decode batches keep one order whatever tile makes the sum: the factor below (a launch of 128 x 256 tiles, one per CU,
-// in super-blocks dealt to the XCDs, 1.8 us per round of k-tiles plus the partials' round trip), either as that many
-// split-K workgroups or, where the tile has registers for it, chunk by chunk in one.  Keeping it costs what a freer factor
-// would gain: 13B decode, 128 rows, two layers 1206 against 1172 us; 7B token step, 48 rows, 796 against 738.
+// hidden state after a few layers, as much as bf16 itself costs, and enough to turn a greedy token between near-equal
+// logits (measured once in four runs: 2 of 48 over four layers and a vocabulary of 32000).  The distance to the 64-bit result is the
+// same in either order.  What the rule below is for is nothing but this: decode batches of up to 128 rows give the bits that they
+// gave when every such launch was made of 128 x 256 tiles, one per CU (in super-blocks dealt to the XCDs, 1.8 us per round
+// of k-tiles plus the partials' round trip - the cost that it minimises), whatever tile makes the sum now: as that many split-K
+// workgroups or, where the tile has registers for it, chunk by chunk in one.  The factor depends on M, N, K and the
+// workspace, so a request's bits may change with the batch around it (4096 x 4096 is 16 splits up to 64 rows, 11 at 128), and above
+// 128 rows the plan is free.  Keeping it costs what a freer factor would gain: 13B decode, 128 rows, two layers 1206 against 1172
+// us; 7B token step, 48 rows, 796 against 738.
 // Short sums (K <= 1024) are free: there another order moves a hidden state by 3e-5 at most, and a freer factor takes a
 // two-layer stage of hidden size 256 from 66 to 59 us.
 constexpr int kSumOrderRows = 128, kSumOrderKTiles = 16;

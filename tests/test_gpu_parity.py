@@ -178,7 +178,7 @@ def run_prefill_case(tdp, shape_name, seq_lens, n_layers=None, stream_id=2, deco
     # the planner's own choice
     (4, 768, 256, 0, 0, 0), (4, 256, 704, 0, 0, 1), (33, 320, 128, 0, 2, 0), (64, 512, 512, 0, 1, 1),
     (512, 1280, 2048, 0, 0, 0), (1000, 256, 64, 0, 0, 1), (257, 516, 192, 0, 2, 1),
-    # every kernel variant (1: 256 x 256 tile, 2: 128 x 256, 3: 128 x 128), ragged M and N, split-K
+    # the variants that the tile argument selects (1: 256 x 256 tile, 2: 128 x 256, 3: 128 x 128), ragged M and N, split-K
     (300, 768, 1024, 1, 1, 0), (257, 516, 192, 1, 2, 1), (513, 520, 448, 1, 2, 1),
     (300, 516, 256, 1, 1, 1), (513, 260, 128, 1, 1, 1),   # whole-tile residual epilogue, ragged M and N
     (100, 384, 256, 2, 3, 0), (130, 1024, 320, 2, 1, 1), (70, 260, 128, 2, 1, 0), (65, 512, 256, 2, 2, 1),
@@ -433,14 +433,14 @@ def test_prefill_7b_shaped_layer_many_tiles(tdp):
 
 
 @pytest.mark.parametrize("shape,seq_lens", [
-    # one head per workgroup (multi-head attention and groups that no power of two divides): a query
-    # tile is 256 positions
-    ("tiny", [4096]),                       # head_dim 64, sixteen query tiles, 257 pages
-    ("tiny", [257, 300, 513, 1000, 256]),   # tile edges: one position into a second tile, exact multiples
-    ("tiny_bias", [700, 259]),              # group of 5 -> one head per workgroup
-    # two heads per workgroup: 128 positions per tile
+    # a query tile is 128 columns, all heads of a group at one position and then the next: 128 positions of one
+    # head (multi-head attention), 25 of five (three columns are left over)
+    ("tiny", [4096]),                       # head_dim 64, 32 query tiles, 257 pages
+    ("tiny", [257, 300, 513, 1000, 256]),   # tile edges: one position into another tile, exact multiples
+    ("tiny_bias", [700, 259]),
+    # two heads: 64 positions per tile
     ("tiny_g2", [300, 129, 257, 128]),
-    # four and eight heads per workgroup: 64 and 32 positions per tile
+    # four and eight heads: 32 and 16 positions per tile
     ("tiny_gqa", [200, 65, 64, 449]),
     ("tiny_h128", [130, 577]),
     ("tiny_mqa", [100, 33, 32, 290]),
@@ -455,14 +455,14 @@ def test_prefill_attention_beyond_one_query_tile(tdp, shape, seq_lens):
 
 
 def test_prefill_7b_shaped_layer_prompts_of_several_query_tiles(tdp):
-    """One 7B-shaped layer (32 heads x 128, multi-head attention: 256 query positions per workgroup)
+    """One 7B-shaped layer (32 heads x 128, multi-head attention: 128 query positions per workgroup)
     on prompts of 257 to 1000 tokens."""
     run_prefill_case(tdp, "7b_quarter", [257, 300, 513, 1000], n_layers=1)
 
 
 def test_prefill_13b_shaped_layer_longest_prompt_of_its_benchmark_batch(tdp):
     """One 13B-shaped layer (40 heads x 128) on a prompt as long as the longest of the 32-prompt
-    benchmark batch (1838 tokens: eight query tiles per head)."""
+    benchmark batch (1838 tokens: fifteen query tiles per head)."""
     run_prefill_case(tdp, "13b_quarter", [int(W.prefill_seq_lens("13b_quarter", 32).max())], n_layers=1)
 
 
