@@ -404,20 +404,29 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
       out[operand_offset(out_lay, b, h * DH + c)] = (bf16)(num / den * out_scale);
     } else {
       const int64_t slot = ((int64_t)b * n_q_heads + h) * max_spans + span;
-      store_agent(part_o + slot * DH + c, num);
-      if (c == 0) {
-        store_agent(part_ml + slot * 2 + 0, mt);
-        store_agent(part_ml + slot * 2 + 1, den);
+      if (spans_done) {
+        store_agent(part_o + slot * DH + c, num);
+        if (c == 0) {
+          store_agent(part_ml + slot * 2 + 0, mt);
+          store_agent(part_ml + slot * 2 + 1, den);
+        }
+      } else {
+        part_o[slot * DH + c] = num;
+        if (c == 0) {
+          part_ml[slot * 2 + 0] = mt;
+          part_ml[slot * 2 + 1] = den;
+        }
       }
     }
   }
-  if (n_spans == 1) return;
+  if (n_spans == 1 || !spans_done) return;
   // ---- a request of several spans: whoever finishes last combines them, in the order of the spans whoever that is,
   //   out = sum_k o_k 2^(m_k - m) / sum_k l_k 2^(m_k - m).
   // The spans of a request are made on different XCDs, whose L2s do not see each other: partials are stored
   // and read at agent scope (past the L2), each wave waits until its stores have arrived, and only then is the span
-  // counted.  The last one puts the counter back to zero for the next launch.  (A second kernel did this: a launch of 4.5 to
-  // 5 us in every layer for small batches, 10 us for 512 requests, nearly all of its workgroups with nothing to do.)
+  // counted.  The last one puts the counter back to zero for the next launch.  (A second kernel, attn_decode_merge_kernel, costs
+  // a launch of 4.5 to 5 us in every layer for small batches, 10 us for 512 requests, nearly all of its workgroups with nothing
+  // to do; where it still is the better way, see attn_decode_counts_spans.)
   __shared__ int s_last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -507,6 +516,29 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   }
 }
 
+// The same by a kernel of its own, in the order of the spans.
+template <int DH>
+__global__ __launch_bounds__(DH) void attn_decode_merge_kernel(const float* __restrict__ part_o,
+                                                               const float* __restrict__ part_ml,
+                                                               const int32_t* __restrict__ ctx_lens,
+                                                               int max_pages_per_seq, int n_q_heads, int max_spans,
+                                                               int span_len, bf16* __restrict__ out,
+                                                               OperandLayout out_lay, float out_scale) {
+  const int h = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
+  const int n_spans = (decode_position(ctx_lens[b], max_pages_per_seq) + span_len) / span_len;
+  if (n_spans <= 1) return;  // finished by the attention kernel itself
+  const int64_t base = ((int64_t)b * n_q_heads + h) * max_spans;
+  float m = kNegBig;
+  for (int k = 0; k < n_spans; ++k) m = fmaxf(m, part_ml[(base + k) * 2]);
+  float num = 0.f, den = 0.f;
+  for (int k = 0; k < n_spans; ++k) {
+    const float w = exp2f(part_ml[(base + k) * 2] - m);
+    den += w * part_ml[(base + k) * 2 + 1];
+    num += w * part_o[(base + k) * DH + c];
+  }
+  out[operand_offset(out_lay, b, h * DH + c)] = (bf16)(num / den * out_scale);
+}
+
 // Span length.  A workgroup's fixed costs (start-up, the merge of its four waves, its partial
 // result) are paid once per span, so spans should be as long as the batch allows while the launch
 // still has several workgroups per CU; a context that fits one span needs no partials at all.
@@ -520,6 +552,20 @@ int attn_decode_span(int batch, int n_kv_heads) {
 int attn_decode_items(int batch, int max_spans, int span_len) {
   // max_spans counts spans of the minimum length; longer spans need proportionally fewer slots
   return batch * ((max_spans * kDecodeSpanMin + span_len - 1) / span_len);
+}
+
+// Whether the attention kernel combines the spans itself.  A workgroup that counts its span waits until its partials have arrived
+// and for the count, a few us in which it holds its slot under a saturated memory system; the second kernel is a launch in
+// every layer and reads the partials of all query heads again.  With four query heads or more per K/V head the count is ahead (a layer
+// with 8 K/V heads of 128 channels, 16 to 200 requests of 500 to 39,000 tokens: 0 to 7 % with eight, 0 to 5 % with five, 4 to -1 % with
+// four).  With one or two the second kernel is, from about ten spans on: one, 16 heads, 16 requests of 9000 / 20,000 / 39,000 tokens 239 /
+// 488 / 927 us with the count, 231 / 455 / 833 with the second kernel; 40 heads 537 / 1119 / 2165 and 522 / 1089 / 2063; two, 8 K/V heads, 64
+// requests 422 / 892 / 1721 and 417 / 868 / 1653 (3000 tokens level, 500 tokens 1.5 to 2.5 us for a kernel that finds nothing to do).
+// How long the contexts are is known on the device alone: the line goes by the longest that the block tables allow.  Spans
+// below 1024 tokens stay with the count: they are for small batches, where the second kernel walks hundreds of them
+// in a row (one request of 100,000 tokens, 16 heads: 240 us, with the count 201).
+bool attn_decode_counts_spans(int batch, int n_q_heads, int n_kv_heads, int max_spans, int span_len) {
+  return n_q_heads > 2 * n_kv_heads || span_len < 1024 || attn_decode_items(batch, max_spans, span_len) < 10 * batch;
 }
 
 // Whether a decode step makes a work list.  Without one a workgroup's look-ups are the request's length and its table row.
@@ -560,6 +606,20 @@ hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_he
     if (kv.fp8) TDP_DECODE(64, true); else TDP_DECODE(64, false);
   }
 #undef TDP_DECODE
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_decode_merge(int batch, int n_q_heads, const KvLayout& kv, const int32_t* ctx_lens,
+                                    int max_pages_per_seq, const float* part_o, const float* part_ml, int max_spans,
+                                    int span_len, void* out, OperandLayout out_layout, hipStream_t s) {
+  if (batch <= 0) return hipSuccess;
+  const float out_scale = kv.fp8 ? kv.v_scale : 1.0f;
+  const dim3 grid(n_q_heads, batch);
+#define TDP_MERGE(DH)                                                                                                  \
+  attn_decode_merge_kernel<DH><<<grid, DH, 0, s>>>(part_o, part_ml, ctx_lens, max_pages_per_seq, n_q_heads, max_spans, \
+                                                   span_len, (bf16*)out, out_layout, out_scale)
+  if (kv.head_dim == 128) TDP_MERGE(128); else TDP_MERGE(64);
+#undef TDP_MERGE
   return hipGetLastError();
 }
 

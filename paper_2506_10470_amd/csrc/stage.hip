@@ -32,7 +32,7 @@ int fail_hip(hipError_t e, const char* what) {
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
-enum TimeClass { T_NORM = 0, T_QKV, T_ROPE, T_ATTN, T_O, T_GU, T_DOWN, T_MERGE, T_COUNT };  // T_MERGE: no kernel of its own any more, reads 0
+enum TimeClass { T_NORM = 0, T_QKV, T_ROPE, T_ATTN, T_O, T_GU, T_DOWN, T_MERGE, T_COUNT };
 
 }  // namespace
 
@@ -179,6 +179,7 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
   if (planned)
     HIP_TRY(launch_attn_plan(ctx_lens, block_tables, c.max_pages_per_seq, M, st->max_chunks, span_len, sc.attn_items,
                              sc.attn_item_pages, s));
+  const bool count_spans = attn_decode_counts_spans(M, c.n_q_heads, c.n_kv_heads, st->max_chunks, span_len);
   const int l_begin = st->layer_count > 0 ? st->layer_first : 0;
   const int l_end = st->layer_count > 0 ? st->layer_first + st->layer_count : c.n_layers;
   // A projection whose K range was split leaves fp32 partials in the workspace; the kernel that
@@ -231,11 +232,16 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
         HIP_TRY(launch_attn_decode(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, planned ? sc.attn_items : nullptr,
                                    planned ? sc.attn_item_pages : block_tables,
                                    planned ? span_len / 16 : c.max_pages_per_seq, ctx_lens,
-                                   sc.part_o, sc.part_ml, sc.spans_done, st->max_chunks, span_len, sc.attn,
-                                   layout_paired(st->dq), s));
+                                   sc.part_o, sc.part_ml, count_spans ? sc.spans_done : nullptr, st->max_chunks, span_len,
+                                   sc.attn, layout_paired(st->dq), s));
       else
         HIP_TRY(launch_attn_prefill(sc.qkv, st->Nqkv_pad, M, n_seqs, c.n_q_heads, kv, cu_seqlens, block_tables,
                                     c.max_pages_per_seq, sc.attn, layout_paired(st->dq), s));
+    }
+    if (ctx_lens && !count_spans) {  // a4, second kernel: requests longer than one span are combined from their partials
+      Timer t(st, s, timed, T_MERGE);
+      HIP_TRY(launch_attn_decode_merge(M, c.n_q_heads, kv, ctx_lens, c.max_pages_per_seq, sc.part_o, sc.part_ml,
+                                       st->max_chunks, span_len, sc.attn, layout_paired(st->dq), s));
     }
     {  // a5: output projection + residual -> h (fp32)
       Timer t(st, s, timed, T_O);

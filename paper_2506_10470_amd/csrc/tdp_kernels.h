@@ -165,15 +165,20 @@ int attn_decode_items(int batch, int max_spans, int span_len);
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
                             int max_spans, int span_len, int4* items, int32_t* item_pages, hipStream_t s);
 // The attention kernel: finishes every request whose context fits one span in one workgroup per K/V head; of a longer one
-// the workgroups leave fp32 partials (part_o, part_ml) and the last of them to finish combines them.  spans_done [batch]
-// [n_kv_heads] counts the finished spans: zero before the first launch, zero again after every launch.
+// the workgroups leave fp32 partials (part_o, part_ml).  With spans_done [batch][n_kv_heads] (zero before the first launch, zero
+// again after every launch) they count the finished spans, and the last of them to finish combines them; with null,
+// launch_attn_decode_merge does so behind it (attn_decode_counts_spans says which way to take).
 // With a work list: items and item_pages as launch_attn_plan left them, item_pitch = span_len / 16.  Without one
 // (attn_decode_planned is false): items null, item_pages = the block tables, item_pitch = max_pages_per_seq.
+bool attn_decode_counts_spans(int batch, int n_q_heads, int n_kv_heads, int max_spans, int span_len);
 bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len);
 hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_heads, const KvLayout& kv,
                               const int4* items, const int32_t* item_pages, int item_pitch, const int32_t* ctx_lens,
                               float* part_o, float* part_ml, unsigned* spans_done, int max_spans, int span_len,
                               void* out, OperandLayout out_layout, hipStream_t s);
+hipError_t launch_attn_decode_merge(int batch, int n_q_heads, const KvLayout& kv, const int32_t* ctx_lens,
+                                    int max_pages_per_seq, const float* part_o, const float* part_ml, int max_spans,
+                                    int span_len, void* out, OperandLayout out_layout, hipStream_t s);
 // diagnostic: dst[i] = E4M3 code of src[i] / scale (to_codes) or dst[i] = value of code src[i] (fp32), through the
 // same device functions the KV kernels use (the decode direction through the hardware conversion)
 hipError_t launch_e4m3_convert(int to_codes, const void* src, void* dst, int64_t n, float scale, hipStream_t s);

@@ -69,3 +69,30 @@ def test_many_spans_are_combined_by_all_threads(q_heads, kv_heads, head_dim):
     from paper_2506_10470_amd import tdp
     sh = W.StageShape("spans", 1, 256, q_heads, kv_heads, head_dim, 128)
     run_decode_case(tdp, sh, [4095, 4096, 10000, 3], max_pages_per_seq=626, span=256)
+
+
+@pytest.mark.parametrize("group,head_dim,kv_scales", [(1, 64, None), (1, 128, (0.03125, 0.7)), (2, 128, None), (2, 64, (0.03125, 0.7))])
+def test_both_ways_of_combining_spans_give_the_same_bits(group, head_dim, kv_scales):
+    """With one or two query heads per K/V head, how long a context the block tables allow decides whether spans are combined by
+    the attention kernel (9216 tokens: nine spans of 1024) or by a kernel behind it (10240: ten).  The order of the spans is the
+    same, so the outputs are."""
+    from paper_2506_10470_amd import tdp
+    heads, ctx = 40, np.array([5000, 0, 1023, 1024, 9215, 3, 2047, 2048, 100, 1500, 4096])
+    sh = W.StageShape("ways", 1, 256, group * heads, heads, head_dim, 128)
+    B = len(ctx)
+    x = W.hidden_states(sh, B, 1, device="cuda")
+    cu = np.concatenate([[0], np.cumsum(ctx)])
+    outs = []
+    for tokens in (9216, 10240):
+        tables, pages = W.block_tables(9, ctx + 1, max_pages_per_seq=tokens // 16)
+        with Stage(tdp, sh, pages, B, 0, 0, tokens // 16, kv_scales=kv_scales) as st:
+            for l in range(sh.n_layers):
+                k, v = (W.kv_packed(sh, l, w, int(cu[-1]), 7, device="cuda") for w in "kv")
+                tdp.tdp_stage_kv_import(st.h, l, k, v, i32(cu), i32(np.maximum(tables, 0)), B, int(cu[-1]))
+            out = torch.full_like(x, float("nan"))
+            tdp.tdp_stage_timing_enable(st.h, True)
+            tdp.tdp_stage_decode(st.h, x, i32(ctx), i32(tables), B, out)
+            assert (tdp.tdp_stage_timing_read(st.h)["attention_merge"] > 0) == (tokens == 10240)
+            outs.append(out.view(torch.int16))
+    assert not torch.isnan(out.float()).any()
+    assert torch.equal(*outs)
