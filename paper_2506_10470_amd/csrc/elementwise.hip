@@ -401,7 +401,7 @@ __device__ __forceinline__ int page_piece_token(int i) { return (i >> 3) & 15; }
 __device__ __forceinline__ int page_piece_channel(int i) { return ((i & 7) + ((i >> 7) << 3)) * 8; }
 
 // tile -> page [channel][16 tokens], tokens < n only; all 256 threads (8-bit: with few channels, two threads for each)
-template <bool KV8, int CH>
+template <bool KV8, int CH, bool NT>
 __device__ __forceinline__ void store_v_page(const PageTile<CH>& tile, uint8_t* v_page, int channels, int n, float v_scale) {
   if constexpr (KV8) {
     constexpr int PARTS = CH < 256 ? 2 : 1, TOK = 16 / PARTS;
@@ -438,8 +438,8 @@ __device__ __forceinline__ void store_v_page(const PageTile<CH>& tile, uint8_t* 
       }
       bf16* dst = reinterpret_cast<bf16*>(v_page) + c * 16 + t0;
       if (t0 + 8 <= n) {
-        st_bf16x8(dst, a);
-        st_bf16x8(dst + 16, b);
+        st_bf16x8_once<NT>(dst, a);
+        st_bf16x8_once<NT>(dst + 16, b);
       } else {
 #pragma unroll
         for (int t = 0; t < 8; ++t)
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256) void v_append_pages_kernel(const bf16* __restr
     if (i < channels * 2 && tok < n) st_bf16x8(&tile[tok][ch], ld_bf16x8(src + (int64_t)tok * ld + ch));
   }
   __syncthreads();
-  store_v_page<KV8, CH>(tile, (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32), channels, n, kv.v_scale);
+  store_v_page<KV8, CH, false>(tile, (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32), channels, n, kv.v_scale);
 }
 
 hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, const KvLayout& kv,
@@ -517,7 +517,10 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
 // transposed page is read and written 16 bytes (8 tokens of a channel; 8-bit: all 16) at a time.  Element by element,
 // with 2-byte accesses on both sides, 23,000 tokens of 40 x 128 channels took 790 us in and 450 us out (0.96 GB each:
 // 1.2 and 2.1 TB/s); like this 195 and 192 us (4.9 TB/s; a plain copy reaches 4.7).
-template <bool KV8, bool TO_PAGES, int CH>
+// ONCE: from 16 MiB of packed keys and values on, stores are non-temporal (1), from 256 MiB on, what the memory-side cache holds, loads
+// as well (2); calls of prompts' caches, in + out, us, ONCE 0 / 1 / 2: 27 MB 27.0 / 23.7 / 30.2; 50 MB 50.4 / 40.4; 120 MB 107 / 100 / 99;
+// 0.95 GB 389 / 388 / 380.  Below that nothing is gained (7 MB 12.5 / 12.4 / 14.2), and a cache just imported is there for the next step.
+template <bool KV8, bool TO_PAGES, int CH, int ONCE>
 __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packed, bf16* __restrict__ v_packed,
                                                       KvLayout kv, const int32_t* __restrict__ cu_seqlens, int n_seqs,
                                                       int total_tokens, const int32_t* __restrict__ block_tables,
@@ -545,8 +548,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
     for (int j = 0; j < PER; ++j) {
       const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
       if (i < pieces && tok < n) {
-        k[j] = ld_bf16x8(kp + (int64_t)tok * dkv + ch);
-        v[j] = ld_bf16x8(vp + (int64_t)tok * dkv + ch);
+        k[j] = ld_bf16x8_once<(ONCE > 1)>(kp + (int64_t)tok * dkv + ch);
+        v[j] = ld_bf16x8_once<(ONCE > 1)>(vp + (int64_t)tok * dkv + ch);
       }
     }
 #pragma unroll
@@ -563,12 +566,12 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
           }
           *reinterpret_cast<uint2*>(k_at(tok, ch)) = c;
         } else {
-          st_bf16x8(reinterpret_cast<bf16*>(k_at(tok, ch)), k[j]);
+          st_bf16x8_once<(ONCE > 0)>(reinterpret_cast<bf16*>(k_at(tok, ch)), k[j]);
         }
       }
     }
     __syncthreads();
-    store_v_page<KV8, CH>(tile, v_page, channels, n, kv.v_scale);
+    store_v_page<KV8, CH, (ONCE > 0)>(tile, v_page, channels, n, kv.v_scale);
   } else {
     bf16x8 k[PER];
     uint2 k8[PER];
@@ -577,7 +580,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
       if (i < pieces && tok < n) {
         if constexpr (KV8) k8[j] = *reinterpret_cast<const uint2*>(k_at(tok, ch));
-        else k[j] = ld_bf16x8(reinterpret_cast<const bf16*>(k_at(tok, ch)));
+        else k[j] = ld_bf16x8_once<(ONCE > 1)>(reinterpret_cast<const bf16*>(k_at(tok, ch)));
       }
     }
     if constexpr (KV8) {
@@ -600,7 +603,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       for (int i = threadIdx.x; i < channels; i += 256) {
         const int t0 = (i & 1) * 8, c = i & ~1;
         const bf16* src = reinterpret_cast<const bf16*>(v_page) + c * 16 + t0;
-        const bf16x8 a = ld_bf16x8(src), b = ld_bf16x8(src + 16);
+        const bf16x8 a = ld_bf16x8_once<(ONCE > 1)>(src), b = ld_bf16x8_once<(ONCE > 1)>(src + 16);
 #pragma unroll
         for (int t = 0; t < 8; ++t) *reinterpret_cast<bf16x2*>(&tile[t0 + t][c]) = bf16x2{a[t], b[t]};
       }
@@ -617,8 +620,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
             k[j][4 + e] = (bf16)(e4m3_to_f32((k8[j].y >> (8 * e)) & 255u) * kv.k_scale);
           }
         }
-        st_bf16x8(kp + (int64_t)tok * dkv + ch, k[j]);
-        st_bf16x8(vp + (int64_t)tok * dkv + ch, ld_bf16x8(&tile[tok][ch]));
+        st_bf16x8_once<(ONCE > 0)>(kp + (int64_t)tok * dkv + ch, k[j]);
+        st_bf16x8_once<(ONCE > 0)>(vp + (int64_t)tok * dkv + ch, ld_bf16x8(&tile[tok][ch]));
       }
     }
   }
@@ -709,10 +712,17 @@ hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const Kv
     // of them throughput counts (8 bits, 4096 channels, 21,768 tokens: 142 us with 512 channels, 153 with 128).
     const bool narrow = pages * ((dkv + kPageChannels - 1) / kPageChannels) < 2048;
     const int ch = narrow ? 128 : kPageChannels;
+    const int64_t bytes = 4ll * total_tokens * dkv;  // of the packed keys and values
     const dim3 grid(pages, (dkv + ch - 1) / ch);
-#define TDP_MOVE_(KV8, TO, CH)                                                                                             \
-  kv_move_kernel<KV8, TO, CH><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
+#define TDP_MOVE__(KV8, TO, CH, ONCE)                                                                                            \
+  kv_move_kernel<KV8, TO, CH, ONCE><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
                                                    block_tables, max_pages_per_seq)
+#define TDP_MOVE_(KV8, TO, CH)                                                                                              \
+  do {                                                                                                                      \
+    if (bytes < 16ll << 20) TDP_MOVE__(KV8, TO, CH, 0);                                                                     \
+    else if (bytes < 256ll << 20) TDP_MOVE__(KV8, TO, CH, 1);                                                               \
+    else TDP_MOVE__(KV8, TO, CH, 2);                                                                                        \
+  } while (0)
 #define TDP_MOVE(KV8, TO) do { if (narrow) TDP_MOVE_(KV8, TO, 128); else TDP_MOVE_(KV8, TO, kPageChannels); } while (0)
     if (kv.fp8) {
       if (to_pages) TDP_MOVE(true, true); else TDP_MOVE(true, false);
@@ -721,6 +731,7 @@ hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const Kv
     }
 #undef TDP_MOVE
 #undef TDP_MOVE_
+#undef TDP_MOVE__
     return hipGetLastError();
   }
   kv_copy_kernel<<<total_tokens, 256, 0, s>>>(to_pages, (bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens,

@@ -39,6 +39,18 @@ __device__ __forceinline__ bf16x8 ld_bf16x8_nt(const bf16* p) {
 __device__ __forceinline__ void st_bf16x8(bf16* p, bf16x8 v) {
   *reinterpret_cast<bf16x8*>(p) = v;
 }
+// Loads and stores that are non-temporal where a launch is too large for what it reads or writes to be found in a cache later.
+template <bool NT>
+__device__ __forceinline__ bf16x8 ld_bf16x8_once(const bf16* p) {
+  if constexpr (NT) return ld_bf16x8_nt(p);
+  else return ld_bf16x8(p);
+}
+template <bool NT>
+__device__ __forceinline__ void st_bf16x8_once(bf16* p, bf16x8 v) {
+  typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4_t;
+  if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(p));
+  else st_bf16x8(p, v);
+}
 __device__ __forceinline__ bf16x8 zero_bf16x8() {
   bf16x8 z;
 #pragma unroll
