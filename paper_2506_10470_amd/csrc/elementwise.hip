@@ -919,23 +919,15 @@ __global__ __launch_bounds__(THREADS) void argmax_rows_kernel(const float* __res
                                                               int32_t* __restrict__ out) {
   constexpr int UN = 8, WAVES = THREADS / 64;
   constexpr bool SHORT = THREADS < 1024;
-  __shared__ float s_val[WAVES];
-  __shared__ int s_idx[WAVES];
+  __shared__ Best s_best[WAVES];
   const float* row = logits + (int64_t)blockIdx.x * ld;
   const int tid = threadIdx.x;
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  auto take = [&](float v, int i) {
-    if (v > best || (v == best && i < bi)) {
-      best = v;
-      bi = i;
-    }
-  };
+  Best best = no_best();
   const int head = min(n, (int)((16 - ((uintptr_t)row & 15)) & 15) / 4);
   const int n4 = (n - head) / 4, tail = head + n4 * 4;
   const f32x4* body = reinterpret_cast<const f32x4*>(row + head);
-  if (tid < head) take(row[tid], tid);
-  if (tid < n - tail) take(row[tail + tid], tail + tid);
+  if (tid < head) take_best(best, row[tid], tid);
+  if (tid < n - tail) take_best(best, row[tail + tid], tail + tid);
   for (int j0 = 0; j0 < n4; j0 += THREADS * UN) {
     f32x4 v[UN];
 #pragma unroll
@@ -946,24 +938,56 @@ __global__ __launch_bounds__(THREADS) void argmax_rows_kernel(const float* __res
       if (SHORT && j0 + u * THREADS >= n4) break;
       const int at = head + 4 * min(j0 + u * THREADS + tid, n4 - 1);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) take(v[u][e], at + e);
+      for (int e = 0; e < 4; ++e) take_best(best, v[u][e], at + e);
     }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float v = __shfl_xor(best, o, 64);
-    const int i = __shfl_xor(bi, o, 64);
-    take(v, i);
-  }
-  if ((tid & 63) == 0) {
-    s_val[tid >> 6] = best;
-    s_idx[tid >> 6] = bi;
-  }
+  for (int o = 32; o > 0; o >>= 1) take_best_of_lane(best, o);
+  if ((tid & 63) == 0) s_best[tid >> 6] = best;
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < WAVES; ++w) take(s_val[w], s_idx[w]);
-    out[blockIdx.x] = bi == 0x7fffffff ? 0 : bi;
+    for (int w = 1; w < WAVES; ++w) take_best(best, s_best[w].value, s_best[w].index);
+    out[blockIdx.x] = best.index == kNoIndex ? 0 : best.index;
   }
+}
+
+// The same with the largest element of every piece of `width` columns known (GemmArgs::row_max): a wave per row takes the first of
+// the pieces with the largest one, up to eight per lane in flight, and finds it there.
+__global__ __launch_bounds__(256) void argmax_pieces_kernel(const float* __restrict__ row_max, int count, int width,
+                                                            const float* __restrict__ logits, int64_t ld, int n, int M,
+                                                            int32_t* __restrict__ out) {
+  constexpr int UN = 8;
+  const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (m >= M) return;
+  const float* maxima = row_max + (int64_t)m * count;
+  const float* row = logits + (int64_t)m * ld;
+  Best piece = no_best();
+  for (int i0 = 0; i0 < count; i0 += 64 * UN) {
+    float v[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (i0 + u * 64 < count) v[u] = maxima[min(i0 + u * 64 + lane, count - 1)];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (i0 + u * 64 < count) take_best(piece, v[u], min(i0 + u * 64 + lane, count - 1));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) take_best_of_lane(piece, o);
+  // (a largest element of minus infinity can be that of a piece of NaN: all of the row is looked through)
+  const bool known = piece.value > -INFINITY;
+  const int begin = known ? piece.index * width : 0, end = known ? min(begin + width, n) : n;
+  Best best = no_best();
+  for (int i = begin + lane; i < end; i += 64) take_best(best, row[i], i);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) take_best_of_lane(best, o);
+  if (lane == 0) out[m] = best.index == kNoIndex ? 0 : best.index;
+}
+
+hipError_t launch_argmax_pieces(const float* row_max, int count, int width, const float* logits, int64_t ld, int M, int n,
+                                int32_t* out, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  argmax_pieces_kernel<<<(M + 3) / 4, 256, 0, s>>>(row_max, count, width, logits, ld, n, M, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_argmax_rows(const float* logits, int64_t ld, int M, int n, int32_t* out, hipStream_t s) {

@@ -37,6 +37,7 @@ struct GemmParams {
   OperandLayout a_lay, w_lay, u_lay;
   int64_t Kpad, Npad, ldo, ldr;
   int M, N_store, epilogue, out_f32, res_f32;
+  float* row_max;  // null, or (plain fp32 epilogue, unsplit, no bias) [M][2 tiles_n]
   int k_tiles_total, k_tiles_per_split, splits;
   int k_tiles_per_chunk;  // 0, or (splits = 1, small tiles) the K range is summed in chunks of this many k-tiles
   int tiles_m, tiles_n;
@@ -115,6 +116,34 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmParams& p, f32x4 (&acc
         }
       }
     }
+  }
+}
+
+// The plain fp32 epilogue with the largest element of every row among the wave's 16 WT columns (unsplit, no bias; minus infinity
+// where there is nothing but NaN).  (The barriers keep the row blocks apart: interleaved they spill.)
+template <int AT, int WT>
+__device__ __forceinline__ void gemm_epilogue16_max(const GemmParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
+                                                    int l16, int kq) {
+#pragma unroll
+  for (int at = 0; at < AT; ++at) {
+    const int m = row0 + at * 16 + l16;
+    if (m < p.M) {
+      float* out = (float*)p.out + (int64_t)m * p.ldo;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int wt = 0; wt < WT; ++wt) {
+        const int n = col0 + wt * 16 + kq * 4;
+        if (n < p.N_store) {
+          const f32x4 v = acc[wt][at];
+          *reinterpret_cast<f32x4*>(out + n) = v;
+          mx = fmaxf(fmaxf(mx, fmaxf(v[0], v[1])), fmaxf(v[2], v[3]));
+        }
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      if (kq == 0) p.row_max[(int64_t)m * (2 * p.tiles_n) + col0 / (16 * WT)] = mx;
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -494,7 +523,9 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
   // loads still in flight target LDS only; they must land before the workgroup's LDS is released.
   // The nops cover the MFMA -> accumulator-read distance, which the compiler cannot see.
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  if (p.splits == 1 && p.epilogue == EPI_RESIDUAL && !p.bias && p.N_store >= 4)
+  if (p.row_max)
+    gemm_epilogue16_max<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
+  else if (p.splits == 1 && p.epilogue == EPI_RESIDUAL && !p.bias && p.N_store >= 4)
     gemm_epilogue16_residual<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
   else
     gemm_epilogue16<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq, split);
@@ -768,6 +799,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.out_f32 = a.epilogue == EPI_SWIGLU ? 0 : a.out_f32;
   p.res_f32 = a.residual_f32;
   p.ws = a.workspace;
+  p.row_max = nullptr;
   p.a_lay = a.a_layout;
   p.w_lay = layout_weights(a.Kpad);
   p.u_lay = a.u_layout;
@@ -788,6 +820,11 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.k_tiles_per_split = (p.k_tiles_total + splits - 1) / splits;
   p.splits = splits;
   p.k_tiles_per_chunk = plan.chunk;
+  if (a.row_max_width) *a.row_max_width = 0;
+  if (a.row_max && splits == 1 && a.epilogue == EPI_STORE && a.out_f32 && !a.bias) {
+    p.row_max = a.row_max;
+    *a.row_max_width = ti.bn() / 2;
+  }
   const int bands = (p.tiles_m + 3) / 4;
   p.band_h = p.tiles_m / bands;
   p.n_tall = p.tiles_m % bands;

@@ -124,6 +124,22 @@ __device__ __forceinline__ void e4m3x16_to_bf16x8x2(uint4 raw, bf16x8& first, bf
   second = g.v;
 }
 
+// Greedy choice: the larger value, of equal ones the lower index; a NaN never wins.  The order of comparisons does not matter.
+struct Best {
+  float value;
+  int index;
+};
+constexpr int kNoIndex = 0x7fffffff;  // nothing seen but NaN
+__device__ __forceinline__ Best no_best() { return Best{-INFINITY, kNoIndex}; }
+__device__ __forceinline__ void take_best(Best& b, float v, int i) {
+  if (v > b.value || (v == b.value && i < b.index)) b = Best{v, i};
+}
+__device__ __forceinline__ void take_best_of_lane(Best& b, int lane_xor) {
+  const float v = __shfl_xor(b.value, lane_xor, 64);
+  const int i = __shfl_xor(b.index, lane_xor, 64);
+  take_best(b, v, i);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

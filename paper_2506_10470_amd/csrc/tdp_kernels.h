@@ -69,7 +69,13 @@ struct GemmArgs {
   // reduce kernel; *splits_used (host) receives the number of splits, 1 meaning `out` was written as
   // usual.  The consumer (launch_rmsnorm_sum, launch_rope_kv with partials) sums them.
   int* splits_used;       // null = reduce here
+  // The largest element of pieces of every row on the way (plain fp32 epilogue without a bias): unless the plan splits K,
+  // row_max[m * (Npad / w) + i] receives that of columns [i w, (i + 1) w) and *row_max_width (host) w, which is else 0.
+  // Room for Npad / kRowMaxWidth floats per row.
+  float* row_max;         // null = not wanted
+  int* row_max_width;
 };
+constexpr int kRowMaxWidth = 64;  // the smallest width
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 
 // How a GEMM is made: a pure function of its shape and of what the caller fixes (host only).
@@ -104,6 +110,9 @@ hipError_t launch_gather_rows(const void* src, int64_t ld_src, int64_t n_src_row
 hipError_t launch_to_bf16(const void* src, int src_is_f32, int64_t n, void* dst, hipStream_t s);
 // out[m] = lowest index among the maxima of logits[m][0..n)
 hipError_t launch_argmax_rows(const float* logits, int64_t ld, int M, int n, int32_t* out, hipStream_t s);
+// The same where the largest elements of the pieces [i width, (i + 1) width) are known: row_max[m * count + i]
+hipError_t launch_argmax_pieces(const float* row_max, int count, int width, const float* logits, int64_t ld, int M, int n,
+                                int32_t* out, hipStream_t s);
 
 // ---- RMSNorm ---------------------------------------------------------------------------------
 hipError_t launch_rmsnorm(const void* x, int x_is_f32, int64_t ldx, const float* gain, float eps, int M, int d,

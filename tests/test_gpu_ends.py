@@ -203,3 +203,27 @@ def test_lm_head_at_llama_size_sampled():
         assert row_rel_err(logits[torch.from_numpy(rows).cuda().long()].cpu().numpy(), ref) <= LOGIT_TOL
         check_tokens(toks.cpu().numpy()[rows], ref)
         assert np.array_equal(toks.cpu().numpy()[:64], E.greedy_tokens(logits[:64].cpu().numpy().astype(np.float64)))
+
+
+@pytest.mark.parametrize("vocab", [19996, 20000, 32000])     # rows below and from 20000 columns on, a whole number of tiles and not
+@pytest.mark.parametrize("M", [1, 33, 200, 512])             # tiles of 32 to 256 rows, the last one partly filled
+def test_greedy_tokens_of_the_head_are_those_of_its_logits(M, vocab):
+    """Few distinct columns in random places: every row's largest logit lies in many pieces of the row at once.  Rows that hold a
+    NaN give only NaN, rows of zeros only ties."""
+    d = 64
+    g = torch.Generator(device="cuda").manual_seed(M + vocab)
+    which = torch.randint(0, 40, (vocab,), generator=g, device="cuda")
+    head = torch.randn(d, 40, generator=g, device="cuda").to(torch.bfloat16)[:, which].contiguous()
+    x = torch.randn(M, d, generator=g, device="cuda").to(torch.bfloat16)
+    x[M // 2, 5] = float("nan")
+    x[M // 3] = 0
+    h = tdp.tdp_ends_create(tdp.EndsConfig(vocab, d, 1e-5, M))
+    tdp.tdp_ends_set_weight(h, tdp.E_LM_HEAD, head, tdp.BF16, tdp.DEVICE, d, vocab)
+    tdp.tdp_ends_set_weight(h, tdp.E_FINAL_NORM, torch.ones(d, device="cuda"), tdp.F32, tdp.DEVICE, d, 1)
+    logits = torch.empty((M, vocab), dtype=torch.float32, device="cuda")
+    toks = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+    tdp.tdp_lm_head(h, x, M, None, M, logits, toks)
+    torch.cuda.synchronize()
+    tdp.tdp_ends_destroy(h)
+    lg = logits.cpu().numpy().astype(np.float64)
+    assert np.array_equal(toks.cpu().numpy(), E.greedy_tokens(np.where(np.isnan(lg), -np.inf, lg)))
