@@ -133,13 +133,18 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(const int32_t* __restric
   }
 }
 
+// ROTATE: the workgroup makes its queries itself, and that of a request's last span appends the new token's key and value, both from
+// the fp32 projection (its finished output, or its split-K partials, summed in split order, plus the bias), rounded once, as
+// rope_kv_kernel does; see attn_decode_rotates for when.  Three waves rotate the queries into LDS, a thread four pairs of
+// channels, while the fourth appends: the one that reads the new token's page, later in its range and behind its own stores.
+//
 // KV8 = the pools hold E4M3 codes (one byte per element) instead of bf16.  A 16-byte load then carries
 // 16 elements, which become two MFMA operands after conversion, so the block grows to 64 tokens
 // (four pages) and the assignment of MFMA k-indices to channels (scores) and of score rows to
 // tokens changes with it; the arithmetic after the conversion is the bf16 kernel's.  The cache
 // scales ride along for free: k_scale in the softmax scale, v_scale in the final division.
-template <int DH, bool KV8>
-__global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restrict__ qkv, int64_t ld,
+template <int DH, bool KV8, bool ROTATE>
+__global__ __launch_bounds__(256, 3) void attn_decode_kernel(const DecodeQueries dq, int batch,
                                                           int n_q_heads, KvLayout kv,
                                                           const int4* __restrict__ items,
                                                           const int32_t* __restrict__ item_pages, int item_pitch,
@@ -159,7 +164,8 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   // the two look-ups a workgroup starts with are independent of each other: its work record and
   // its span's page list (lane j holds pages j, 64 + j, ...; at most 256 pages per span)
   const int pages_per_span = span_len >> 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = ROTATE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   int my_pages[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   const int4 it = items ? items[item] : make_int4(item, 0, decode_position(ctx_lens[item], item_pitch) + 1, 0);
   if (it.x < 0) return;
   const int b = it.x, span = it.y;
-  const int n_total = it.z;  // ctx + 1: the new token's K/V were appended before this kernel
+  const int n_total = it.z;  // ctx + 1: with the new token
   const int last_entry = items ? pages_per_span - 1 : (n_total - 1) >> 4;
   const int s_begin = span * span_len;
   const int s_end = min(s_begin + span_len, n_total);
@@ -184,12 +190,138 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(const bf16* __restr
   const int t_begin = s_begin + BT * ((wave * n_blocks) >> 2);
   const int t_end = min(s_begin + BT * (((wave + 1) * n_blocks) >> 2), s_end);
 
+  __shared__ __attribute__((aligned(16))) bf16 s_q[ROTATE ? 16 : 1][DH + 8];
+  if constexpr (ROTATE) {
+    auto page_of = [&](int i) {  // i is wave-uniform
+      const int r = i >> 6;
+      return __builtin_amdgcn_readlane(r == 0 ? my_pages[0] : r == 1 ? my_pages[1] : r == 2 ? my_pages[2] : my_pages[3], i & 63);
+    };
+    constexpr int KU = DH / 8, VU = DH / 4, ZN = 8;  // units of a head: four pairs, four values; splits asked for at once
+    static_assert(KU + VU <= 64, "one wave appends");
+    const bool owner = s_end == n_total;  // of the new token
+    // a unit's columns of the projection: four pairs (col0 + i, col1 + i) of the channels c0 + i, c0 + i + DH / 2 of a head, or four
+    // values col0 + i
+    struct Unit {
+      int c0, col0, col1;
+      f32x4 part[ZN][2], bias[2];
+      float4 cs[2];
+    } unit;
+    const float* const row = dq.proj + (int64_t)b * dq.ld;
+    const int64_t split_stride = (int64_t)batch * dq.ld;
+    const int pos = n_total - 1;
+    auto fetch = [&](int head, int index, int distance) {
+      unit.c0 = index * 4;
+      unit.col0 = head * DH + unit.c0;
+      unit.col1 = unit.col0 + distance;
+  #pragma unroll
+      for (int z = 0; z < ZN; ++z) {
+        if (z < dq.splits) {
+          unit.part[z][0] = *reinterpret_cast<const f32x4*>(row + z * split_stride + unit.col0);
+          unit.part[z][1] = *reinterpret_cast<const f32x4*>(row + z * split_stride + unit.col1);
+        } else {
+          unit.part[z][0] = unit.part[z][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+      const float4* cs = reinterpret_cast<const float4*>(dq.rope_table + (int64_t)pos * (DH / 2) + unit.c0 % (DH / 2));
+      unit.cs[0] = cs[0];
+      unit.cs[1] = cs[1];
+      if (dq.bias) {
+        unit.bias[0] = *reinterpret_cast<const f32x4*>(dq.bias + unit.col0);
+        unit.bias[1] = *reinterpret_cast<const f32x4*>(dq.bias + unit.col1);
+      }
+    };
+    auto sums = [&](f32x4 (&f)[2]) {
+      f[0] = f[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  #pragma unroll
+      for (int z = 0; z < ZN; ++z)
+  #pragma unroll
+        for (int c = 0; c < 2; ++c) f[c] += unit.part[z][c];
+      for (int z = ZN; z < dq.splits; ++z) {
+        f[0] += *reinterpret_cast<const f32x4*>(row + z * split_stride + unit.col0);
+        f[1] += *reinterpret_cast<const f32x4*>(row + z * split_stride + unit.col1);
+      }
+      if (dq.bias) {
+        f[0] += unit.bias[0];
+        f[1] += unit.bias[1];
+      }
+    };
+    auto rotated = [&](float (&lo)[4], float (&hi)[4]) {
+      f32x4 ab[2];
+      sums(ab);
+      const float2 t2[4] = {{unit.cs[0].x, unit.cs[0].y}, {unit.cs[0].z, unit.cs[0].w},
+                            {unit.cs[1].x, unit.cs[1].y}, {unit.cs[1].z, unit.cs[1].w}};
+  #pragma unroll
+      for (int i = 0; i < 4; ++i) rotate_pair(ab[0][i], ab[1][i], t2[i], unit.c0 + i, lo[i], hi[i]);
+    };
+    auto four = [](const float (&f)[4]) {
+      bf16x4 r;
+  #pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = (bf16)f[i];
+      return r;
+    };
+    auto codes4 = [](const float (&f)[4], float scale) -> uint32_t {
+      uint32_t c = 0u;
+  #pragma unroll
+      for (int i = 0; i < 4; ++i) c |= f32_to_e4m3(f[i] / scale) << (8 * i);
+      return c;
+    };
+    if (wave < 3) {
+      if ((int)threadIdx.x < G * KU) fetch(kvh * G + threadIdx.x / KU, threadIdx.x % KU, DH / 2);
+    } else if (owner) {
+      if (lane < KU) fetch(n_q_heads + kvh, lane, DH / 2);
+      else if (lane < KU + VU) fetch(n_q_heads + Hkv + kvh, lane - KU, 0);
+    }
+
+    if (wave < 3) {
+      for (int i = threadIdx.x; i < G * KU; i += 192) {
+        if (i != (int)threadIdx.x) fetch(kvh * G + i / KU, i % KU, DH / 2);  // (more than twelve heads)
+        float lo[4], hi[4];
+        rotated(lo, hi);
+        *reinterpret_cast<bf16x4*>(&s_q[i / KU][unit.c0]) = four(lo);
+        *reinterpret_cast<bf16x4*>(&s_q[i / KU][DH / 2 + unit.c0]) = four(hi);
+      }
+    } else if (owner) {
+      const int64_t page = page_of((pos >> 4) - (s_begin >> 4));
+      const int slot = pos & 15;
+      if (lane < KU) {
+        float lo[4], hi[4];
+        rotated(lo, hi);
+        constexpr int ESZ = KV8 ? 1 : 2;
+        uint8_t* k_lo = (uint8_t*)kv.k_pool + k_pool_byte(kv, page, kvh, slot, unit.c0 * ESZ);
+        uint8_t* k_hi = (uint8_t*)kv.k_pool + k_pool_byte(kv, page, kvh, slot, (DH / 2 + unit.c0) * ESZ);
+        if constexpr (KV8) {  // from fp32 straight to the code: one rounding
+          *reinterpret_cast<uint32_t*>(k_lo) = codes4(lo, kv.k_scale);
+          *reinterpret_cast<uint32_t*>(k_hi) = codes4(hi, kv.k_scale);
+        } else {
+          *reinterpret_cast<bf16x4*>(k_lo) = four(lo);
+          *reinterpret_cast<bf16x4*>(k_hi) = four(hi);
+        }
+      } else if (lane < KU + VU) {
+        f32x4 f[2];
+        sums(f);
+        const int64_t at = ((page * Hkv + kvh) * DH + unit.c0) * 16 + slot;  // [page][kv head][channel][16 slots]
+  #pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          // the value is a bf16 quantity in both forms of the cache (the 8-bit code is taken from it)
+          const bf16 x = (bf16)f[0][i];
+          if constexpr (KV8)
+            ((uint8_t*)kv.v_pool)[at + i * 16] = (uint8_t)f32_to_e4m3((float)x / kv.v_scale);
+          else
+            ((bf16*)kv.v_pool)[at + i * 16] = x;
+        }
+      }
+      // (read back by other lanes of this wave, whose memory operations are carried out in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+  }
+
   // Query fragments.  bf16 pools: k-step kk covers channels kk*32 + kg*8 .. +8.  8-bit pools: a
   // lane's 16-byte key load covers channels ld*64 + kg*16 .. +16, whose halves feed k-steps 2 ld and
   // 2 ld + 1, so the query is gathered in that order.
   bf16x8 qf[KS];
   {
-    const bf16* qp = qkv + (int64_t)b * ld + (int64_t)(kvh * G + (r16 < G ? r16 : 0)) * DH;
+    const bf16* qp = ROTATE ? &s_q[r16][0] : (const bf16*)dq.qkv + (int64_t)b * dq.ld + (int64_t)(kvh * G + (r16 < G ? r16 : 0)) * DH;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       const int ch = KV8 ? (kk >> 1) * 64 + kg * 16 + (kk & 1) * 8 : kk * 32 + kg * 8;
@@ -576,6 +708,14 @@ bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len)
   return attn_decode_items(batch, max_spans, span_len) > batch || batch * n_kv_heads > 3 * 256;
 }
 
+// Whether the attention kernel rotates the queries and appends the new keys and values itself.  A kernel in front of it is a launch in
+// every layer, 4 to 8 us for small batches.  As long as all (request, K/V head) pairs run at once (three workgroups per CU) the
+// rotation is ahead inside, two layers, us: 70B, 8 / 16 / 64 requests 612 / 632 / 783 with the kernel in front, 594 / 621 / 766 inside; 7B,
+// 2 / 16 requests 231 / 282 and 217 / 267; Qwen, 48 492 and 474; toy widths, 4 / 256 requests 68.5 / 75 and 67 / 70.6.  Around 800 to 1000
+// pairs the two are level, and beyond that every value stored among the reads costs more than it does in front of them: 13B, 5120
+// pairs, 1215 and 1285 (without the stores of the values 1207).
+bool attn_decode_rotates(int batch, int n_kv_heads) { return batch * n_kv_heads <= 3 * 256; }
+
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
                             int max_spans, int span_len, int4* items, int32_t* item_pages, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
@@ -585,7 +725,7 @@ hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables
   return hipGetLastError();
 }
 
-hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_heads, const KvLayout& kv,
+hipError_t launch_attn_decode(const DecodeQueries& dq, int batch, int n_q_heads, const KvLayout& kv,
                               const int4* items, const int32_t* item_pages, int item_pitch, const int32_t* ctx_lens,
                               float* part_o, float* part_ml, unsigned* spans_done, int max_spans, int span_len,
                               void* out, OperandLayout out_layout, hipStream_t s) {
@@ -595,16 +735,17 @@ hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_he
   const float out_scale = kv.fp8 ? kv.v_scale : 1.0f;
   const int max_items = attn_decode_items(batch, max_spans, span_len);
   const unsigned grid = (unsigned)max_items * kv.n_kv_heads;
-#define TDP_DECODE(DH, KV8)                                                                                        \
-  attn_decode_kernel<DH, KV8><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, n_q_heads, kv, items, item_pages,         \
-                                                   item_pitch, ctx_lens, part_o, part_ml, spans_done, max_spans, \
-                                                   span_len, (bf16*)out,                                         \
-                                                   out_layout, scale_log2, out_scale)
+#define TDP_DECODE_(DH, KV8, ROTATE)                                                                                   \
+  attn_decode_kernel<DH, KV8, ROTATE><<<grid, 256, 0, s>>>(dq, batch, n_q_heads, kv, items, item_pages, item_pitch, ctx_lens, \
+                                                           part_o, part_ml, spans_done, max_spans, span_len, (bf16*)out, \
+                                                           out_layout, scale_log2, out_scale)
+#define TDP_DECODE(DH, KV8) do { if (dq.qkv) TDP_DECODE_(DH, KV8, false); else TDP_DECODE_(DH, KV8, true); } while (0)
   if (kv.head_dim == 128) {
     if (kv.fp8) TDP_DECODE(128, true); else TDP_DECODE(128, false);
   } else {
     if (kv.fp8) TDP_DECODE(64, true); else TDP_DECODE(64, false);
   }
+#undef TDP_DECODE_
 #undef TDP_DECODE
   return hipGetLastError();
 }

@@ -248,6 +248,8 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 // i + head_dim/2 and turns the pair by pos * base^(-2i/head_dim); the table holds (cos, sin) of that
 // angle, computed in double precision on the host.
 //
+// (Small decode batches do this inside the attention kernel, see attn_decode_rotates.)
+//
 // A unit is eight rotated pairs or eight values; a token's units are walked by gridDim.y workgroups of 256 threads.
 // Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In decode, and in prefill
 // where there are partials to sum, every unit has a thread of its own, which asks for the partials of UN splits at
@@ -304,16 +306,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, in
       const float(&a)[8] = ab[0];
       const float(&b)[8] = ab[1];
       float fra[8], frb[8];
-      // (Which product of the second half is fused has no meaning of its own: written out, it is the choice that the compiler
-      // once made in each of the eight places, and keeps queries and keys to the bit.  Either form rounds the other product
-      // once in fp32, 2^-16 of the bf16 or 8-bit rounding behind it.)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float2 t2 = cs[c0 + i];
-        fra[i] = __builtin_fmaf(a[i], t2.x, -(b[i] * t2.y));
-        frb[i] = i == 1 || i == 3 || i == 5 ? __builtin_fmaf(a[i], t2.y, b[i] * t2.x)
-                                            : __builtin_fmaf(b[i], t2.x, a[i] * t2.y);
-      }
+      for (int i = 0; i < 8; ++i) rotate_pair(a[i], b[i], cs[c0 + i], i, fra[i], frb[i]);
       // byte offsets of this thread's two 8-channel pieces in the K pool (a piece never straddles a 64-byte cut)
       const int esz = kv.fp8 ? 1 : 2;
       const int64_t k_lo = head >= n_q_heads ? k_pool_byte(kv, page, head - n_q_heads, slot, c0 * esz) : 0;

@@ -217,19 +217,22 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
       HIP_TRY(launch_gemm(g, s));
       g.splits_used = nullptr;
     }
-    {  // a3: rotary embedding + KV append, from the fp32 projection (if it was split: sums the partials and
-       // adds the bias, which the GEMM's epilogue has done otherwise)
+    // a3: rotary embedding + KV append, from the fp32 projection (if it was split: sums the partials and adds the bias, which the
+    // GEMM's epilogue has done otherwise); in small decode batches inside the attention kernel
+    const bool split = qkv_splits > 1, rotates = ctx_lens && attn_decode_rotates(M, c.n_kv_heads);
+    const DecodeQueries dq{rotates ? nullptr : sc.qkv, st->Nqkv_pad, split ? sc.ws : sc.qkv32, split ? g.bias : nullptr, st->rope_table,
+                           qkv_splits};
+    if (!rotates) {
       Timer t(st, s, timed, T_ROPE);
-      const bool split = qkv_splits > 1;
       HIP_TRY(launch_rope_kv(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, st->rope_table, st->max_pos, ctx_lens,
-                             cu_seqlens, n_seqs, block_tables, c.max_pages_per_seq, split ? sc.ws : sc.qkv32,
-                             qkv_splits, split ? g.bias : nullptr, s));
-      g.bias = nullptr;
+                             cu_seqlens, n_seqs, block_tables, c.max_pages_per_seq, dq.proj, qkv_splits,
+                             dq.bias, s));
     }
+    g.bias = nullptr;
     {  // a4: attention
       Timer t(st, s, timed, T_ATTN);
       if (ctx_lens)
-        HIP_TRY(launch_attn_decode(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, planned ? sc.attn_items : nullptr,
+        HIP_TRY(launch_attn_decode(dq, M, c.n_q_heads, kv, planned ? sc.attn_items : nullptr,
                                    planned ? sc.attn_item_pages : block_tables,
                                    planned ? span_len / 16 : c.max_pages_per_seq, ctx_lens,
                                    sc.part_o, sc.part_ml, count_spans ? sc.spans_done : nullptr, st->max_chunks, span_len,

@@ -78,6 +78,16 @@ __device__ __forceinline__ int64_t operand_row_offset(const L& lay, int r) {
   return (int64_t)(r >> lay.shift) * lay.group + (int64_t)(r & ((1 << lay.shift) - 1)) * lay.par;
 }
 
+// One rotated pair: channels i and i + head_dim / 2 turned by the angle whose (cos, sin) is cs.  Which product of the second is
+// fused has no meaning of its own: written out, it is the choice that a compiler once made for each i % 8, and keeps queries
+// and keys to the bit wherever they are rotated.  Either form rounds the other product once in fp32, 2^-16 of the bf16 or 8-bit
+// rounding behind it.
+__device__ __forceinline__ void rotate_pair(float a, float b, float2 cs, int i, float& ra, float& rb) {
+  const int i8 = i & 7;
+  ra = __builtin_fmaf(a, cs.x, -(b * cs.y));
+  rb = i8 == 1 || i8 == 3 || i8 == 5 ? __builtin_fmaf(a, cs.y, b * cs.x) : __builtin_fmaf(b, cs.x, a * cs.y);
+}
+
 // ---- 8-bit KV cache: OCP E4M3 (sign, 4 exponent bits with bias 7, 3 mantissa bits; exponent field
 // 0 is subnormal, no infinities, S.1111.111 is NaN, largest finite magnitude 448) -------------------
 // fp32 -> code: round to nearest, ties to the even code; magnitudes from 448 up (infinity included)

@@ -179,9 +179,20 @@ hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables
 // launch_attn_decode_merge does so behind it (attn_decode_counts_spans says which way to take).
 // With a work list: items and item_pages as launch_attn_plan left them, item_pitch = span_len / 16.  Without one
 // (attn_decode_planned is false): items null, item_pages = the block tables, item_pitch = max_pages_per_seq.
+// Where the queries come from: the rotated bf16 rows that launch_rope_kv leaves, or (qkv null) the projection, from which the kernel then
+// rotates them and appends the new tokens' keys and values itself (attn_decode_rotates).
+struct DecodeQueries {
+  const void* qkv;
+  int64_t ld;                // of the bf16 rows and of the projection
+  const float* proj;         // fp32 [split][batch][ld]: the split-K partials, or (splits = 1) the finished output
+  const float* bias;         // added to the sums, or null
+  const float2* rope_table;  // (cos, sin) of [position][head_dim / 2]
+  int splits;
+};
+bool attn_decode_rotates(int batch, int n_kv_heads);
 bool attn_decode_counts_spans(int batch, int n_q_heads, int n_kv_heads, int max_spans, int span_len);
 bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len);
-hipError_t launch_attn_decode(const void* qkv, int64_t ld, int batch, int n_q_heads, const KvLayout& kv,
+hipError_t launch_attn_decode(const DecodeQueries& dq, int batch, int n_q_heads, const KvLayout& kv,
                               const int4* items, const int32_t* item_pages, int item_pitch, const int32_t* ctx_lens,
                               float* part_o, float* part_ml, unsigned* spans_done, int max_spans, int span_len,
                               void* out, OperandLayout out_layout, hipStream_t s);
