@@ -852,26 +852,53 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
   const bf16* k_frag = &sK[0][0][0] + krow * DH;
   const int k_swz = (krow / RWK) % CR;
 
-  // staging: this thread's chunks of K and of V^T of the next 64-token block (two 32-token halves)
-  bf16x8 kreg[NCH], vreg[NCH];
-  auto load_block = [&](int kb) {
-    const int p0 = kb >> 4;
-    int64_t page[4];  // never dereference a table entry past the last page
+  // Staging of the next 64-token block (two 32-token halves).  The pages of a block are looked up a block before its keys and values
+  // are requested.  16-bit pools go straight into LDS, an instruction 1 KiB of it, each lane from where the swizzle wants its 16
+  // bytes to come: wave w takes the keys of the block's page w, and half of the channels of the values of a half; 8-bit pools go
+  // through registers for the conversion.  What that leaves of the registers holds all fragments of a half at once.  (Everything
+  // through registers, look-ups and loads in one go, values past the prompt masked on the way, fragments read two by two: 16.0 us
+  // for one prompt of 307 tokens of 32 heads, now 12.9; 6713 tokens of 40 / 8 heads 210 -> 183; 19346 of 64 / 8 944 -> 834; 8 bits, 12
+  // prompts of a 13B shape, where the look-ups and the fragments alone count, 139 -> 115.  Both halves' scores in front of one
+  // softmax over 64 tokens: level.)
+  int page[4];
+  auto look_up = [&](int kb) {  // never dereference a table entry past the last page
 #pragma unroll
-    for (int i = 0; i < 4; ++i) page[i] = bt[min(p0 + i, last_page)];
+    for (int i = 0; i < 4; ++i) page[i] = bt[min((kb >> 4) + i, last_page)];
+  };
+  bf16x8 kreg[KV8 ? NCH : 1], vreg[KV8 ? NCH : 1];
+  const int w = __builtin_amdgcn_readfirstlane(wave);
+  const unsigned k_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&sK[0][0][0];
+  const unsigned v_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&sV[0][0][0];
+  constexpr int HEAD = 16 * DH;         // elements of a page, one K/V head
+  constexpr int TPI = 512 / DH;         // key rows (tokens) of an instruction
+  static_assert(KV8 || (NW == 4 && NCH * TPI == 16), "a wave's instructions make one page of keys");
+  // this lane's element offsets into its page of K (instruction j), and into its page of V (instruction 0; 16 channels further on in each)
+  int k_off[KV8 ? 1 : NCH];
+  const int v_row = lane >> 2, v_chunk = (lane & 3) ^ ((v_row >> 2) & 3);
+  const int v_off = ((w & 1) * (DH / 2) + v_row) * 16 + (v_chunk & 1) * 8;
+  if constexpr (!KV8) {
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      const int ci = tid + NT * j;
-      // K: consecutive threads walk the pool in address order - the QP chunks of a 64-byte piece, the 16
-      // tokens of the page, the pieces of the row, the four pages of the block
-      const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
-      const int64_t kp = page[kpg];
-      const int vsub = ci / (DH * 4), vr = (ci >> 2) % DH, vc = ci & 3;
-      const int64_t vp = vsub ? (vc < 2 ? page[2] : page[3]) : (vc < 2 ? page[0] : page[1]);
-      const int64_t k_at = (kp * Hkv + kvh) * (16 * DH) + (kpiece * 16 + kt16) * (QP * 8) + kq * 8;
-      const int64_t v_at = ((vp * Hkv + kvh) * DH + vr) * 16 + (vc & 1) * 8;
-      bf16x8 v;
-      if constexpr (KV8) {
+      const int slot = j * TPI + lane / CR, ktok = (w & 1) * 16 + slot, kc = (lane % CR) ^ ((ktok / RWK) % CR);
+      k_off[j] = (kc / QP) * 512 + slot * 32 + kc % QP * 8;
+    }
+  }
+  auto request = [&](unsigned lds_addr, const bf16* from) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(from) : "memory");
+  };
+  auto load_block = [&](int buf) {
+    if constexpr (KV8) {
+#pragma unroll
+      for (int j = 0; j < NCH; ++j) {
+        const int ci = tid + NT * j;
+        // K: consecutive threads walk the pool in address order - the QP chunks of a 64-byte piece, the 16
+        // tokens of the page, the pieces of the row, the four pages of the block
+        const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
+        const int64_t kp = kpg == 0 ? page[0] : kpg == 1 ? page[1] : kpg == 2 ? page[2] : page[3];
+        const int vsub = ci / (DH * 4), vr = (ci >> 2) % DH, vc = ci & 3;
+        const int64_t vp = vsub ? (vc < 2 ? page[2] : page[3]) : (vc < 2 ? page[0] : page[1]);
+        const int64_t k_at = (kp * Hkv + kvh) * HEAD + (kpiece * 16 + kt16) * (QP * 8) + kq * 8;
+        const int64_t v_at = ((vp * Hkv + kvh) * DH + vr) * 16 + (vc & 1) * 8;
         union {
           uint32_t u[4];
           bf16x8 x;
@@ -883,37 +910,60 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         e4m3x4_to_bf16x4(rv.x, cv.u[0], cv.u[1]);
         e4m3x4_to_bf16x4(rv.y, cv.u[2], cv.u[3]);
         kreg[j] = ck.x;
-        v = cv.x;
-      } else {
-        kreg[j] = ld_bf16x8(kpool + k_at);
-        v = ld_bf16x8(vpool + v_at);
+        vreg[j] = cv.x;
       }
-      if (kb + 64 > L) {  // slots past the prompt may hold anything, even NaN
+    } else {
+      const int64_t k_page = w == 0 ? page[0] : w == 1 ? page[1] : w == 2 ? page[2] : page[3];
+      const int64_t v_page = w < 2 ? (v_chunk < 2 ? page[0] : page[1]) : (v_chunk < 2 ? page[2] : page[3]);
+      const bf16* kp = kpool + (k_page * Hkv + kvh) * HEAD;
+      const bf16* vp = vpool + (v_page * Hkv + kvh) * HEAD + v_off;
+      const unsigned half = buf * (64 * DH * 2) + w * (NCH * 1024);
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (kb + vsub * 32 + vc * 8 + e >= L) v[e] = (bf16)0.0f;
-      }
-      vreg[j] = v;
+      for (int j = 0; j < NCH; ++j) request(k_lds + half + j * 1024, kp + k_off[j]);
+#pragma unroll
+      for (int j = 0; j < NCH; ++j) request(v_lds + half + j * 1024, vp + j * 256);
     }
   };
-  auto store_block = [&](int buf) {
+  // the block kb has arrived in buffer buf for all waves
+  auto settle = [&](int kb, int buf) {
+    if constexpr (KV8) {
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      const int ci = tid + NT * j;
-      const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
-      const int ksub = kpg >> 1, ktok = (kpg & 1) * 16 + kt16, kc = kpiece * QP + kq;
-      st_bf16x8(&sK[buf][ksub][ktok * DH + ((kc ^ ((ktok / RWK) % CR)) << 3)], kreg[j]);
-      const int vsub = ci / (DH * 4), vr = (ci >> 2) % DH, vc = ci & 3;
-      st_bf16x8(&sV[buf][vsub][vr * 32 + ((vc ^ ((vr >> 2) & 3)) << 3)], vreg[j]);
+      for (int j = 0; j < NCH; ++j) {
+        const int ci = tid + NT * j;
+        const int kq = ci % QP, kt16 = (ci / QP) % 16, kpiece = (ci / (QP * 16)) % (CR / QP), kpg = ci / (16 * CR);
+        const int ksub = kpg >> 1, ktok = (kpg & 1) * 16 + kt16, kc = kpiece * QP + kq;
+        st_bf16x8(&sK[buf][ksub][ktok * DH + ((kc ^ ((ktok / RWK) % CR)) << 3)], kreg[j]);
+        const int vsub = ci / (DH * 4), vr = (ci >> 2) % DH, vc = ci & 3;
+        st_bf16x8(&sV[buf][vsub][vr * 32 + ((vc ^ ((vr >> 2) & 3)) << 3)], vreg[j]);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (kb + 64 > L) {  // slots past the prompt may hold anything, even NaN
+#pragma unroll
+      for (int j = 0; j < NCH; ++j) {
+        const int ci = tid + NT * j, vsub = ci / (DH * 4), vr = (ci >> 2) % DH, vc = ci & 3;
+        const int keep = L - (kb + vsub * 32 + vc * 8);
+        if (keep < 8) {
+          bf16* at = &sV[buf][vsub][vr * 32 + ((vc ^ ((vr >> 2) & 3)) << 3)];
+          bf16x8 v = ld_bf16x8(at);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (e >= keep) v[e] = (bf16)0.0f;
+          st_bf16x8(at, v);
+        }
+      }
+      __syncthreads();
     }
   };
 
+  look_up(0);
   load_block(0);
-  store_block(0);
-  __syncthreads();
+  look_up(64);
+  settle(0, 0);
   for (int kb0 = 0, buf = 0; kb0 < kv_end; kb0 += 64, buf ^= 1) {
     const bool more = kb0 + 64 < kv_end;
-    if (more) load_block(kb0 + 64);
+    if (more) load_block(buf ^ 1);
+    look_up(kb0 + 128);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
       const int kb = kb0 + sub * 32;
@@ -922,9 +972,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
       f32x16 sc;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+      bf16x8 kf[KS];  // all of the block's fragments first: one LDS round trip and not one per pair of MFMAs
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-        sc = mfma32(ld_bf16x8(k_frag + (buf * 2 + sub) * 32 * DH + (((kk * 2 + kg) ^ k_swz) << 3)), qf[kk], sc);
+      for (int kk = 0; kk < KS; ++kk) kf[kk] = ld_bf16x8(k_frag + (buf * 2 + sub) * 32 * DH + (((kk * 2 + kg) ^ k_swz) << 3));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) sc = mfma32(kf[kk], qf[kk], sc);
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 vf[DT][2];  // on their way during the softmax
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+          const int r = d * 32 + l32;
+          vf[d][st] = ld_bf16x8(&sV[buf][sub][r * 32 + (((st * 2 + kg) ^ ((r >> 2) & 3)) << 3)]);
+        }
+      __builtin_amdgcn_sched_barrier(0);
       // element i of this lane is token kb + (i/8)*16 + kg*8 + i%8 of query column qpos
       if (kb + 31 > p_first || kb + 32 > L) {  // the block crosses the diagonal or the prompt's end
 #pragma unroll
@@ -957,15 +1020,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
       }
       lsum += psum;
 #pragma unroll
-      for (int d = 0; d < DT; ++d) {
-        const int r = d * 32 + l32;
+      for (int d = 0; d < DT; ++d)
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
-          o[d] = mfma32(ld_bf16x8(&sV[buf][sub][r * 32 + (((st * 2 + kg) ^ ((r >> 2) & 3)) << 3)]), pb[st], o[d]);
-      }
+        for (int st = 0; st < 2; ++st) o[d] = mfma32(vf[d][st], pb[st], o[d]);
     }
-    if (more) store_block(buf ^ 1);
-    __syncthreads();
+    if (more) settle(kb0 + 64, buf ^ 1);
   }
   lsum += __shfl_xor(lsum, 32, 64);
   if (real && qpos < L) {
