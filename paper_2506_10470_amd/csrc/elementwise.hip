@@ -248,7 +248,8 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 // i + head_dim/2 and turns the pair by pos * base^(-2i/head_dim); the table holds (cos, sin) of that
 // angle, computed in double precision on the host.
 //
-// (Small decode batches do this inside the attention kernel, see attn_decode_rotates.)
+// (Small decode batches do this inside the attention kernel, see attn_decode_rotates, an unsplit projection of a prefill in its
+// epilogue, see gemm_can_rotate.)
 //
 // A unit is eight rotated pairs or eight values; a token's units are walked by gridDim.y workgroups of 256 threads.
 // Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In decode, and in prefill
@@ -474,6 +475,37 @@ __global__ __launch_bounds__(256) void v_append_pages_kernel(const bf16* __restr
   store_v_page<KV8, CH, false>(tile, (uint8_t*)kv.v_pool + (page * dkv + c0) * (KV8 ? 16 : 32), channels, n, kv.v_scale);
 }
 
+__global__ __launch_bounds__(256) void token_pages_kernel(const int32_t* __restrict__ cu_seqlens, int n_seqs, int n_tokens,
+                                                          const int32_t* __restrict__ block_tables, int max_pages_per_seq,
+                                                          int2* __restrict__ token_pages) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= n_tokens) return;
+  int seq, pos;
+  locate_token(t, nullptr, cu_seqlens, n_seqs, max_pages_per_seq, seq, pos);
+  token_pages[t] = make_int2(pos, block_tables[(int64_t)seq * max_pages_per_seq + pos / 16]);
+}
+
+hipError_t launch_token_pages(const int32_t* cu_seqlens, int n_seqs, int n_tokens, const int32_t* block_tables, int max_pages_per_seq,
+                              int2* token_pages, hipStream_t s) {
+  if (n_tokens <= 0) return hipSuccess;
+  token_pages_kernel<<<(n_tokens + 255) / 256, 256, 0, s>>>(cu_seqlens, n_seqs, n_tokens, block_tables, max_pages_per_seq, token_pages);
+  return hipGetLastError();
+}
+
+hipError_t launch_v_append(const void* qkv, int64_t ld, int n_tokens, int n_q_heads, const KvLayout& kv, const int32_t* cu_seqlens,
+                           int n_seqs, const int32_t* block_tables, int max_pages_per_seq, hipStream_t s) {
+  if (n_tokens <= 0) return hipSuccess;
+  const int dkv = kv.n_kv_heads * kv.head_dim, v_col = n_q_heads * kv.head_dim + dkv;
+  const dim3 grid((n_tokens >> 4) + n_seqs + 1, (dkv + kPageChannels - 1) / kPageChannels);
+  if (kv.fp8)
+    v_append_pages_kernel<true><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, v_col, kv, cu_seqlens, n_seqs, n_tokens, block_tables,
+                                                     max_pages_per_seq);
+  else
+    v_append_pages_kernel<false><<<grid, 256, 0, s>>>((const bf16*)qkv, ld, v_col, kv, cu_seqlens, n_seqs, n_tokens, block_tables,
+                                                      max_pages_per_seq);
+  return hipGetLastError();
+}
+
 hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, const KvLayout& kv,
                           const float2* rope_table, int max_pos, const int32_t* ctx_lens,
                           const int32_t* cu_seqlens, int n_seqs, const int32_t* block_tables,
@@ -491,17 +523,9 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
   else
     rope_kv_kernel<1><<<grid, 256, 0, s>>>((bf16*)qkv, ld, n_q_heads, kv, rope_table, ctx_lens, cu_seqlens, n_seqs,
                                            block_tables, max_pages_per_seq, proj, 1, n_tokens, bias, paged_v);
-  if (paged_v) {
-    const dim3 vgrid((n_tokens >> 4) + n_seqs + 1, (kv.n_kv_heads * dh + kPageChannels - 1) / kPageChannels);
-    const int v_col = (n_q_heads + kv.n_kv_heads) * dh;
-    if (kv.fp8)
-      v_append_pages_kernel<true><<<vgrid, 256, 0, s>>>((const bf16*)qkv, ld, v_col, kv, cu_seqlens, n_seqs, n_tokens,
-                                                        block_tables, max_pages_per_seq);
-    else
-      v_append_pages_kernel<false><<<vgrid, 256, 0, s>>>((const bf16*)qkv, ld, v_col, kv, cu_seqlens, n_seqs, n_tokens,
-                                                         block_tables, max_pages_per_seq);
-  }
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !paged_v) return e;
+  return launch_v_append(qkv, ld, n_tokens, n_q_heads, kv, cu_seqlens, n_seqs, block_tables, max_pages_per_seq, s);
 }
 
 // ------------------------------------------------------------------ KV import / export

@@ -37,6 +37,7 @@ struct GemmParams {
   OperandLayout a_lay, w_lay, u_lay;
   int64_t Kpad, Npad, ldo, ldr;
   int M, N_store, epilogue, out_f32, res_f32;
+  PrefillRotation rot;  // EPI_ROTATE
   float* row_max;  // null, or (plain fp32 epilogue, unsplit, no bias) [M][2 tiles_n]
   int k_tiles_total, k_tiles_per_split, splits;
   int k_tiles_per_chunk;  // 0, or (splits = 1, small tiles) the K range is summed in chunks of this many k-tiles
@@ -144,6 +145,92 @@ __device__ __forceinline__ void gemm_epilogue16_max(const GemmParams& p, f32x4 (
       if (kq == 0) p.row_max[(int64_t)m * (2 * p.tiles_n) + col0 / (16 * WT)] = mx;
     }
     __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The epilogue of an unsplit QKV projection in prefill: bias, rotation, one rounding; queries and values go to the bf16 rows, keys to
+// their slots.  A wave's columns are whole heads (16 WT = 128: one of 128 channels or two of 64), so a lane holds both channels of
+// its pairs: tile t of a head and tile t + H, H = head_dim / 32.  Bound: the stores, and two look-ups in a row (a token's position,
+// then its (cos, sin)), asked for two row blocks at a time.  Against
+// an fp32 projection that a kernel of its own reads back (19346 tokens of 70B: 2302 + 216 us; 7959 of 7B: 708 + 123; 6713 of Qwen: 460 +
+// 52) the projection is no longer: 2289, 693, 434.
+template <int AT, int WT, int H>
+__device__ __forceinline__ void gemm_epilogue16_rotate(const GemmParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
+                                                       int l16, int kq) {
+  const PrefillRotation& r = p.rot;
+  constexpr int DH = 32 * H, AB = 2;
+  const bool odd = kq & 1;  // channels 4 .. 7 of eight
+  int2 where[AT];
+#pragma unroll
+  for (int at = 0; at < AT; ++at) where[at] = r.token_pages[min(row0 + at * 16 + l16, p.M - 1)];
+#pragma unroll
+  for (int hd = 0; hd < WT / (2 * H); ++hd) {
+    const int col = col0 + hd * DH, head = col / DH, kvh = head - r.n_q_heads;
+    if (kvh >= 2 * r.kv.n_kv_heads) continue;  // padding
+    f32x4 bias[2 * H];
+    if (p.bias) {
+#pragma unroll
+      for (int t = 0; t < 2 * H; ++t) bias[t] = *reinterpret_cast<const f32x4*>(p.bias + col + t * 16 + kq * 4);
+    }
+    const bool value = kvh >= r.kv.n_kv_heads;
+#pragma unroll
+    for (int a0 = 0; a0 < AT; a0 += AB) {
+      float4 cs[AB][H][2];
+      if (!value) {
+#pragma unroll
+        for (int ab = 0; ab < AB; ++ab) {
+          if (a0 + ab >= AT) break;
+          const float4* table = reinterpret_cast<const float4*>(r.rope_table + (int64_t)where[a0 + ab].x * (DH / 2) + kq * 4);
+#pragma unroll
+          for (int t = 0; t < H; ++t) {
+            cs[ab][t][0] = table[t * 8];
+            cs[ab][t][1] = table[t * 8 + 1];
+          }
+        }
+      }
+#pragma unroll
+      for (int ab = 0; ab < AB; ++ab) {
+        const int at = a0 + ab;
+        if (at >= AT) break;
+        const int m = row0 + at * 16 + l16;
+        if (m >= p.M) continue;
+        bf16* row = (bf16*)r.qkv + (int64_t)m * r.ld + col + kq * 4;
+        const int64_t page = where[at].y;
+        const int slot = where[at].x & 15;
+#pragma unroll
+        for (int t = 0; t < H; ++t) {
+          f32x4 a = acc[hd * 2 * H + t][at], b = acc[hd * 2 * H + t + H][at];
+          if (p.bias) {
+            a += bias[t];
+            b += bias[t + H];
+          }
+          float lo[4] = {a[0], a[1], a[2], a[3]}, hi[4] = {b[0], b[1], b[2], b[3]};
+          if (!value) {
+            const float4 c0 = cs[ab][t][0], c1 = cs[ab][t][1];
+            rotate_pair(a[0], b[0], make_float2(c0.x, c0.y), 0, lo[0], hi[0]);  // (channel 0 and 4, ... of eight are alike but for 3)
+            rotate_pair(a[1], b[1], make_float2(c0.z, c0.w), 1, lo[1], hi[1]);
+            rotate_pair(a[2], b[2], make_float2(c1.x, c1.y), 2, lo[2], hi[2]);
+            rotate_pair(a[3], b[3], make_float2(c1.z, c1.w), odd ? 7 : 3, lo[3], hi[3]);
+          }
+          bf16x4 l4, h4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            l4[e] = (bf16)lo[e];
+            h4[e] = (bf16)hi[e];
+          }
+          if (value || kvh < 0) {
+            *reinterpret_cast<bf16x4*>(row + t * 16) = l4;
+            *reinterpret_cast<bf16x4*>(row + (t + H) * 16) = h4;
+          } else {
+            const int c = t * 16 + kq * 4;
+            uint8_t* pool = (uint8_t*)r.kv.k_pool;
+            *reinterpret_cast<bf16x4*>(pool + k_pool_byte(r.kv, page, kvh, slot, 2 * c)) = l4;
+            *reinterpret_cast<bf16x4*>(pool + k_pool_byte(r.kv, page, kvh, slot, 2 * c + DH)) = h4;
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
@@ -523,7 +610,12 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
   // loads still in flight target LDS only; they must land before the workgroup's LDS is released.
   // The nops cover the MFMA -> accumulator-read distance, which the compiler cannot see.
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  if (p.row_max)
+  if (WT == 8 && p.epilogue == EPI_ROTATE) {
+    if constexpr (WT == 8) {
+      if (p.rot.kv.head_dim == 128) gemm_epilogue16_rotate<AT, WT, 4>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
+      else gemm_epilogue16_rotate<AT, WT, 2>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
+    }
+  } else if (p.row_max)
     gemm_epilogue16_max<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
   else if (p.splits == 1 && p.epilogue == EPI_RESIDUAL && !p.bias && p.N_store >= 4)
     gemm_epilogue16_residual<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
@@ -788,6 +880,18 @@ void gemm_tile_size(int tile, int* rows, int* weight_rows) {
   *weight_rows = kTiles[tile].bn();
 }
 
+static GemmPlan plan_of(const GemmArgs& a) {
+  const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
+  return a.form.tile ? a.form : gemm_plan({a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems});
+}
+
+// (A wave of a tile of 256 weight rows has 128 columns, whole heads.  Not for 8-bit pools: with the conversion in it the epilogue is too
+// long to be unrolled, and accumulators that are indexed at run time live in memory: 20 times the time.)
+bool gemm_can_rotate(const GemmArgs& a) {
+  const GemmPlan plan = plan_of(a);
+  return a.epilogue == EPI_STORE && plan.splits == 1 && kTiles[plan.tile].wt == 8;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   GemmParams p;
@@ -812,7 +916,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.epilogue = a.epilogue;
   p.k_tiles_total = (int)(a.Kpad / 64);
   const bool defer = a.splits_used != nullptr && a.epilogue != EPI_SWIGLU;
-  const GemmPlan plan = a.form.tile ? a.form : gemm_plan({a.M, a.force_tile, a.force_splits, a.epilogue, defer, a.Npad, a.Kpad, a.workspace_elems});
+  const GemmPlan plan = plan_of(a);
   const TileInfo& ti = kTiles[plan.tile];
   const int splits = plan.splits;
   p.tiles_m = (a.M + ti.bm() - 1) / ti.bm();
@@ -820,6 +924,10 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.k_tiles_per_split = (p.k_tiles_total + splits - 1) / splits;
   p.splits = splits;
   p.k_tiles_per_chunk = plan.chunk;
+  if (a.rotation) {
+    p.epilogue = EPI_ROTATE;
+    p.rot = *a.rotation;
+  }
   if (a.row_max_width) *a.row_max_width = 0;
   if (a.row_max && splits == 1 && a.epilogue == EPI_STORE && a.out_f32 && !a.bias) {
     p.row_max = a.row_max;

@@ -60,6 +60,7 @@ struct tdp_stage {
     float *h = nullptr, *xa = nullptr, *xb = nullptr;  // residual stream, fp32 between layers
     float* ws = nullptr;
     float *part_o = nullptr, *part_ml = nullptr;
+    int2* token_pages = nullptr;    // prefill: (position, page) of every token
     unsigned* spans_done = nullptr;  // finished spans of every (request, K/V head): zero between launches
     int4* attn_items = nullptr;     // decode work list, rebuilt every step
     int32_t* attn_item_pages = nullptr;  // physical pages of every item's span
@@ -187,6 +188,7 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
   // projections), which saves a reduce launch and one round trip of the result per projection.
   // (measured on the 70B-shaped stage with 1024 threads per row: +1.3 % at 16 rows, +1.7 % at 128, +1.6 % at 512)
   const bool fuse_reduce = true;
+  bool pages_known = false;  // prefill: sc.token_pages of this call
   int down_splits = 1;  // > 1: x (this layer's input) still has to be formed from h + partials
   for (int l = l_begin; l < l_end; ++l) {
     const KvLayout kv = kv_layout(st, l);
@@ -203,6 +205,8 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     int qkv_splits = 1, o_splits = 1;
+    bool rotated = false;  // the projection's epilogue rotates and appends
+    const PrefillRotation rotation{sc.qkv, st->Nqkv_pad, kv, st->rope_table, sc.token_pages, c.n_q_heads};
     g.workspace = sc.ws;
     g.workspace_elems = st->ws_elems;
     g.M = M;
@@ -214,15 +218,25 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
       g.residual = nullptr; g.ldr = 0; g.epilogue = EPI_STORE; g.out_f32 = 1; g.residual_f32 = 0;
       g.bias = st->has_bias ? st->bqkv + (int64_t)l * st->Nqkv_pad : nullptr;
       g.splits_used = fuse_reduce ? &qkv_splits : nullptr;
+      rotated = !ctx_lens && !kv.fp8 && gemm_can_rotate(g);
+      if (rotated && !pages_known) {
+        HIP_TRY(launch_token_pages(cu_seqlens, n_seqs, M, block_tables, c.max_pages_per_seq, sc.token_pages, s));
+        pages_known = true;
+      }
+      g.rotation = rotated ? &rotation : nullptr;
       HIP_TRY(launch_gemm(g, s));
       g.splits_used = nullptr;
+      g.rotation = nullptr;
     }
     // a3: rotary embedding + KV append, from the fp32 projection (if it was split: sums the partials and adds the bias, which the
     // GEMM's epilogue has done otherwise); in small decode batches inside the attention kernel
     const bool split = qkv_splits > 1, rotates = ctx_lens && attn_decode_rotates(M, c.n_kv_heads);
     const DecodeQueries dq{rotates ? nullptr : sc.qkv, st->Nqkv_pad, split ? sc.ws : sc.qkv32, split ? g.bias : nullptr, st->rope_table,
                            qkv_splits};
-    if (!rotates) {
+    if (rotated) {
+      Timer t(st, s, timed, T_ROPE);
+      HIP_TRY(launch_v_append(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, cu_seqlens, n_seqs, block_tables, c.max_pages_per_seq, s));
+    } else if (!rotates) {
       Timer t(st, s, timed, T_ROPE);
       HIP_TRY(launch_rope_kv(sc.qkv, st->Nqkv_pad, M, c.n_q_heads, kv, st->rope_table, st->max_pos, ctx_lens,
                              cu_seqlens, n_seqs, block_tables, c.max_pages_per_seq, dq.proj, qkv_splits,
@@ -362,6 +376,7 @@ int tdp_stage_create(const tdp_stage_config* cfg, tdp_stage** out) {
     A(&sc.part_ml, mb * c.n_q_heads * st->max_chunks * 2, false);
     A(&sc.spans_done, mb * c.n_kv_heads, true);
     A(&sc.attn_items, mb * st->max_chunks, false);
+    if (i == 0) A(&sc.token_pages, c.max_tokens, false);
     // spans longer than the minimum round the span count up: up to (1024 / 256 - 1) extra minimum spans' worth
     A(&sc.attn_item_pages, mb * (st->max_chunks + kDecodeSpanMax / kDecodeSpanMin) * (kDecodeSpanMin / 16), false);
   }
@@ -403,7 +418,7 @@ void tdp_stage_destroy(tdp_stage* st) {
     if (p) (void)hipFree(p);
   for (tdp_stage::Scratch& sc : st->sc) {
     void* sp[] = {sc.y, sc.qkv, sc.qkv32, sc.attn, sc.h, sc.u, sc.xa, sc.xb, sc.ws, sc.part_o, sc.part_ml,
-                  sc.spans_done, sc.attn_items, sc.attn_item_pages};
+                  sc.spans_done, sc.attn_items, sc.attn_item_pages, sc.token_pages};
     for (void* p : sp)
       if (p) (void)hipFree(p);
   }

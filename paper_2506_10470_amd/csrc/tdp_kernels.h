@@ -34,6 +34,7 @@ static inline OperandLayout layout_weights(int64_t K) {
 enum Epilogue : int {
   EPI_STORE = 0,     // out = acc                        (QKV projection)
   EPI_RESIDUAL = 1,  // out = residual + acc             (O and down projections)
+  EPI_ROTATE = 3,    // chosen by launch_gemm, see GemmArgs::rotation
   EPI_SWIGLU = 2,    // out[:, j] = silu(gate_j) * up_j  (gate/up projection; W rows interleaved
                      //                                   in blocks of 32: gate block, up block)
 };
@@ -42,6 +43,7 @@ constexpr int kGemmTileMax = 3;  // kernel variants that force_tile selects: 1 =
 struct GemmPlan {
   int tile, splits, chunk;  // chunk: k-tiles of 64 per chunk, 0 = all of K (of a split) in one sum
 };
+struct PrefillRotation;
 struct GemmArgs {
   const void* A;      // bf16, M rows x Kpad columns in a_layout; rows >= M are never read
   OperandLayout a_layout;
@@ -74,9 +76,13 @@ struct GemmArgs {
   // Room for Npad / kRowMaxWidth floats per row.
   float* row_max;         // null = not wanted
   int* row_max_width;
+  // QKV projection of a prefill, if gemm_can_rotate says that its plan allows it: the epilogue adds the bias, rotates, rounds once, writes
+  // queries and values to the bf16 rows and keys to their pages; `out` is not written.
+  const PrefillRotation* rotation;  // null = not wanted
 };
 constexpr int kRowMaxWidth = 64;  // the smallest width
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+bool gemm_can_rotate(const GemmArgs& a);
 
 // How a GEMM is made: a pure function of its shape and of what the caller fixes (host only).
 struct GemmPlanKey {
@@ -151,6 +157,20 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
                           const float2* rope_table, int max_pos, const int32_t* ctx_lens,
                           const int32_t* cu_seqlens, int n_seqs, const int32_t* block_tables,
                           int max_pages_per_seq, const float* proj, int splits, const float* bias, hipStream_t s);
+// What the epilogue of the QKV projection needs to do the same (GemmArgs::rotation), and the two steps around it: every token's
+// position and page, once per call, and the append of the values from the rows, page by page.
+struct PrefillRotation {
+  void* qkv;  // bf16 rows, ld
+  int64_t ld;
+  KvLayout kv;
+  const float2* rope_table;
+  const int2* token_pages;  // (position, page)
+  int n_q_heads;
+};
+hipError_t launch_token_pages(const int32_t* cu_seqlens, int n_seqs, int n_tokens, const int32_t* block_tables, int max_pages_per_seq,
+                              int2* token_pages, hipStream_t s);
+hipError_t launch_v_append(const void* qkv, int64_t ld, int n_tokens, int n_q_heads, const KvLayout& kv, const int32_t* cu_seqlens,
+                           int n_seqs, const int32_t* block_tables, int max_pages_per_seq, hipStream_t s);
 // KV import/export between packed logical order [tokens][Hkv][dh] and the paged pools.
 hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const KvLayout& kv,
                           const int32_t* cu_seqlens, int n_seqs, int total_tokens,
