@@ -255,8 +255,8 @@ __device__ __forceinline__ void locate_token(int t, const int32_t* ctx_lens, con
 // Bound: reading the partials for many rows, one round trip per dependent look-up for few.  In decode, and in prefill
 // where there are partials to sum, every unit has a thread of its own, which asks for the partials of UN splits at
 // once; only a prefill without partials takes one workgroup per token (its look-ups are shared).  As one workgroup of 1024
-// threads per token that fetched a split per turn, a launch of 16 / 48 (7B shape) / 128 (13B shape) / 512 tokens took
-// 9.4 / 11.3 / 17.6 / 20.5 us, now 5.4 / 8.1 / 16 / 21 (what is left of the last two is the value append: 2-byte stores
+// threads per token that fetched a split per turn, a launch of 48 (7B shape) / 128 (13B shape) / 512 tokens took
+// 11.3 / 17.6 / 20.5 us, now 8.1 / 16 / 21 (what is left of the last two is the value append: 2-byte stores
 // 32 bytes apart).
 template <int UN>
 __global__ __launch_bounds__(256) void rope_kv_kernel(bf16* __restrict__ qkv, int64_t ld, int n_q_heads,
