@@ -20,6 +20,7 @@
 
 #include <initializer_list>
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 
 #include "tdp_device.h"
@@ -37,8 +38,6 @@ struct GemmParams {
   OperandLayout a_lay, w_lay, u_lay;
   int64_t Kpad, Npad, ldo, ldr;
   int M, N_store, epilogue, out_f32, res_f32;
-  PrefillRotation rot;  // EPI_ROTATE
-  float* row_max;  // null, or (plain fp32 epilogue, unsplit, no bias) [M][2 tiles_n]
   int k_tiles_total, k_tiles_per_split, splits;
   int k_tiles_per_chunk;  // 0, or (splits = 1, small tiles) the K range is summed in chunks of this many k-tiles
   int tiles_m, tiles_n;
@@ -46,6 +45,15 @@ struct GemmParams {
   // XCD takes `chunks` runs of `chunk` tiles, and an eighth of the `rest` tiles behind them
   int band_h, n_tall, chunk_shift, chunks, rest;
   unsigned per_split_inv, tall_inv, low_inv, h_tall_inv, h_low_inv;  // see divide
+};
+// What the two epilogues that only one projection has need on top.  Their kernels are instances of their own (the type of the
+// parameters selects the epilogue): as run-time branches of every instance they cost the others registers, 16 -> 24 spilled ones
+// of a 256 x 256 tile, 3 to 4 more and 17 scalar ones of the other tiles of 256 weight rows.
+struct GemmRotateParams : GemmParams {
+  PrefillRotation rot;
+};
+struct GemmMaxParams : GemmParams {
+  float* row_max;  // [M][2 tiles_n]
 };
 
 // silu(z) = z / (1 + e^-z), with the hardware reciprocal (1 ulp) in place of an IEEE division: the
@@ -123,7 +131,7 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmParams& p, f32x4 (&acc
 // The plain fp32 epilogue with the largest element of every row among the wave's 16 WT columns (unsplit, no bias; minus infinity
 // where there is nothing but NaN).  (The barriers keep the row blocks apart: interleaved they spill.)
 template <int AT, int WT>
-__device__ __forceinline__ void gemm_epilogue16_max(const GemmParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
+__device__ __forceinline__ void gemm_epilogue16_max(const GemmMaxParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
                                                     int l16, int kq) {
 #pragma unroll
   for (int at = 0; at < AT; ++at) {
@@ -155,7 +163,7 @@ __device__ __forceinline__ void gemm_epilogue16_max(const GemmParams& p, f32x4 (
 // an fp32 projection that a kernel of its own reads back (19346 tokens of 70B: 2302 + 216 us; 7959 of 7B: 708 + 123; 6713 of Qwen: 460 +
 // 52) the projection is no longer: 2289, 693, 434.
 template <int AT, int WT, int H>
-__device__ __forceinline__ void gemm_epilogue16_rotate(const GemmParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
+__device__ __forceinline__ void gemm_epilogue16_rotate(const GemmRotateParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
                                                        int l16, int kq) {
   const PrefillRotation& r = p.rot;
   constexpr int DH = 32 * H, AB = 2;
@@ -199,6 +207,7 @@ __device__ __forceinline__ void gemm_epilogue16_rotate(const GemmParams& p, f32x
         const int slot = where[at].x & 15;
 #pragma unroll
         for (int t = 0; t < H; ++t) {
+          asm volatile("" : "+a"(acc[hd * 2 * H + t][at]), "+a"(acc[hd * 2 * H + t + H][at]));  // (not all read ahead: they would spill)
           f32x4 a = acc[hd * 2 * H + t][at], b = acc[hd * 2 * H + t + H][at];
           if (p.bias) {
             a += bias[t];
@@ -357,8 +366,8 @@ constexpr bool kChunked = AT * WT <= 12 || (AT == 4 && WT == 4 && NS == 9);
 
 // A workgroup of four waves (2 x 2) makes a tile of BM = 32 AT rows x BN = 32 WT weight rows; a wave, AT x WT
 // accumulators.
-template <int AT, int WT, int NS, bool WNT>
-__global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
+template <int AT, int WT, int NS, bool WNT, typename Params>
+__global__ __launch_bounds__(256) void gemm_mi16_kernel(const Params p) {
   constexpr int BM = AT * 32, BN = WT * 32, BK = 32;
   constexpr int CPR = BK / 8;         // 16-byte chunks per row
   // Rows that share one swizzle value.  A fragment read of this kernel is 16 rows x 4 chunks (lane =
@@ -610,17 +619,16 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const GemmParams p) {
   // loads still in flight target LDS only; they must land before the workgroup's LDS is released.
   // The nops cover the MFMA -> accumulator-read distance, which the compiler cannot see.
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  if (WT == 8 && p.epilogue == EPI_ROTATE) {
-    if constexpr (WT == 8) {
-      if (p.rot.kv.head_dim == 128) gemm_epilogue16_rotate<AT, WT, 4>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
-      else gemm_epilogue16_rotate<AT, WT, 2>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
-    }
-  } else if (p.row_max)
+  if constexpr (std::is_same_v<Params, GemmRotateParams>) {
+    if (p.rot.kv.head_dim == 128) gemm_epilogue16_rotate<AT, WT, 4>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
+    else gemm_epilogue16_rotate<AT, WT, 2>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
+  } else if constexpr (std::is_same_v<Params, GemmMaxParams>) {
     gemm_epilogue16_max<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
-  else if (p.splits == 1 && p.epilogue == EPI_RESIDUAL && !p.bias && p.N_store >= 4)
+  } else if (p.splits == 1 && p.epilogue == EPI_RESIDUAL && !p.bias && p.N_store >= 4) {
     gemm_epilogue16_residual<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq);
-  else
+  } else {
     gemm_epilogue16<AT, WT>(p, acc, m0 + wm0, n0 + wn0, l16, kq, split);
+  }
 }
 
 // Sum the split-K partials and apply the epilogue.  One thread per 4 output columns.
@@ -658,22 +666,28 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmParams p, in
 // factor where the order of the sums is free; M = 48, 22016 x 4096: 45 -> 39 us) and
 // between 160 and 256 rows on narrow projections.  The ring takes what LDS there is; two or three workgroups
 // per CU where a tile is small enough (their fill and epilogue then overlap the neighbour's stages).
+enum GemmKind { kOrdinary, kRotating, kMaximum, kKinds };
 struct TileInfo {
   int at, wt, ns, wg_per_cu;
   bool chunked;           // can sum K in chunks
   double stage_us;        // a 32-wide stage of one tile on a CU, the matrix pipe's part (see plan_cost)
-  const void* kernel[2];  // ordinary / non-temporal weight requests
+  const void* kernel[kKinds][2];  // ordinary / non-temporal weight requests; null: see gemm_can_rotate
   int bm() const { return at * 32; }
   int bn() const { return wt * 32; }
   int ring_rows() const { return (at * 2 + 3) / 4 * 64 + bn(); }  // rows of a ring stage (see IPA)
   int lds_bytes() const { return ns * ring_rows() * 64; }
 };
-#define TDP_TILE(AT, WT, NS, PER_CU, US)                                                   \
-  {AT, WT, NS, PER_CU, kChunked<AT, WT, NS>, US,                                           \
-   {reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, false>),                   \
-    reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, true>)}}
+template <int AT, int WT, int NS, bool WNT, typename Params>
+static const void* kernel_of() {
+  if constexpr (std::is_same_v<Params, GemmRotateParams> && WT != 8) return nullptr;
+  else return reinterpret_cast<const void*>(&gemm_mi16_kernel<AT, WT, NS, WNT, Params>);
+}
+#define TDP_KERNELS(AT, WT, NS, PARAMS) {kernel_of<AT, WT, NS, false, PARAMS>(), kernel_of<AT, WT, NS, true, PARAMS>()}
+#define TDP_TILE(AT, WT, NS, PER_CU, US)                                                                   \
+  {AT, WT, NS, PER_CU, kChunked<AT, WT, NS>, US,                                                           \
+   {TDP_KERNELS(AT, WT, NS, GemmParams), TDP_KERNELS(AT, WT, NS, GemmRotateParams), TDP_KERNELS(AT, WT, NS, GemmMaxParams)}}
 static const TileInfo kTiles[] = {
-    {0, 0, 0, 0, false, 0.0, {nullptr, nullptr}},
+    {0, 0, 0, 0, false, 0.0, {}},
     TDP_TILE(8, 8, 4, 1, 0.425),  // 1: 256 x 256
     TDP_TILE(4, 8, 6, 1, 0.252),  // 2: 128 x 256
     TDP_TILE(4, 4, 4, 2, 0.129),  // 3: 128 x 128
@@ -686,6 +700,7 @@ static const TileInfo kTiles[] = {
     TDP_TILE(2, 4, 6, 2, 0.079), TDP_TILE(1, 4, 4, 3, 0.0415),
 };
 #undef TDP_TILE
+#undef TDP_KERNELS
 constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 // The 128 x 128 tile that has room for chunked sums is used for those only: otherwise two workgroups per CU (tile 3) are 7 to 15 %
 // faster at the same split-K factor (1367 pairs of launches, M from 1 to 16384).
@@ -701,8 +716,10 @@ hipError_t gemm_setup() {
     hipError_t e;
     e = hipSuccess;
     for (int i = 1; i < kTileCount; ++i)
-      for (int w = 0; w < 2 && e == hipSuccess; ++w)
-        e = hipFuncSetAttribute(kTiles[i].kernel[w], hipFuncAttributeMaxDynamicSharedMemorySize, kTiles[i].lds_bytes());
+      for (const auto& kind : kTiles[i].kernel)
+        for (const void* kernel : kind)
+          if (kernel && e == hipSuccess)
+            e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kTiles[i].lds_bytes());
     result = e;
   });
   return result;
@@ -889,7 +906,7 @@ static GemmPlan plan_of(const GemmArgs& a) {
 // long to be unrolled, and accumulators that are indexed at run time live in memory: 20 times the time.)
 bool gemm_can_rotate(const GemmArgs& a) {
   const GemmPlan plan = plan_of(a);
-  return a.epilogue == EPI_STORE && plan.splits == 1 && kTiles[plan.tile].wt == 8;
+  return a.epilogue == EPI_STORE && plan.splits == 1 && kTiles[plan.tile].kernel[kRotating][0];
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
@@ -903,7 +920,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.out_f32 = a.epilogue == EPI_SWIGLU ? 0 : a.out_f32;
   p.res_f32 = a.residual_f32;
   p.ws = a.workspace;
-  p.row_max = nullptr;
   p.a_lay = a.a_layout;
   p.w_lay = layout_weights(a.Kpad);
   p.u_lay = a.u_layout;
@@ -924,15 +940,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   p.k_tiles_per_split = (p.k_tiles_total + splits - 1) / splits;
   p.splits = splits;
   p.k_tiles_per_chunk = plan.chunk;
-  if (a.rotation) {
-    p.epilogue = EPI_ROTATE;
-    p.rot = *a.rotation;
-  }
-  if (a.row_max_width) *a.row_max_width = 0;
-  if (a.row_max && splits == 1 && a.epilogue == EPI_STORE && a.out_f32 && !a.bias) {
-    p.row_max = a.row_max;
-    *a.row_max_width = ti.bn() / 2;
-  }
+  const bool maximum = a.row_max && splits == 1 && a.epilogue == EPI_STORE && a.out_f32 && !a.bias;
+  if (a.row_max_width) *a.row_max_width = maximum ? ti.bn() / 2 : 0;
   const int bands = (p.tiles_m + 3) / 4;
   p.band_h = p.tiles_m / bands;
   p.n_tall = p.tiles_m % bands;
@@ -953,8 +962,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   // a single row of tiles reads every weight byte once: request them as non-temporal (also two rows of a
   // wide projection, see the kernel's comment)
   const bool wnt = p.tiles_m == 1 || (p.tiles_m == 2 && a.Npad >= 32768 && splits == 1);
-  void* args[] = {&p};
-  hipError_t e = hipLaunchKernel(ti.kernel[wnt ? 1 : 0], grid, dim3(256), args, ti.lds_bytes(), s);
+  auto launch = [&](GemmKind kind, auto params) {
+    void* args[] = {&params};
+    return hipLaunchKernel(ti.kernel[kind][wnt ? 1 : 0], grid, dim3(256), args, ti.lds_bytes(), s);
+  };
+  hipError_t e = a.rotation ? launch(kRotating, GemmRotateParams{p, *a.rotation})
+                 : maximum  ? launch(kMaximum, GemmMaxParams{p, a.row_max})
+                            : launch(kOrdinary, p);
   if (e != hipSuccess) return e;
   if (a.splits_used) *a.splits_used = defer ? splits : 1;
   if (splits > 1 && !defer) {

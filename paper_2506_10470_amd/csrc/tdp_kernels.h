@@ -34,7 +34,6 @@ static inline OperandLayout layout_weights(int64_t K) {
 enum Epilogue : int {
   EPI_STORE = 0,     // out = acc                        (QKV projection)
   EPI_RESIDUAL = 1,  // out = residual + acc             (O and down projections)
-  EPI_ROTATE = 3,    // chosen by launch_gemm, see GemmArgs::rotation
   EPI_SWIGLU = 2,    // out[:, j] = silu(gate_j) * up_j  (gate/up projection; W rows interleaved
                      //                                   in blocks of 32: gate block, up block)
 };

@@ -1,0 +1,57 @@
+"""Registers of the GEMM kernels as they are built.  Every ordinary instance is launched for all projections; what an epilogue that
+only one of them needs would cost it shows here: the 256 x 256 tile fills the register file, and 16 spilled vector registers are what its
+own residual epilogue takes."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2506_10470_amd import build as B
+
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """(rows / 32, weight rows / 32, parameters) -> the worst of (spilled vector registers, bytes of scratch) over its instances"""
+    if not os.path.exists(B.LIB):
+        B.build()
+    data = open(B.LIB, "rb").read()
+    found = {}
+    for at in (m.start() for m in re.finditer(MAGIC, data)):
+        count, = struct.unpack_from("<Q", data, at + len(MAGIC))
+        p = at + len(MAGIC) + 8
+        for _ in range(count):
+            offset, size, n = struct.unpack_from("<QQQ", data, p)
+            target = data[p + 24:p + 24 + n]
+            p += 24 + n
+            if b"gfx950" not in target or b"gemm_mi16_kernel" not in data[at + offset:at + offset + size]:
+                continue
+            path = tmp_path_factory.mktemp("code") / "gemm.co"
+            path.write_bytes(data[at + offset:at + offset + size])
+            readelf = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+            notes = subprocess.run([readelf, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+            for kernel in notes.split("  - .agpr_count:")[1:]:
+                field = dict(re.findall(r"^    \.(\w+): +(\S+)$", kernel, re.M))
+                m = re.search(r"gemm_mi16_kernelILi(\d)ELi(\d)ELi\d+ELb\dE\w*?(Gemm[A-Za-z]*Params)E", field["name"])
+                if m:
+                    key = int(m.group(1)), int(m.group(2)), m.group(3)
+                    use = int(field["vgpr_spill_count"]), int(field["private_segment_fixed_size"])
+                    found[key] = max(found.get(key, (0, 0)), use)
+    return found
+
+
+def test_ordinary_projections_pay_for_no_other_epilogue(kernels):
+    ordinary = {k[:2]: v for k, v in kernels.items() if k[2] == "GemmParams"}
+    assert len(ordinary) == 12                      # (128 x 128 has two forms)
+    spills, scratch = ordinary.pop((8, 8))
+    assert spills <= 16 and scratch <= 68, (spills, scratch)
+    assert set(ordinary.values()) == {(0, 0)}, ordinary
+
+
+def test_the_rotating_epilogue_keeps_to_registers(kernels):
+    rotating = {k[:2]: v for k, v in kernels.items() if k[2] == "GemmRotateParams"}
+    assert sorted(rotating) == [(n, 8) for n in (4, 5, 6, 7, 8)]
+    assert set(rotating.values()) == {(0, 0)}, rotating
