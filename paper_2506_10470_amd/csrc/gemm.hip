@@ -129,30 +129,37 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmParams& p, f32x4 (&acc
 }
 
 // The plain fp32 epilogue with the largest element of every row among the wave's 16 WT columns (unsplit, no bias; minus infinity
-// where there is nothing but NaN).  (The barriers keep the row blocks apart: interleaved they spill.)
+// where there is nothing but NaN).  The exchanges between lanes, two round trips through LDS for each row block, come behind all stores
+// and are in flight together: made block by block in front of the next one's stores they took most of what the maxima save (see
+// tdp_lm_head).  (Accumulators are read block by block; all read ahead they spill.)
 template <int AT, int WT>
 __device__ __forceinline__ void gemm_epilogue16_max(const GemmMaxParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
                                                     int l16, int kq) {
+  float mx[AT];
 #pragma unroll
   for (int at = 0; at < AT; ++at) {
     const int m = row0 + at * 16 + l16;
-    if (m < p.M) {
-      float* out = (float*)p.out + (int64_t)m * p.ldo;
-      float mx = -INFINITY;
+    float* out = (float*)p.out + (int64_t)m * p.ldo;
+    mx[at] = -INFINITY;
 #pragma unroll
-      for (int wt = 0; wt < WT; ++wt) {
-        const int n = col0 + wt * 16 + kq * 4;
-        if (n < p.N_store) {
-          const f32x4 v = acc[wt][at];
-          *reinterpret_cast<f32x4*>(out + n) = v;
-          mx = fmaxf(fmaxf(mx, fmaxf(v[0], v[1])), fmaxf(v[2], v[3]));
-        }
+    for (int wt = 0; wt < WT; ++wt) {
+      const int n = col0 + wt * 16 + kq * 4;
+      asm volatile("" : "+a"(acc[wt][at]));
+      if (m < p.M && n < p.N_store) {
+        const f32x4 v = acc[wt][at];
+        *reinterpret_cast<f32x4*>(out + n) = v;
+        mx[at] = fmaxf(fmaxf(mx[at], fmaxf(v[0], v[1])), fmaxf(v[2], v[3]));
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (kq == 0) p.row_max[(int64_t)m * (2 * p.tiles_n) + col0 / (16 * WT)] = mx;
     }
-    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int at = 0; at < AT; ++at) mx[at] = fmaxf(mx[at], __shfl_xor(mx[at], 16, 64));
+#pragma unroll
+  for (int at = 0; at < AT; ++at) mx[at] = fmaxf(mx[at], __shfl_xor(mx[at], 32, 64));
+#pragma unroll
+  for (int at = 0; at < AT; ++at) {
+    const int m = row0 + at * 16 + l16;
+    if (kq == 0 && m < p.M) p.row_max[(int64_t)m * (2 * p.tiles_n) + col0 / (16 * WT)] = mx[at];
   }
 }
 

@@ -897,9 +897,8 @@ int tdp_lm_head(tdp_ends* e, const void* hidden_in, int32_t n_rows_in, const int
   g.out = logits; g.ldo = V; g.epilogue = EPI_STORE; g.out_f32 = 1;
   g.workspace = e->ws; g.workspace_elems = e->ws_elems;
   // The greedy token of a long row: the projection notes the largest logit of every piece of it, and a wave looks at those and at
-  // one piece, instead of a workgroup at all logits again (final norm to token, 512 rows of 32000 at d 8192: 225 -> 218 us; 300 at
-  // 5120: 125 -> 118; 4 rows of a toy width 14.6 -> 12.4).  On shorter rows there is less to read again than the second look-up
-  // costs (100 rows of 8004 at 5120: 29.1 without, 29.7 with).
+  // one piece, instead of a workgroup at all logits again (final norm to token, 512 rows of 32000 at d 8192: 224 -> 213 us; 300 at
+  // 5120: 123 -> 115; 4 rows of a toy width 14.8 -> 12.4).
   int width = 0;
   g.row_max = next_token && V >= kRowMaxColumns ? e->row_max : nullptr;
   g.row_max_width = &width;

@@ -55,3 +55,9 @@ def test_the_rotating_epilogue_keeps_to_registers(kernels):
     rotating = {k[:2]: v for k, v in kernels.items() if k[2] == "GemmRotateParams"}
     assert sorted(rotating) == [(n, 8) for n in (4, 5, 6, 7, 8)]
     assert set(rotating.values()) == {(0, 0)}, rotating
+
+
+def test_the_maximum_epilogue_keeps_to_registers(kernels):
+    maximum = {k[:2]: v for k, v in kernels.items() if k[2] == "GemmMaxParams"}
+    assert len(maximum) == 12
+    assert set(maximum.values()) == {(0, 0)}, maximum
