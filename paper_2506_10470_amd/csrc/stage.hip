@@ -765,7 +765,7 @@ int tdp_stage_timing_read(tdp_stage* st, float* ms) {
 
 // ---- the two ends of the pipeline ---------------------------------------------------------------
 
-constexpr int64_t kRowMaxColumns = 20000;
+constexpr int64_t kRowMaxColumns = 4000;
 
 struct tdp_ends {
   tdp_ends_config cfg;
@@ -898,7 +898,9 @@ int tdp_lm_head(tdp_ends* e, const void* hidden_in, int32_t n_rows_in, const int
   g.workspace = e->ws; g.workspace_elems = e->ws_elems;
   // The greedy token of a long row: the projection notes the largest logit of every piece of it, and a wave looks at those and at
   // one piece, instead of a workgroup at all logits again (final norm to token, 512 rows of 32000 at d 8192: 224 -> 213 us; 300 at
-  // 5120: 123 -> 115; 4 rows of a toy width 14.8 -> 12.4).
+  // 5120: 123 -> 115; 4 rows of a toy width 14.8 -> 12.4).  From 4000 columns on that is never behind by more than the 0.3 us of repeated runs
+  // (ten batches of 1 to 512 rows, d 256 to 8192): 512 rows of 4000 / 8004 at d 256 16.6 -> 13.6 / 21.9 -> 15.3, at 5120 35.8 -> 34.6 /
+  // 51.1 -> 48.5.  At 2000 columns the two are level, within 0.5 us either way.
   int width = 0;
   g.row_max = next_token && V >= kRowMaxColumns ? e->row_max : nullptr;
   g.row_max_width = &width;

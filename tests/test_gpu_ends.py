@@ -205,7 +205,7 @@ def test_lm_head_at_llama_size_sampled():
         assert np.array_equal(toks.cpu().numpy()[:64], E.greedy_tokens(logits[:64].cpu().numpy().astype(np.float64)))
 
 
-@pytest.mark.parametrize("vocab", [19996, 20000, 32000])     # rows below and from 20000 columns on, a whole number of tiles and not
+@pytest.mark.parametrize("vocab", [3996, 4000, 19996, 20000, 32000])  # rows below and from 4000 columns on, a whole number of tiles and not
 @pytest.mark.parametrize("M", [1, 33, 200, 512])             # tiles of 32 to 256 rows, the last one partly filled
 def test_greedy_tokens_of_the_head_are_those_of_its_logits(M, vocab):
     """Few distinct columns in random places: every row's largest logit lies in many pieces of the row at once.  Rows that hold a
