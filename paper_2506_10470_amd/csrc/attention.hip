@@ -709,12 +709,23 @@ bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len)
 }
 
 // Whether the attention kernel rotates the queries and appends the new keys and values itself.  A kernel in front of it is a launch in
-// every layer, 4 to 8 us for small batches.  As long as all (request, K/V head) pairs run at once (three workgroups per CU) the
-// rotation is ahead inside, two layers, us: 70B, 8 / 16 / 64 requests 612 / 632 / 783 with the kernel in front, 594 / 621 / 766 inside; 7B,
-// 2 / 16 requests 231 / 282 and 217 / 267; Qwen, 48 492 and 474; toy widths, 4 / 256 requests 68.5 / 75 and 67 / 70.6.  Around 800 to 1000
-// pairs the two are level, and beyond that every value stored among the reads costs more than it does in front of them: 13B, 5120
-// pairs, 1215 and 1285 (without the stores of the values 1207).
-bool attn_decode_rotates(int batch, int n_kv_heads) { return batch * n_kv_heads <= 3 * 256; }
+// every layer, 4 to 8 us for small batches.  As long as there are no more (request, K/V head) pairs than three workgroups per CU the
+// rotation is ahead inside or level, two layers, us, both ways in turn on one card: 70B, 8 / 16 / 64 requests 586 / 604 / 747 with the kernel in
+// front, 579 / 598 / 747 inside; 7B, 2 / 16 requests 229 / 268 and 222 / 262; Qwen, 48 481 and 476; toy widths, 4 / 256 requests 67.0 / 75.1 and
+// 66.3 / 72.4.  At 880 pairs the two are level, and beyond that every value stored among the reads costs more than it does in front of
+// them: 13B, 5120 pairs, 1202 and 1258.
+// A request of several spans has its queries rotated once per span.  Beside spans of 1024 tokens and more that is lost in the reads at any
+// length (QKV and attention of one layer, inside / in front, 128 to 768 pairs, contexts of 1000 to 100,000 tokens: 0.93 to 1.01, 70B with 64
+// requests of 20,000 972 / 978 us).  Beside the spans of 256 of fewer than 128 pairs it is not, once there are many of them: 0.92 to 0.99 up to
+// 4000 workgroups, level around 5000, and from there 1.01 to 1.04, with 8-bit pools to 1.07 (70B, 8 requests of 10,000 / 30,000 / 100,000
+// tokens 171 / 315 / 837 us inside, 172 / 309 / 811 in front; 7B, 8 bits, 3 requests of 20,000 / 100,000 1.02 / 1.05).  How long the contexts
+// are is known on the device alone; the line goes by the workgroups of the longest that the block tables allow, at a place where contexts
+// spread over that length lose as much as they gain.  (16 query heads on one K/V head need a second turn of the rotating waves:
+// 120 requests of 2000 tokens, 960 workgroups, 1.03.)
+bool attn_decode_rotates(int batch, int n_kv_heads, int max_spans, int span_len) {
+  if (batch * n_kv_heads > 3 * 256) return false;
+  return span_len >= 1024 || (int64_t)attn_decode_items(batch, max_spans, span_len) * n_kv_heads <= 8192;
+}
 
 hipError_t launch_attn_plan(const int32_t* ctx_lens, const int32_t* block_tables, int max_pages_per_seq, int batch,
                             int max_spans, int span_len, int4* items, int32_t* item_pages, hipStream_t s) {

@@ -230,7 +230,7 @@ int run_layers(tdp_stage* st, tdp_stage::Scratch& sc, bool timed, const void* hi
     }
     // a3: rotary embedding + KV append, from the fp32 projection (if it was split: sums the partials and adds the bias, which the
     // GEMM's epilogue has done otherwise); in small decode batches inside the attention kernel
-    const bool split = qkv_splits > 1, rotates = ctx_lens && attn_decode_rotates(M, c.n_kv_heads);
+    const bool split = qkv_splits > 1, rotates = ctx_lens && attn_decode_rotates(M, c.n_kv_heads, st->max_chunks, span_len);
     const DecodeQueries dq{rotates ? nullptr : sc.qkv, st->Nqkv_pad, split ? sc.ws : sc.qkv32, split ? g.bias : nullptr, st->rope_table,
                            qkv_splits};
     if (rotated) {

@@ -208,7 +208,7 @@ struct DecodeQueries {
   const float2* rope_table;  // (cos, sin) of [position][head_dim / 2]
   int splits;
 };
-bool attn_decode_rotates(int batch, int n_kv_heads);
+bool attn_decode_rotates(int batch, int n_kv_heads, int max_spans, int span_len);
 bool attn_decode_counts_spans(int batch, int n_q_heads, int n_kv_heads, int max_spans, int span_len);
 bool attn_decode_planned(int batch, int n_kv_heads, int max_spans, int span_len);
 hipError_t launch_attn_decode(const DecodeQueries& dq, int batch, int n_q_heads, const KvLayout& kv,

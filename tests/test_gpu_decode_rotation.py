@@ -1,5 +1,5 @@
-"""Rotation and append of a decode step: inside the attention kernel while all (request, K/V head) pairs run at once, by a kernel
-in front of it beyond that.  The arithmetic is the same, so what is stored and attended to is, bit for bit."""
+"""Rotation and append of a decode step: inside the attention kernel while all (request, K/V head) pairs run at once and spans of 256
+tokens are not too many, by a kernel in front of it beyond that.  The arithmetic is the same, so what is stored and attended to is, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -71,3 +71,42 @@ def test_both_places_give_the_same_bits(heads, kv_heads, dh, scales, bias):
     for other in results[1:]:
         for a, b in zip(results[0], other):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("spans,inside", [(128, True), (129, False)])   # of 256 tokens that a block-table row has room for
+@pytest.mark.parametrize("scales", [None, (0.03125, 0.7)])
+def test_many_short_spans_are_rotated_in_front(spans, inside, scales):
+    """64 pairs of requests whose block tables allow 8192 or 8256 workgroups; the same requests give the same bits either way."""
+    from paper_2506_10470_amd import tdp
+    B, heads, kv_heads, dh = 32, 4, 2, 64
+    d, dkv = heads * dh, kv_heads * dh
+    ctx = np.array([0, 255, 256, 700, 1500] + [11] * (B - 5))
+    cu, total = i32(np.concatenate([[0], np.cumsum(ctx)])), int(ctx.sum())
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = {n: (torch.randn(*s, generator=g, device="cuda") * 0.1).to(torch.bfloat16)
+         for n, s in (("wq", (d, d)), ("wk", (d, dkv)), ("wv", (d, dkv)), ("wo", (d, d)))}
+    x = torch.randn(B, d, generator=g, device="cuda").to(torch.bfloat16)
+    k, v = (torch.randn(total, kv_heads, dh, generator=g, device="cuda").to(torch.bfloat16) for _ in "kv")
+    outs = []
+    for width in (128, spans * 16):
+        tables, pages = W.block_tables(5, ctx + 1, max_pages_per_seq=width)
+        st = tdp.tdp_stage_create(tdp.StageConfig(
+            n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=dh, d_ff=128, rms_eps=1e-5, rope_base=1e4,
+            page_size=16, num_pages=pages, max_batch=B, max_tokens=0, max_seqs=0, max_pages_per_seq=width,
+            kv_dtype=tdp.KV_FP8_E4M3 if scales else tdp.KV_BF16, k_scale=scales[0] if scales else 0.0,
+            v_scale=scales[1] if scales else 0.0))
+        try:
+            for name, t in w.items():
+                tdp.tdp_stage_set_weight(st, 0, tdp.WEIGHT_IDS[name], t, tdp.BF16, tdp.DEVICE, *t.shape)
+            for name in ("g_attn", "g_mlp"):
+                tdp.tdp_stage_set_weight(st, 0, tdp.WEIGHT_IDS[name], torch.ones(d, device="cuda"), tdp.F32, tdp.DEVICE, d, 1)
+            tdp.tdp_stage_kv_import(st, 0, k, v, cu, i32(np.maximum(tables, 0)), B, total)
+            out = torch.full((B, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            tdp.tdp_stage_timing_enable(st, True)
+            tdp.tdp_stage_decode(st, x, i32(ctx), i32(tables), B, out)
+            torch.cuda.synchronize()
+            assert (tdp.tdp_stage_timing_read(st)["rope_kv"] == 0) == (inside or width == 128)
+            outs.append(out.view(torch.int16))
+        finally:
+            tdp.tdp_stage_destroy(st)
+    assert not torch.isnan(out.float()).any() and torch.equal(*outs)
