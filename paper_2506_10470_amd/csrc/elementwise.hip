@@ -535,10 +535,18 @@ hipError_t launch_rope_kv(void* qkv, int64_t ld, int n_tokens, int n_q_heads, co
 // transposed page is read and written 16 bytes (8 tokens of a channel; 8-bit: all 16) at a time.  Element by element,
 // with 2-byte accesses on both sides, 23,000 tokens of 40 x 128 channels took 790 us in and 450 us out (0.96 GB each:
 // 1.2 and 2.1 TB/s); like this 195 and 192 us (4.9 TB/s; a plain copy reaches 4.7).
-// ONCE: from 16 MiB of packed keys and values on, stores are non-temporal (1), from 256 MiB on, what the memory-side cache holds, loads
-// as well (2); calls of prompts' caches, in + out, us, ONCE 0 / 1 / 2: 27 MB 27.0 / 23.7 / 30.2; 50 MB 50.4 / 40.4; 120 MB 107 / 100 / 99;
-// 0.95 GB 389 / 388 / 380.  Below that nothing is gained (7 MB 12.5 / 12.4 / 14.2), and a cache just imported is there for the next step.
-template <bool KV8, bool TO_PAGES, int CH, int ONCE>
+// Non-temporal loads (NTL) and stores (NTS), by the bytes of the packed keys and values, plain below 16 MiB.  What stands behind a move
+// counts as much as the move: an imported cache is there for the next step to read.  All us, 13B shape, both ways in turn; "in + out":
+// import and export of three caches in turn; "step": import, then the decode step that reads it.
+//   Import, 16 bits: stores up to 64 MiB (34 MB in + out 34.9 -> 29.2, step 152.9 and 153.7; 50 MB 48.8 -> 46.8, step 160.5 and 161.6), from
+//   there on the packed arrays are loaded so and the pages stored as usual (90 MB in + out 84.3 -> 80.8, step 180.0 -> 176.9; 250 MB 210.7 ->
+//   209.3, step 274.0 -> 262.6; arrays just written, import, step 371 -> 358).  Pages stored so cost the step more than the move gains: 250
+//   MB, step 289 with non-temporal stores, 285 with both.
+//   Import, 8 bits: half the bytes are stored, plain, and from 64 MiB on loaded so (90 MB in + out 88.0 -> 84.5, step 188.6 -> 186.8).
+//   Export: stores (decode step, then export: 70 MB 175.6 -> 170.6, 8 bits 171.0 -> 167.0), from 256 MiB on, what the memory-side cache
+//   holds, 16-bit loads as well (400 MB 389.9 -> 377.3, stores alone 381.8).  Below that a cache may still hold the pages (24 MB, the
+//   same cache again and again, 17.5 and 22.0).
+template <bool KV8, bool TO_PAGES, int CH, bool NTL, bool NTS>
 __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packed, bf16* __restrict__ v_packed,
                                                       KvLayout kv, const int32_t* __restrict__ cu_seqlens, int n_seqs,
                                                       int total_tokens, const int32_t* __restrict__ block_tables,
@@ -566,8 +574,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
     for (int j = 0; j < PER; ++j) {
       const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
       if (i < pieces && tok < n) {
-        k[j] = ld_bf16x8_once<(ONCE > 1)>(kp + (int64_t)tok * dkv + ch);
-        v[j] = ld_bf16x8_once<(ONCE > 1)>(vp + (int64_t)tok * dkv + ch);
+        k[j] = ld_bf16x8_once<NTL>(kp + (int64_t)tok * dkv + ch);
+        v[j] = ld_bf16x8_once<NTL>(vp + (int64_t)tok * dkv + ch);
       }
     }
 #pragma unroll
@@ -584,12 +592,12 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
           }
           *reinterpret_cast<uint2*>(k_at(tok, ch)) = c;
         } else {
-          st_bf16x8_once<(ONCE > 0)>(reinterpret_cast<bf16*>(k_at(tok, ch)), k[j]);
+          st_bf16x8_once<NTS>(reinterpret_cast<bf16*>(k_at(tok, ch)), k[j]);
         }
       }
     }
     __syncthreads();
-    store_v_page<KV8, CH, (ONCE > 0)>(tile, v_page, channels, n, kv.v_scale);
+    store_v_page<KV8, CH, NTS>(tile, v_page, channels, n, kv.v_scale);
   } else {
     bf16x8 k[PER];
     uint2 k8[PER];
@@ -598,7 +606,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       const int i = threadIdx.x + 256 * j, tok = page_piece_token(i), ch = page_piece_channel(i);
       if (i < pieces && tok < n) {
         if constexpr (KV8) k8[j] = *reinterpret_cast<const uint2*>(k_at(tok, ch));
-        else k[j] = ld_bf16x8_once<(ONCE > 1)>(reinterpret_cast<const bf16*>(k_at(tok, ch)));
+        else k[j] = ld_bf16x8_once<NTL>(reinterpret_cast<const bf16*>(k_at(tok, ch)));
       }
     }
     if constexpr (KV8) {
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
       for (int i = threadIdx.x; i < channels; i += 256) {
         const int t0 = (i & 1) * 8, c = i & ~1;
         const bf16* src = reinterpret_cast<const bf16*>(v_page) + c * 16 + t0;
-        const bf16x8 a = ld_bf16x8_once<(ONCE > 1)>(src), b = ld_bf16x8_once<(ONCE > 1)>(src + 16);
+        const bf16x8 a = ld_bf16x8_once<NTL>(src), b = ld_bf16x8_once<NTL>(src + 16);
 #pragma unroll
         for (int t = 0; t < 8; ++t) *reinterpret_cast<bf16x2*>(&tile[t0 + t][c]) = bf16x2{a[t], b[t]};
       }
@@ -638,8 +646,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(bf16* __restrict__ k_packe
             k[j][4 + e] = (bf16)(e4m3_to_f32((k8[j].y >> (8 * e)) & 255u) * kv.k_scale);
           }
         }
-        st_bf16x8_once<(ONCE > 0)>(kp + (int64_t)tok * dkv + ch, k[j]);
-        st_bf16x8_once<(ONCE > 0)>(vp + (int64_t)tok * dkv + ch, ld_bf16x8(&tile[tok][ch]));
+        st_bf16x8_once<NTS>(kp + (int64_t)tok * dkv + ch, k[j]);
+        st_bf16x8_once<NTS>(vp + (int64_t)tok * dkv + ch, ld_bf16x8(&tile[tok][ch]));
       }
     }
   }
@@ -732,24 +740,28 @@ hipError_t launch_kv_copy(int to_pages, void* k_packed, void* v_packed, const Kv
     const int ch = narrow ? 128 : kPageChannels;
     const int64_t bytes = 4ll * total_tokens * dkv;  // of the packed keys and values
     const dim3 grid(pages, (dkv + ch - 1) / ch);
-#define TDP_MOVE__(KV8, TO, CH, ONCE)                                                                                            \
-  kv_move_kernel<KV8, TO, CH, ONCE><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
-                                                   block_tables, max_pages_per_seq)
-#define TDP_MOVE_(KV8, TO, CH)                                                                                              \
-  do {                                                                                                                      \
-    if (bytes < 16ll << 20) TDP_MOVE__(KV8, TO, CH, 0);                                                                     \
-    else if (bytes < 256ll << 20) TDP_MOVE__(KV8, TO, CH, 1);                                                               \
-    else TDP_MOVE__(KV8, TO, CH, 2);                                                                                        \
-  } while (0)
-#define TDP_MOVE(KV8, TO) do { if (narrow) TDP_MOVE_(KV8, TO, 128); else TDP_MOVE_(KV8, TO, kPageChannels); } while (0)
-    if (kv.fp8) {
-      if (to_pages) TDP_MOVE(true, true); else TDP_MOVE(true, false);
+    const bool some = bytes >= 16ll << 20, many = bytes >= 64ll << 20, most = bytes >= 256ll << 20;  // (see the kernel)
+#define TDP_MOVE_(KV8, TO, CH, NTL, NTS)                                                                                           \
+  kv_move_kernel<KV8, TO, CH, NTL, NTS><<<grid, 256, 0, s>>>((bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens, n_seqs, total_tokens, \
+                                                             block_tables, max_pages_per_seq)
+#define TDP_MOVE(KV8, TO, NTS) \
+  do { if (narrow) TDP_MOVE_(KV8, TO, 128, false, NTS); else TDP_MOVE_(KV8, TO, kPageChannels, false, NTS); } while (0)
+    // (2047 workgroups of 512 channels are less than 64 MiB)
+    if (to_pages) {
+      if (kv.fp8 && many) TDP_MOVE_(true, true, kPageChannels, true, false);
+      else if (kv.fp8) TDP_MOVE(true, true, false);
+      else if (many) TDP_MOVE_(false, true, kPageChannels, true, false);
+      else if (some) TDP_MOVE(false, true, true);
+      else TDP_MOVE(false, true, false);
     } else {
-      if (to_pages) TDP_MOVE(false, true); else TDP_MOVE(false, false);
+      if (kv.fp8 && some) TDP_MOVE(true, false, true);
+      else if (kv.fp8) TDP_MOVE(true, false, false);
+      else if (most) TDP_MOVE_(false, false, kPageChannels, true, true);
+      else if (some) TDP_MOVE(false, false, true);
+      else TDP_MOVE(false, false, false);
     }
 #undef TDP_MOVE
 #undef TDP_MOVE_
-#undef TDP_MOVE__
     return hipGetLastError();
   }
   kv_copy_kernel<<<total_tokens, 256, 0, s>>>(to_pages, (bf16*)k_packed, (bf16*)v_packed, kv, cu_seqlens,

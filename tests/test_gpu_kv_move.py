@@ -80,7 +80,7 @@ def test_a_prefix_of_the_packed_tokens_can_be_moved(tdp):
 
 
 @pytest.mark.parametrize("kv_scales", [None, (0.03125, 0.7)])
-@pytest.mark.parametrize("tokens", [3276, 3277, 52428, 52429])   # 1280 channels: one token below and from 16 and 256 MiB on
+@pytest.mark.parametrize("tokens", [3276, 3277, 13107, 13108, 52428, 52429])   # 1280 channels: one token below and from 16, 64, 256 MiB on
 def test_large_moves_equal_the_element_path(tdp, tokens, kv_scales):
     lens = [4095] * (tokens // 4095) + [tokens % 4095]
     test_page_moves_equal_the_element_path(tdp, "wide", lens, kv_scales)
