@@ -227,3 +227,28 @@ def test_greedy_tokens_of_the_head_are_those_of_its_logits(M, vocab):
     tdp.tdp_ends_destroy(h)
     lg = logits.cpu().numpy().astype(np.float64)
     assert np.array_equal(toks.cpu().numpy(), E.greedy_tokens(np.where(np.isnan(lg), -np.inf, lg)))
+
+
+@pytest.mark.parametrize("M", [3, 200])
+def test_infinite_logits(M):
+    """The first weight of chosen columns is minus infinity: their logits are minus infinity, infinity or (a zero in the hidden state)
+    NaN by the sign of a row's first element.  All columns of the first half, every third one behind it; in the second vocabulary all."""
+    d, vocab = 64, 4100
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn(M, d, generator=g, device="cuda").to(torch.bfloat16)
+    x[0, 0], x[1, 0], x[2, 0] = 1.0, -1.0, 0.0
+    for columns in (torch.cat([torch.arange(vocab // 2), torch.arange(vocab // 2, vocab, 3)]), torch.arange(vocab)):
+        head = torch.randn(d, vocab, generator=g, device="cuda").to(torch.bfloat16)
+        head[0, columns.cuda()] = -float("inf")
+        h = tdp.tdp_ends_create(tdp.EndsConfig(vocab, d, 1e-5, M))
+        tdp.tdp_ends_set_weight(h, tdp.E_LM_HEAD, head, tdp.BF16, tdp.DEVICE, d, vocab)
+        tdp.tdp_ends_set_weight(h, tdp.E_FINAL_NORM, torch.ones(d, device="cuda"), tdp.F32, tdp.DEVICE, d, 1)
+        logits = torch.empty((M, vocab), dtype=torch.float32, device="cuda")
+        toks = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+        tdp.tdp_lm_head(h, x, M, None, M, logits, toks)
+        torch.cuda.synchronize()
+        tdp.tdp_ends_destroy(h)
+        lg = logits.cpu().numpy().astype(np.float64)
+        up = x[:, 0].float().cpu().numpy() > 0
+        assert np.isneginf(lg[up][:, columns]).all() and np.isnan(lg[2, columns]).all()
+        assert np.array_equal(toks.cpu().numpy(), E.greedy_tokens(np.where(np.isnan(lg), -np.inf, lg)))

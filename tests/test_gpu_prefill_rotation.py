@@ -10,10 +10,16 @@ from stage_helpers import i32
 pytestmark = pytest.mark.gpu
 
 
-# (with 2560 + 1024 columns a last tile of the projection is half padding; M - 1 and odd lengths leave rows of the last tile over)
-@pytest.mark.parametrize("heads,kv_heads,dh,M", [(16, 16, 128, 1407), (20, 4, 128, 2431), (32, 8, 64, 2815), (32, 32, 64, 1500)])
+# Every tile that can rotate is an epilogue of its own.  (With 2560 + 1024 columns a last tile of the projection is half padding; odd
+# lengths leave rows of the last tile over; with 29 heads and with 44 + 11 a wave's two heads of 64 channels are a query and a key, and a
+# key and a value.)
+@pytest.mark.parametrize("heads,kv_heads,dh,M,rows", [
+    (16, 16, 128, 2567, 128), (16, 16, 128, 1407, 160), (16, 16, 128, 1703, 192), (16, 16, 128, 2001, 224), (16, 16, 128, 2505, 256),
+    (20, 4, 128, 2431, 160), (32, 8, 64, 2815, 160), (32, 32, 64, 1500, 160),
+    (44, 11, 64, 1823, 128), (29, 29, 64, 1501, 160), (44, 11, 64, 2503, 192), (29, 29, 64, 2203, 224), (44, 11, 64, 3407, 256),
+])
 @pytest.mark.parametrize("bias", [False, True])
-def test_both_places_give_the_same_bits(heads, kv_heads, dh, M, bias):
+def test_both_places_give_the_same_bits(heads, kv_heads, dh, M, rows, bias):
     """One layer in which every sum is exact: inputs of +-1 with rms_eps = 0, weights and biases in 16ths, the output projection the
     identity, no MLP.  The first prompts have to come out of a large call as they do out of a small one."""
     from paper_2506_10470_amd import tdp
@@ -23,6 +29,7 @@ def test_both_places_give_the_same_bits(heads, kv_heads, dh, M, bias):
     n_qkv = -(-(d + 2 * dkv) // 256) * 256
     ways = [tdp.tdp_gemm_plan(m, n_qkv, d, 0, True, min(8 * 512 * max(n_qkv, d), 64 << 20)) for m in (first, M)]
     assert [p["splits"] == 1 and p["weight_rows"] == 256 for p in ways] == [False, True], ways
+    assert ways[1]["rows"] == rows, ways
     rest = M - first
     all_lens = np.concatenate([lens, np.full(rest // 333, 333), [rest % 333]])
     g = torch.Generator(device="cuda").manual_seed(M)
