@@ -322,7 +322,9 @@ TDP_API int tdp_probe_mfma_bf16(int32_t iters, int32_t launches, int32_t random_
  * gemm_down, attention_merge) into ms[8].  "attention" is the attention kernel (prefill or
  * decode).  The partial results of decode requests longer than one span are combined inside it, or, for
  * large batches of long contexts, by a kernel behind it, whose class is "attention_merge" (0 otherwise).  It also
- * rotates and appends in small decode batches: "rope_kv" is 0 there.
+ * rotates and appends in small decode batches: "rope_kv" is 0 there.  In a prefill whose QKV projection is made
+ * unsplit in tiles of 256 weight rows, on a 16-bit cache, queries and keys are rotated and keys appended by the
+ * projection, within "gemm_qkv"; "rope_kv" is then the append of the values alone.
  */
 TDP_API int tdp_stage_timing_enable(tdp_stage* st, int32_t on);
 TDP_API int tdp_stage_timing_read(tdp_stage* st, float* ms /* host [8] */);

@@ -747,6 +747,9 @@ hipError_t gemm_setup() {
 // 256 x 128 tiles unsplit where 256 x 256 in two splits are faster (with the rotation 79.2 + 51.2 us against 70.5 + 51.9); Qwen at
 // 512 rows 56.0 + 16.9 against 45.3 + 17.8, 70B at 384 rows 87.1 + 15.8 against 67.5 + 18.4.  Over 264 cases with M from 129 to
 // 16384 the choice was 2.5 % slower than the fastest, now 0.2 %.
+// (These costs are of the projection with a rotation kernel behind it.  An unsplit tile of 256 weight rows of a 16-bit prefill stores no
+// fp32 and has none, see gemm_can_rotate; the plan, which decode and 8-bit caches share, does not count that in, so it can keep a split
+// or a tile of 128 weight rows where rotating in the epilogue would be a little ahead.)
 static double plan_cost(const TileInfo& ti, int64_t M, int64_t Npad, int per, int splits, int epilogue, bool defer,
                         bool rotated) {
   const double tm = (double)((M + ti.bm() - 1) / ti.bm()), tn = (double)(Npad / ti.bn());
