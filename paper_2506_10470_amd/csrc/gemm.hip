@@ -167,8 +167,8 @@ __device__ __forceinline__ void gemm_epilogue16_max(const GemmMaxParams& p, f32x
 // their slots.  A wave's columns are whole heads (16 WT = 128: one of 128 channels or two of 64), so a lane holds both channels of
 // its pairs: tile t of a head and tile t + H, H = head_dim / 32.  Bound: the stores, and two look-ups in a row (a token's position,
 // then its (cos, sin)), asked for two row blocks at a time.  Against
-// an fp32 projection that a kernel of its own reads back (19346 tokens of 70B: 2302 + 216 us; 7959 of 7B: 708 + 123; 6713 of Qwen: 460 +
-// 52) the projection is no longer: 2289, 693, 434.
+// an fp32 projection that a kernel of its own reads back (19346 tokens of 70B: 2364 + 219 us; 7959 of 7B: 705 + 128; 6713 of Qwen: 467 +
+// 52) the projection is no longer: 2325, 711, 441.
 template <int AT, int WT, int H>
 __device__ __forceinline__ void gemm_epilogue16_rotate(const GemmRotateParams& p, f32x4 (&acc)[WT][AT], int row0, int col0,
                                                        int l16, int kq) {
