@@ -971,6 +971,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
   load_block(0);
   look_up(64);
   settle(0, 0);
+  // The queries have arrived as well.  Used here, they are waited for here; left to the loop, each of its turns waits for them again, and so for
+  // the requests of the next block, which are behind them in the same counter.
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
   for (int kb0 = 0, buf = 0; kb0 < kv_end; kb0 += 64, buf ^= 1) {
     const bool more = kb0 + 64 < kv_end;
     if (more) load_block(buf ^ 1);

@@ -88,3 +88,22 @@ def test_no_two_cache_moves_are_the_same_code(code_objects):
             code[m.group(3)] = data[at:at + int(m.group(2))]
     assert len(code) >= 8
     assert len(set(code.values())) == len(code), sorted(code)
+
+
+def test_prefill_attention_does_not_wait_for_the_next_block_early(code_objects):
+    """16-bit pools: a block is requested straight into LDS while the one before it is computed.  The only wait for memory between the
+    requests and the barrier behind that block is the one in front of the barrier; any other drains the same counter."""
+    tool = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    seen = 0
+    for path in code_objects:
+        if b"attn_prefill_kernel" not in path.read_bytes():
+            continue
+        text = subprocess.run([tool, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        for m in re.finditer(r"^\w+ <\S*attn_prefill_kernel\S*ELb0E\S*>:\n(.*?)(?=^\w+ <|\Z)", text, re.M | re.S):
+            lines = m.group(1).splitlines()
+            last = max(i for i, l in enumerate(lines) if "global_load_lds" in l)
+            barrier = next(i for i in range(last, len(lines)) if "s_barrier" in lines[i])
+            waits = [l.strip() for l in lines[last:barrier] if "s_waitcnt" in l and "vmcnt" in l]
+            assert len(waits) == 1 and "vmcnt(0)" in waits[0], waits
+            seen += 1
+    assert seen == 2
